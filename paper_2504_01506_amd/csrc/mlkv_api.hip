@@ -261,8 +261,6 @@ int check_table(mlkv_table* t) {
   return MLKV_OK;
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 RowStore store_of(const mlkv_table* t) {
   RowStore s;
   s.rows = t->rows;
@@ -544,10 +542,6 @@ GetArgs get_args(mlkv_table* t, const uint64_t* d_keys, int64_t n, float* d_out,
   return a;
 }
 
-bool get_vec4(const mlkv_table* t, const float* d_out) {
-  return (t->dim % 4 == 0) && (d_out == nullptr || aligned16(d_out));
-}
-
 // The table's state after a get call was queued.
 void get_done(mlkv_table* t, bool count, bool fixed) {
   if (!fixed) {
@@ -570,7 +564,7 @@ int get_call(mlkv_table* t, const uint64_t* d_keys, int64_t n, float* d_out, uin
   if (fixed == nullptr && (rc = ensure_workspace(t, n, static_cast<hipStream_t>(hip_stream))) != MLKV_OK)
     return rc;
   const GetArgs a = get_args(t, d_keys, n, d_out, d_blocked, count, fixed);
-  hipError_t e = launch_get(a, get_vec4(t, d_out), static_cast<hipStream_t>(hip_stream),
+  hipError_t e = launch_get(a, static_cast<hipStream_t>(hip_stream),
                             fixed ? LaunchHook{} : hook_of(t));
   if (e != hipSuccess) return hip_fail(e, "mlkv_get launch");
   get_done(t, count, fixed != nullptr);
@@ -774,8 +768,7 @@ int put_call(mlkv_table* t, const uint64_t* d_keys, const float* src, int64_t n,
   if ((rc = check_put(t, d_keys, src, n, op, lr, eps)) != MLKV_OK || n == 0) return rc;
   if ((rc = ensure_workspace(t, n, static_cast<hipStream_t>(hip_stream))) != MLKV_OK) return rc;
   const PutArgs a = put_args(t, d_keys, src, n, op, lr, eps);
-  const bool vec4 = (t->dim % 4 == 0) && aligned16(src);
-  hipError_t e = launch_put(a, vec4, static_cast<hipStream_t>(hip_stream), hook_of(t));
+  hipError_t e = launch_put(a, static_cast<hipStream_t>(hip_stream), hook_of(t));
   if (e != hipSuccess) return hip_fail(e, "put launch");
   t->epoch++;
   return MLKV_OK;
@@ -824,12 +817,11 @@ int mlkv_get_put_grad(mlkv_table* t, const uint64_t* d_get_keys, int64_t n_get, 
   GetArgs g = get_args(t, d_get_keys, n_get, d_out, d_blocked, true, nullptr);
   g.xkey = t->mid_xkey;
   g.xslot = t->mid_xslot;
-  const bool pvec4 = (t->dim % 4 == 0) && aligned16(d_grads);
   const LaunchHook hook = hook_of(t);
-  e = launch_put(p, pvec4, st, hook, kPutProbe);
-  if (e == hipSuccess) e = launch_get(g, get_vec4(t, d_out), st, hook);
+  e = launch_put(p, st, hook, kPutProbe);
+  if (e == hipSuccess) e = launch_get(g, st, hook);
   if (e == hipSuccess && done != nullptr) e = hipEventRecord(done, st);
-  if (e == hipSuccess) e = launch_put(p, pvec4, st, hook, kPutAfterProbe);
+  if (e == hipSuccess) e = launch_put(p, st, hook, kPutAfterProbe);
   if (e != hipSuccess) return hip_fail(e, "mlkv_get_put_grad launch");
   get_done(t, true, false);
   t->epoch++;  // the put

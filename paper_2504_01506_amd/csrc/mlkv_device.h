@@ -331,14 +331,30 @@ __device__ __forceinline__ void block_bitonic_sort(P a, uint32_t N) {
 // ---------------------------------------------------------------------------
 // Lane <-> row-element mapping. A wave is split into RPW = 64/LPR lane groups;
 // a group of LPR lanes covers one row, VEC consecutive floats per lane per
-// chunk, K chunks: column of (chunk k, element v) = (k*LPR + q)*VEC + v.
+// chunk, K chunks: lane q's floats of chunk k start at column (k*LPR + q)*VEC.
+// Rows may start at any 4-byte boundary (a width that is no multiple of four,
+// a caller's buffer): the 16-byte accesses below are declared 4-byte aligned.
+// Where the last floats of a row do not fill a lane (VEC = 4), that lane moves
+// back to the row's last four columns; the first twice() of its floats are
+// then its neighbour's too. Both lanes compute the same values for them and
+// store them alike; only sums over a row's columns must take them once.
 // ---------------------------------------------------------------------------
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int VEC_, int LPR_, int K_>
 struct RowMap {
   static constexpr int VEC = VEC_;
   static constexpr int LPR = LPR_;
   static constexpr int K = K_;
   static constexpr int RPW = 64 / LPR_;
+  static __device__ __forceinline__ bool on(int k, int q, int D) { return (k * LPR + q) * VEC < D; }
+  static __device__ __forceinline__ int col(int k, int q, int D) {
+    const int c = (k * LPR + q) * VEC;
+    return VEC == 1 || c < D - VEC ? c : D - VEC;
+  }
+  static __device__ __forceinline__ int twice(int k, int q, int D) {
+    return VEC == 1 ? 0 : (k * LPR + q) * VEC - col(k, q, D);
+  }
 };
 
 template <int VEC>

@@ -200,9 +200,51 @@ struct TierArgs {
   Ctrl* ctrl;
 };
 
-hipError_t launch_get(const GetArgs& a, bool vec4, hipStream_t st, const LaunchHook& hook);
+// Row maps: the fewest lanes that cover a row, four floats each (one float
+// each for rows shorter than that), at any alignment. A map of one float per
+// lane and a whole wave per row, which widths that are no multiple of four
+// (and buffers off 16 bytes) took before, left most lanes idle: two steps of
+// 106,496 lookups at dim 10 took 849 us and take 137. Rows of 4 floats on one
+// lane instead of four (three of them idle): two steps of the 2^20-operation
+// key-value mix 161.7 -> 159.6 us.
+using MapD1 = RowMap<1, 1, 1>;      // dim 1
+using MapD2 = RowMap<1, 2, 1>;      // dim 2
+using MapD3 = RowMap<1, 4, 1>;      // dim 3
+using MapD4 = RowMap<4, 1, 1>;      // dim 4
+using MapD8 = RowMap<4, 2, 1>;      // dim <= 8
+using MapD16 = RowMap<4, 4, 1>;     // dim <= 16
+using MapD32 = RowMap<4, 8, 1>;     // dim <= 32
+using MapD64 = RowMap<4, 16, 1>;    // dim <= 64
+using MapD128 = RowMap<4, 32, 1>;   // dim <= 128
+using MapD256 = RowMap<4, 64, 1>;   // dim <= 256
+using MapD512 = RowMap<4, 64, 2>;   // dim <= 512
+using MapD1024 = RowMap<4, 64, 4>;  // dim <= 1024
+#define MLKV_MAPS(F)                                                                                             \
+  F(MapD1) F(MapD2) F(MapD3) F(MapD4) F(MapD8) F(MapD16) F(MapD32) F(MapD64) F(MapD128) F(MapD256) F(MapD512) \
+  F(MapD1024)
+
+// The items a radix tile reads. First pass: put_probe's items, tile t being
+// put tiles 4t .. 4t+3, kPutTile slots each, the first (meta >> 16) of them
+// used. Later passes: the dense output of the previous pass.
+struct RsSrc {
+  const uint64_t* src;
+  const uint32_t* meta;   // first pass only
+  int ntiles;             // put tiles
+  const uint32_t* total;  // later passes: items in all
+};
+
+hipError_t launch_assign(const GetArgs& a, int ntiles, int tlen, int grid, const RangeLists& rl, hipStream_t st,
+                         const LaunchHook& hook);
+hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits, uint32_t* cnt, int rtiles,
+                             int stride, uint64_t* dst, uint32_t* total_out, hipStream_t st,
+                             const LaunchHook& hook);
+template <class M>
+hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHook& hook);
+template <class M>
+hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase);
+hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_tier_lookahead(const TierArgs& a, hipStream_t st, const LaunchHook& hook);
-hipError_t launch_put(const PutArgs& a, bool vec4, hipStream_t st, const LaunchHook& hook, int phase = kPutAll);
+hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase = kPutAll);
 hipError_t launch_lookup(Bucket* idx, uint32_t nb_log2, const uint64_t* keys, int64_t n,
                          int64_t* rows_out, hipStream_t st);
 hipError_t launch_export_slots(const Bucket* idx, uint64_t nslots, uint64_t* keys_out,

@@ -1,6 +1,10 @@
 // HIP kernels of libmlkv for gfx950 (MI355X): hash-index probe, row gather,
 // in-batch dedup by MSD radix partition + LDS sort + run-length encoding, and
 // the fp64 segment-reduce fused with the row-wise Adagrad scatter-update.
+//
+// The kernels that move rows are templates over a row map. This file is
+// compiled once for each map M with MLKV_MAP=M (that map's kernels and their
+// launchers) and once without (the other kernels, and the choice of a map).
 #include "mlkv_kernels.h"
 
 #include <type_traits>
@@ -13,7 +17,8 @@ namespace mlkv {
 template <int VEC>
 __device__ __forceinline__ typename VecT<VEC>::T load_vec(const float* p) {
   if constexpr (VEC == 4) {
-    return *reinterpret_cast<const float4*>(p);
+    const Words4 v = *reinterpret_cast<const Words4*>(p);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
   } else {
     return *p;
   }
@@ -22,7 +27,8 @@ __device__ __forceinline__ typename VecT<VEC>::T load_vec(const float* p) {
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const typename VecT<VEC>::T& v) {
   if constexpr (VEC == 4) {
-    *reinterpret_cast<float4*>(p) = v;
+    *reinterpret_cast<Words4*>(p) =
+        Words4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
   } else {
     *p = v;
   }
@@ -86,10 +92,10 @@ __device__ __forceinline__ void wave_emit_rows(float* __restrict__ out, const Ro
       const uint32_t rr = __shfl(row, r, 64);
       const int hh = __shfl(how, r, 64);
       const uint64_t ss = __shfl((unsigned long long)s0, r, 64);
-      const int col = (k * LPR + q) * VEC;
+      const int col = M::col(k, q, D);
       const int64_t p = wave_base + r;
       if constexpr (kTrack) skip |= (hh == 2 ? 1u : 0u) << u;
-      if (uu < UNITS && p < n && col < D) {
+      if (uu < UNITS && p < n && M::on(k, q, D)) {
         if (hh == 1) v[u] = load_vec<VEC>(store.ptr(rr) + col);
         else if (hh == 0) v[u] = init_vec<VEC>(ss, col);
       }
@@ -100,9 +106,9 @@ __device__ __forceinline__ void wave_emit_rows(float* __restrict__ out, const Ro
       const int it = uu / K;
       const int k = uu % K;
       const int r = it * RPW + g;
-      const int col = (k * LPR + q) * VEC;
+      const int col = M::col(k, q, D);
       const int64_t p = wave_base + r;
-      if (uu < UNITS && p < n && col < D && (!kTrack || !((skip >> u) & 1u)))
+      if (uu < UNITS && p < n && M::on(k, q, D) && (!kTrack || !((skip >> u) & 1u)))
         store_vec<VEC>(out + (size_t)p * (size_t)D + col, v[u]);
     }
   }
@@ -466,6 +472,7 @@ __device__ __forceinline__ void write_new_rows(const KP ks, const SP sl, const R
   write_init_rows<NT>(ks, rk, m, base, store, D, seed);
 }
 
+#ifndef MLKV_MAP
 __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
     Bucket* __restrict__ idx, const NewKey* __restrict__ newlist, const uint32_t* __restrict__ tile_cnt,
     int ntiles, int tile_size, const RowStore store, float* __restrict__ state, int D,
@@ -822,6 +829,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
     __syncthreads();
   }
 }
+#endif  // MLKV_MAP
 
 // ===========================================================================
 // Put. The (key, position) pairs of a call flow through "items":
@@ -1058,10 +1066,10 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
     double* dst = partials + (size_t)(base + s_lanes[entry]) * (size_t)D;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
+      const int col = M::col(k, q, D);
 #pragma unroll
       for (int v = 0; v < VEC; ++v)
-        if (col + v < D) dst[col + v] = acc[k][v];
+        if (M::on(k, q, D)) dst[col + v] = acc[k][v];
     }
   };
   if (op != kOpAssign) {
@@ -1090,8 +1098,8 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
             const float* gr = grads + (size_t)(base + s_lanes[j + u]) * (size_t)D;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const int col = (k * LPR + q) * VEC;
-              if (col < D) gv[u][k] = load_vec<VEC>(gr + col);
+              const int col = M::col(k, q, D);
+              if (M::on(k, q, D)) gv[u][k] = load_vec<VEC>(gr + col);
             }
           }
         }
@@ -1100,8 +1108,7 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
           if (j + u < e) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const int col = (k * LPR + q) * VEC;
-              if (col < D) {
+              if (M::on(k, q, D)) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) acc[k][v] += (double)VecT<VEC>::get(gv[u][k], v);
               }
@@ -1222,10 +1229,10 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
         const double* src = partials + (size_t)(base + s_lanes[b == kb ? kb + 1 : b]) * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
+          const int col = M::col(k, q, D);
 #pragma unroll
           for (int v = 0; v < VEC; ++v)
-            if (col + v < D) acc[k][v] += src[col + v];
+            if (M::on(k, q, D)) acc[k][v] += src[col + v];
         }
       }
       store_row(kb);
@@ -1275,11 +1282,10 @@ struct SegmentOps {
     double sq = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
 #pragma unroll
       for (int x = 0; x < VEC; ++x) {
         const double gx = (double)VecT<VEC>::get(g[k], x);
-        if (col + x < D) sq += gx * gx;
+        if (M::on(k, q, D) && x >= M::twice(k, q, D)) sq += gx * gx;
       }
     }
     sq = group_sum<LPR>(sq);
@@ -1292,8 +1298,8 @@ struct SegmentOps {
     // quotients give the same infinities and NaNs as a plain fp32 division
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
-      if (col < D) {
+      const int col = M::col(k, q, D);
+      if (M::on(k, q, D)) {
 #pragma unroll
         for (int x = 0; x < VEC; ++x) {
           const float gx = VecT<VEC>::get(g[k], x);
@@ -1312,8 +1318,8 @@ struct SegmentOps {
                                              float lr) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
-      if (col < D) {
+      const int col = M::col(k, q, D);
+      if (M::on(k, q, D)) {
 #pragma unroll
         for (int x = 0; x < VEC; ++x)
           VecT<VEC>::set(w[k], x, __fsub_rn(VecT<VEC>::get(w[k], x), __fmul_rn(lr, VecT<VEC>::get(g[k], x))));
@@ -1326,8 +1332,8 @@ struct SegmentOps {
   static __device__ __forceinline__ void assign(const V (&g)[K], float* __restrict__ wrow, int D, int q) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
-      if (col < D) store_vec<VEC>(wrow + col, g[k]);
+      const int col = M::col(k, q, D);
+      if (M::on(k, q, D)) store_vec<VEC>(wrow + col, g[k]);
     }
   }
 
@@ -1356,8 +1362,8 @@ struct SegmentOps {
     float* gp = reinterpret_cast<float*>(const_cast<double*>(partials) + (size_t)pos * (size_t)D);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
-      if (col < D) {
+      const int col = M::col(k, q, D);
+      if (M::on(k, q, D)) {
         V v;
 #pragma unroll
         for (int x = 0; x < VEC; ++x) VecT<VEC>::set(v, x, (float)acc[k][x]);
@@ -1553,17 +1559,17 @@ __device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA,
             const double* pr = c.partials + (size_t)item_pos(x) * (size_t)D;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const int col = (k * LPR + q) * VEC;
+              const int col = M::col(k, q, D);
 #pragma unroll
               for (int v = 0; v < VEC; ++v)
-                if (col + v < D) pv[u][k][v] = pr[col + v];
+                if (M::on(k, q, D)) pv[u][k][v] = pr[col + v];
             }
           } else {
             const float* gr = c.grads + (size_t)item_pos(x) * (size_t)D;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const int col = (k * LPR + q) * VEC;
-              if (col < D) gv[u][k] = load_vec<VEC>(gr + col);
+              const int col = M::col(k, q, D);
+              if (M::on(k, q, D)) gv[u][k] = load_vec<VEC>(gr + col);
             }
           }
         }
@@ -1574,8 +1580,7 @@ __device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA,
       if (!use[u]) continue;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const int col = (k * LPR + q) * VEC;
-        if (col < D) {
+        if (M::on(k, q, D)) {
 #pragma unroll
           for (int x = 0; x < VEC; ++x)
             acc[k][x] += summ[u] ? pv[u][k][x] : (double)VecT<VEC>::get(gv[u][k], x);
@@ -1587,10 +1592,10 @@ __device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA,
         } else {
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const int col = (k * LPR + q) * VEC;
+            const int col = M::col(k, q, D);
 #pragma unroll
             for (int x = 0; x < VEC; ++x)
-              if (col + x < D) s_part[(size_t)gid * D + col + x] = acc[k][x];
+              if (M::on(k, q, D)) s_part[(size_t)gid * D + col + x] = acc[k][x];
           }
         }
         Ops::zero(acc);
@@ -1607,10 +1612,10 @@ __device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA,
       } else {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
+          const int col = M::col(k, q, D);
 #pragma unroll
           for (int x = 0; x < VEC; ++x)
-            if (col + x < D) s_part[(size_t)gid * D + col + x] = acc[k][x];
+            if (M::on(k, q, D)) s_part[(size_t)gid * D + col + x] = acc[k][x];
         }
       }
     }
@@ -1621,10 +1626,10 @@ __device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA,
     for (uint32_t h = gid + 1; h < (uint32_t)NG && h * L < end; ++h) {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const int col = (k * LPR + q) * VEC;
+        const int col = M::col(k, q, D);
 #pragma unroll
         for (int x = 0; x < VEC; ++x)
-          if (col + x < D) acc[k][x] += s_part[(size_t)h * D + col + x];
+          if (M::on(k, q, D)) acc[k][x] += s_part[(size_t)h * D + col + x];
       }
     }
     Ops::store_g(acc, c.partials, item_pos(it[seg[tail]]), D, q);
@@ -1671,8 +1676,8 @@ __device__ __forceinline__ void update_segments(IP it, SP seg, uint32_t S, const
                                   : c.grads + (size_t)pos * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
-          if (col < D) {
+          const int col = M::col(k, q, D);
+          if (M::on(k, q, D)) {
             gf[u][k] = load_vec<VEC>(src + col);
             w[u][k] = load_vec<VEC>(c.store.ptr(row[u]) + col);
           }
@@ -1713,7 +1718,7 @@ struct ReduceCfg {
 };
 
 constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-constexpr int kMaxGroups = 256;  // lane groups of a reduce block at most
+constexpr int kMaxGroups = 1024;  // lane groups of a reduce block at most
 // Segments of more than kLongSeg items are put in order through a bitmask of
 // their items' places in the gathered list (at most kMaskSegs of them per
 // partition; others compare their items pairwise).
@@ -1927,7 +1932,7 @@ template <int VEC>
 struct RawRow;
 template <>
 struct RawRow<4> {
-  uint4 lo, hi;
+  Words4 lo, hi;
 };
 template <>
 struct RawRow<1> {
@@ -1939,11 +1944,11 @@ __device__ __forceinline__ void load_raw(RawRow<VEC>& r, const float* __restrict
                                          const double* __restrict__ partials, size_t off, bool summed) {
   if constexpr (VEC == 4) {
     if (summed) {
-      const uint4* p = reinterpret_cast<const uint4*>(partials + off);
+      const Words4* p = reinterpret_cast<const Words4*>(partials + off);
       r.lo = p[0];
       r.hi = p[1];
     } else {
-      r.lo = *reinterpret_cast<const uint4*>(grads + off);
+      r.lo = *reinterpret_cast<const Words4*>(grads + off);
     }
   } else {
     if (summed) r.lo = *reinterpret_cast<const uint2*>(partials + off);
@@ -1978,7 +1983,7 @@ template <class M, int N, bool kClk>
 __device__ __forceinline__ void update_rows(const bool (&on)[N], const uint32_t (&rw)[N],
                                             const typename VecT<M::VEC>::T (&gq)[N][M::K], const RedCtx& c, int q,
                                             bool d_pow2, double inv_d) {
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K;
+  constexpr int VEC = M::VEC, K = M::K;
   using V = typename VecT<VEC>::T;
   const int D = c.D;
   V w[N][K];
@@ -1995,8 +2000,8 @@ __device__ __forceinline__ void update_rows(const bool (&on)[N], const uint32_t 
       wr[u] = c.store.wptr(rw[u]);
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const int col = (k * LPR + q) * VEC;
-        if (col < D) w[u][k] = load_vec<VEC>(wr[u] + col);
+        const int col = M::col(k, q, D);
+        if (M::on(k, q, D)) w[u][k] = load_vec<VEC>(wr[u] + col);
       }
       if (c.op == kOpAdagrad) G[u] = c.state[rw[u]];
       if (clk) cl[u] = clock_low(c.clock, rw[u]);
@@ -2045,10 +2050,10 @@ __device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32
     double* dst = s_piece + (size_t)gid * DMAX;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int col = (k * LPR + q) * VEC;
+      const int col = M::col(k, q, D);
 #pragma unroll
       for (int x = 0; x < VEC; ++x)
-        if (col + x < D) dst[col + x] = a[k][x];
+        if (M::on(k, q, D)) dst[col + x] = a[k][x];
     }
   };
   auto to_f32 = [&](V (&g)[K], const double (&a)[K][VEC]) {
@@ -2096,16 +2101,16 @@ __device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32
         const size_t base = (size_t)item_pos(x[u]) * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
-          if (col < D) load_raw<VEC>(raw[u][k], c.grads, c.partials, base + col, summ);
+          const int col = M::col(k, q, D);
+          if (M::on(k, q, D)) load_raw<VEC>(raw[u][k], c.grads, c.partials, base + col, summ);
         }
         if (fst[u] == j && j >= lo) {  // an owned segment starts: its row (the first item carries it)
           const uint32_t r = item_tag(x[u]);
           wp[u] = c.store.wptr(r);
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const int col = (k * LPR + q) * VEC;
-            if (col < D) wl[u][k] = load_vec<VEC>(wp[u] + col);
+            const int col = M::col(k, q, D);
+            if (M::on(k, q, D)) wl[u][k] = load_vec<VEC>(wp[u] + col);
           }
           if (c.op == kOpAdagrad) Gl[u] = c.state[r];
           if (clk) Cl[u] = clock_low(c.clock, r);
@@ -2127,8 +2132,7 @@ __device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32
         const bool summ = item_summed(x[u]);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
-          if (col < D) add_raw<VEC>(acc[k], raw[u][k], summ);
+          if (M::on(k, q, D)) add_raw<VEC>(acc[k], raw[u][k], summ);
         }
         last_ends = end[u] == j + 1;
         last_owned = fst[u] >= lo;
@@ -2169,8 +2173,8 @@ __device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32
           const float* gr = c.grads + (size_t)item_pos(xs) * (size_t)D;
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const int col = (k * LPR + q) * VEC;
-            if (col < D) gq[u][k] = load_vec<VEC>(gr + col);
+            const int col = M::col(k, q, D);
+            if (M::on(k, q, D)) gq[u][k] = load_vec<VEC>(gr + col);
           }
         }
       }
@@ -2189,10 +2193,10 @@ __device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32
       const double* src = s_piece + (size_t)h * DMAX;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const int col = (k * LPR + q) * VEC;
+        const int col = M::col(k, q, D);
 #pragma unroll
         for (int xx = 0; xx < VEC; ++xx)
-          if (col + xx < D) acc[k][xx] += src[col + xx];
+          if (M::on(k, q, D)) acc[k][xx] += src[col + xx];
       }
     }
     V g[K];
@@ -2266,8 +2270,8 @@ __device__ __forceinline__ void upsert_last(const uint64_t* __restrict__ it, uin
         const float* src = c.grads + (size_t)(s_last[h] - 1u) * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
-          if (col < D) v[u][k] = load_vec<VEC>(src + col);
+          const int col = M::col(k, q, D);
+          if (M::on(k, q, D)) v[u][k] = load_vec<VEC>(src + col);
         }
         if (clk) cl[u] = clock_low(c.clock, rw[u]);
       }
@@ -2306,8 +2310,8 @@ __device__ __forceinline__ void assign_segments(const uint64_t* srt, const uint3
         const float* src = c.grads + (size_t)item_pos(srt[seg[s + 1] - 1]) * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-          const int col = (k * LPR + q) * VEC;
-          if (col < D) v[u][k] = load_vec<VEC>(src + col);
+          const int col = M::col(k, q, D);
+          if (M::on(k, q, D)) v[u][k] = load_vec<VEC>(src + col);
         }
         if (clk) cl[u] = clock_low(c.clock, rw[u]);
       }
@@ -2523,16 +2527,6 @@ __device__ __forceinline__ uint32_t rs_key(uint64_t x, uint32_t cap) {
   return item_fresh(x) ? cap + item_tag(x) : item_tag(x);
 }
 
-// The items a radix tile reads. First pass: put_probe's items, tile t being
-// put tiles 4t .. 4t+3, kPutTile slots each, the first (meta >> 16) of them
-// used. Later passes: the dense output of the previous pass.
-struct RsSrc {
-  const uint64_t* src;
-  const uint32_t* meta;   // first pass only
-  int ntiles;             // put tiles
-  const uint32_t* total;  // later passes: items in all
-};
-
 // Loads the tile's items: v[k] = item of element k * kRsThreads + tid, ok[k]
 // whether it exists.
 __device__ __forceinline__ void rs_load(const RsSrc& s, uint64_t (&v)[kRsPer], bool (&ok)[kRsPer]) {
@@ -2551,6 +2545,7 @@ __device__ __forceinline__ void rs_load(const RsSrc& s, uint64_t (&v)[kRsPer], b
   }
 }
 
+#ifndef MLKV_MAP
 // Digit counts of one radix tile: cnt[d * stride + tile], digit-major, so that
 // a digit's counts over the tiles are contiguous (stride >= tiles, a multiple of 4).
 __global__ __launch_bounds__(kRsThreads) void k_rsort_count(RsSrc s, uint32_t cap, int shift, int bits,
@@ -2642,6 +2637,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rsort_scatter(RsSrc s, uint32_t 
     __syncthreads();  // before the table is cleared again
   }
 }
+#endif  // MLKV_MAP
 
 // Cut point of the sorted items at or after p: the first position q >= p
 // where a key's run starts (q = T if none).
@@ -2812,6 +2808,7 @@ __global__ __launch_bounds__(NT) void k_rsort_reduce(
   else sum_and_update<M, NT, kClk>(s_srt, s_seg, s_sid, S, SA, MA, c, s_piece, s_slo);
 }
 
+#ifndef MLKV_MAP
 // ===========================================================================
 // Inspection kernels
 // ===========================================================================
@@ -2873,12 +2870,42 @@ __global__ __launch_bounds__(256) void k_read_clock(const unsigned long long* __
     out[i] = ok ? (uint32_t)(clock[r] & kClockCount) : 0xFFFFFFFFu;
   }
 }
+#endif  // MLKV_MAP
 
 // ===========================================================================
 // Launchers
 // ===========================================================================
+#ifndef MLKV_MAP
+hipError_t launch_assign(const GetArgs& a, int ntiles, int tlen, int grid, const RangeLists& rl, hipStream_t st,
+                         const LaunchHook& hook) {
+  hook(K_ASSIGN_NEW, 0, st);
+  hipLaunchKernelGGL(k_assign_new, dim3(grid), dim3(kAssignThreads), 0, st, a.idx, a.newlist, a.tile_cnt, ntiles,
+                     tlen, a.store, a.state, a.D, a.seed, a.capacity, a.ctrl, a.epoch, a.xkey, a.xslot, a.clock,
+                     a.cepoch, rl);
+  hook(K_ASSIGN_NEW, 1, st);
+  return hipGetLastError();
+}
+
+// One pass of the radix sort: counts, then the scatter by digit.
+hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits, uint32_t* cnt, int rtiles,
+                             int stride, uint64_t* dst, uint32_t* total_out, hipStream_t st,
+                             const LaunchHook& hook) {
+  hook(K_RSORT_COUNT, 0, st);
+  hipLaunchKernelGGL(k_rsort_count, dim3((unsigned)rtiles), dim3(kRsThreads), 0, st, src, cap, shift, bits, cnt,
+                     stride);
+  hook(K_RSORT_COUNT, 1, st);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hook(K_RSORT_SCATTER, 0, st);
+  hipLaunchKernelGGL(k_rsort_scatter, dim3((unsigned)rtiles), dim3(kRsThreads), 0, st, src, cap, shift, bits,
+                     (const uint32_t*)cnt, rtiles, stride, dst, total_out);
+  hook(K_RSORT_SCATTER, 1, st);
+  return hipGetLastError();
+}
+#endif  // MLKV_MAP
+
 template <class M>
-static hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
+hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
   const int tlen = get_tile_len(a.n, a.cus);
   const int64_t ntiles = (a.n + tlen - 1) / tlen;
   const int grid = (int)std::min<int64_t>(ntiles, kMaxRanges);  // row assignment: one block per key range
@@ -2893,12 +2920,7 @@ static hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHoo
   hook(K_GET_PROBE_GATHER, 1, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hook(K_ASSIGN_NEW, 0, st);
-  hipLaunchKernelGGL(k_assign_new, dim3(grid), dim3(kAssignThreads), 0, st, a.idx, a.newlist,
-                     a.tile_cnt, (int)ntiles, tlen, a.store, a.state, a.D, a.seed, a.capacity,
-                     a.ctrl, a.epoch, a.xkey, a.xslot, a.clock, a.cepoch, rl);
-  hook(K_ASSIGN_NEW, 1, st);
-  return hipGetLastError();
+  return launch_assign(a, (int)ntiles, tlen, grid, rl, st, hook);
 }
 
 // Lets kernel `f` (an instance of a reduce kernel) use `bytes` of dynamic
@@ -2970,16 +2992,9 @@ static hipError_t launch_put_radix(const PutArgs& a, hipStream_t st, const Launc
     src.meta = p == 0 ? a.meta : nullptr;
     src.ntiles = (int)ntiles;
     src.total = total;
-    hook(K_RSORT_COUNT, 0, st);
-    hipLaunchKernelGGL(k_rsort_count, dim3((unsigned)rtiles), dim3(kRsThreads), 0, st, src, cap, p * bits, bits,
-                       cnt, stride);
-    hook(K_RSORT_COUNT, 1, st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hook(K_RSORT_SCATTER, 0, st);
-    hipLaunchKernelGGL(k_rsort_scatter, dim3((unsigned)rtiles), dim3(kRsThreads), 0, st, src, cap, p * bits, bits,
-                       (const uint32_t*)cnt, rtiles, stride, buf[p & 1], p == 0 ? total : (uint32_t*)nullptr);
-    hook(K_RSORT_SCATTER, 1, st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_rsort_pass(src, cap, p * bits, bits, cnt, rtiles, stride, buf[p & 1],
+                               p == 0 ? total : (uint32_t*)nullptr, st, hook)) != hipSuccess)
+      return e;
   }
   const bool clk = a.clock != nullptr;
   if ((e = clk ? rsort_lds_attr<M, true>() : rsort_lds_attr<M, false>()) != hipSuccess) return e;
@@ -2995,7 +3010,7 @@ static hipError_t launch_put_radix(const PutArgs& a, hipStream_t st, const Launc
 }
 
 template <class M>
-static hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
+hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
   constexpr int NT = ReduceCfg<M>::NT;
   using L = ReduceLds<NT>;
   static_assert((size_t)ReduceCfg<M>::NG * ReduceCfg<M>::DMAX * sizeof(double) <= L::reuse,
@@ -3025,19 +3040,22 @@ static hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHoo
   return hipGetLastError();
 }
 
-// Row maps: float4 lanes when rows are 16-byte aligned multiples of 4 floats.
-using MapD16 = RowMap<4, 4, 1>;     // dim <= 16
-using MapD32 = RowMap<4, 8, 1>;     // dim <= 32
-using MapD64 = RowMap<4, 16, 1>;    // dim <= 64
-using MapD128 = RowMap<4, 32, 1>;   // dim <= 128
-using MapD256 = RowMap<4, 64, 1>;   // dim <= 256
-using MapD512 = RowMap<4, 64, 2>;   // dim <= 512
-using MapD1024 = RowMap<4, 64, 4>;  // dim <= 1024
-using MapAny = RowMap<1, 64, 16>;   // any dim <= 1024, one float per lane
+#ifdef MLKV_MAP
+template hipError_t launch_get_t<MLKV_MAP>(const GetArgs&, hipStream_t, const LaunchHook&);
+template hipError_t launch_put_t<MLKV_MAP>(const PutArgs&, hipStream_t, const LaunchHook&, int);
+#else
+#define MLKV_EXTERN(M)                                                                          \
+  extern template hipError_t launch_get_t<M>(const GetArgs&, hipStream_t, const LaunchHook&);   \
+  extern template hipError_t launch_put_t<M>(const PutArgs&, hipStream_t, const LaunchHook&, int);
+MLKV_MAPS(MLKV_EXTERN)
 
 template <class F>
-static hipError_t dispatch_map(int D, bool vec4, F f) {
-  if (!vec4) return f(MapAny{});
+static hipError_t dispatch_map(int D, F f) {
+  if (D == 1) return f(MapD1{});
+  if (D == 2) return f(MapD2{});
+  if (D == 3) return f(MapD3{});
+  if (D == 4) return f(MapD4{});
+  if (D <= 8) return f(MapD8{});
   if (D <= 16) return f(MapD16{});
   if (D <= 32) return f(MapD32{});
   if (D <= 64) return f(MapD64{});
@@ -3047,12 +3065,12 @@ static hipError_t dispatch_map(int D, bool vec4, F f) {
   return f(MapD1024{});
 }
 
-hipError_t launch_get(const GetArgs& a, bool vec4, hipStream_t st, const LaunchHook& hook) {
-  return dispatch_map(a.D, vec4, [&](auto m) { return launch_get_t<decltype(m)>(a, st, hook); });
+hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
+  return dispatch_map(a.D, [&](auto m) { return launch_get_t<decltype(m)>(a, st, hook); });
 }
 
-hipError_t launch_put(const PutArgs& a, bool vec4, hipStream_t st, const LaunchHook& hook, int phase) {
-  return dispatch_map(a.D, vec4, [&](auto m) { return launch_put_t<decltype(m)>(a, st, hook, phase); });
+hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
+  return dispatch_map(a.D, [&](auto m) { return launch_put_t<decltype(m)>(a, st, hook, phase); });
 }
 
 hipError_t launch_lookup(Bucket* idx, uint32_t nb_log2, const uint64_t* keys, int64_t n, int64_t* rows_out,
@@ -3103,5 +3121,7 @@ hipError_t launch_read_clock(const unsigned long long* clock, const unsigned lon
   hipLaunchKernelGGL(k_read_clock, dim3((unsigned)grid), dim3(256), 0, st, clock, size_now, ids, n, out, ctrl);
   return hipGetLastError();
 }
+
+#endif  // MLKV_MAP
 
 }  // namespace mlkv
