@@ -12,8 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 KERNELS = os.path.join(CSRC, "mlkv_kernels.hip")
 # the row maps of mlkv_kernels.h (MLKV_MAPS), one compilation of mlkv_kernels.hip each, the slowest first
-MAPS = ("MapD1024", "MapD512", "MapD256", "MapD128", "MapD64", "MapD32", "MapD16", "MapD8", "MapD4", "MapD3",
-        "MapD2", "MapD1")
+MAPS = ("MapD1024", "MapD512", "MapD256", "MapD128", "MapD64", "MapD32", "MapD16", "MapD3")
 UNITS = [(KERNELS, m) for m in MAPS] + [(os.path.join(CSRC, f), None)
                                        for f in ("mlkv_kernels.hip", "mlkv_api.hip", "mlkv_tier.hip")]
 LIB = os.path.join(HERE, "libmlkv.so")

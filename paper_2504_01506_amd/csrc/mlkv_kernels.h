@@ -200,18 +200,15 @@ struct TierArgs {
   Ctrl* ctrl;
 };
 
-// Row maps: the fewest lanes that cover a row, four floats each (one float
-// each for rows shorter than that), at any alignment. A map of one float per
-// lane and a whole wave per row, which widths that are no multiple of four
-// (and buffers off 16 bytes) took before, left most lanes idle: two steps of
-// 106,496 lookups at dim 10 took 849 us and take 137. Rows of 4 floats on one
-// lane instead of four (three of them idle): two steps of the 2^20-operation
-// key-value mix 161.7 -> 159.6 us.
-using MapD1 = RowMap<1, 1, 1>;      // dim 1
-using MapD2 = RowMap<1, 2, 1>;      // dim 2
-using MapD3 = RowMap<1, 4, 1>;      // dim 3
-using MapD4 = RowMap<4, 1, 1>;      // dim 4
-using MapD8 = RowMap<4, 2, 1>;      // dim <= 8
+// Row maps: lanes that cover a row, four floats each (one float each for rows
+// shorter than that), at any alignment. A map of one float per lane and a
+// whole wave per row, which widths that are no multiple of four (and buffers
+// off 16 bytes) took before, left most lanes idle: two steps of 106,496
+// lookups at dim 10 took 849 us and take 137. Not fewer than four lanes: with
+// one per row of dim 4 a block has 1024 lane groups, which cut nearly every
+// segment into pieces that one of them adds up (two steps of 194,468 lookups
+// 243 us against 152).
+using MapD3 = RowMap<1, 4, 1>;      // dim <= 3
 using MapD16 = RowMap<4, 4, 1>;     // dim <= 16
 using MapD32 = RowMap<4, 8, 1>;     // dim <= 32
 using MapD64 = RowMap<4, 16, 1>;    // dim <= 64
@@ -219,9 +216,7 @@ using MapD128 = RowMap<4, 32, 1>;   // dim <= 128
 using MapD256 = RowMap<4, 64, 1>;   // dim <= 256
 using MapD512 = RowMap<4, 64, 2>;   // dim <= 512
 using MapD1024 = RowMap<4, 64, 4>;  // dim <= 1024
-#define MLKV_MAPS(F)                                                                                             \
-  F(MapD1) F(MapD2) F(MapD3) F(MapD4) F(MapD8) F(MapD16) F(MapD32) F(MapD64) F(MapD128) F(MapD256) F(MapD512) \
-  F(MapD1024)
+#define MLKV_MAPS(F) F(MapD3) F(MapD16) F(MapD32) F(MapD64) F(MapD128) F(MapD256) F(MapD512) F(MapD1024)
 
 // The items a radix tile reads. First pass: put_probe's items, tile t being
 // put tiles 4t .. 4t+3, kPutTile slots each, the first (meta >> 16) of them

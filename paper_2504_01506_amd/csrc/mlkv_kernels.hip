@@ -1718,7 +1718,7 @@ struct ReduceCfg {
 };
 
 constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-constexpr int kMaxGroups = 1024;  // lane groups of a reduce block at most
+constexpr int kMaxGroups = 256;  // lane groups of a reduce block at most
 // Segments of more than kLongSeg items are put in order through a bitmask of
 // their items' places in the gathered list (at most kMaskSegs of them per
 // partition; others compare their items pairwise).
@@ -3051,11 +3051,7 @@ MLKV_MAPS(MLKV_EXTERN)
 
 template <class F>
 static hipError_t dispatch_map(int D, F f) {
-  if (D == 1) return f(MapD1{});
-  if (D == 2) return f(MapD2{});
-  if (D == 3) return f(MapD3{});
-  if (D == 4) return f(MapD4{});
-  if (D <= 8) return f(MapD8{});
+  if (D <= 3) return f(MapD3{});
   if (D <= 16) return f(MapD16{});
   if (D <= 32) return f(MapD32{});
   if (D <= 64) return f(MapD64{});
