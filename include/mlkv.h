@@ -94,8 +94,8 @@ int mlkv_get(mlkv_table *t, const uint64_t *d_keys, int64_t n, float *d_out, voi
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): mlkv_get
  * with the same results (rows, key -> row, size, errors), that allocates
- * nothing. Its per-call scratch (new-key lists and per-tile counts) lives in
- * a fixed device array of about 1.8 MiB per GPU, part of the library's code
+ * nothing. Its per-call scratch (new-key lists, per-tile counts, rows) lives in
+ * a fixed device array of about 2.1 MiB per GPU, part of the library's code
  * object, which each GPU the library runs on holds until the process ends.
  *   - 0 <= n <= MLKV_NOALLOC_MAX_KEYS; larger n is refused with MLKV_EINVAL.
  *   - Every call on a GPU shares that GPU's array: calls of this function on
@@ -280,8 +280,8 @@ int mlkv_read_rows(mlkv_table *t, const int64_t *d_rows, int64_t n, float *d_row
 int mlkv_read_staleness(mlkv_table *t, const int64_t *d_rows, int64_t n, uint32_t *d_out, void *hip_stream);
 
 /* ---- per-kernel timing (benchmarks) ----
- * The library runs MLKV_NUM_KERNELS kernels: 0 get_probe_gather and
- * 1 assign_new for mlkv_get, mlkv_get_bounded and mlkv_lookahead;
+ * The library runs MLKV_NUM_KERNELS kernels: 0 get_probe and
+ * 1 get_rows for mlkv_get, mlkv_get_bounded and mlkv_lookahead;
  * 2 put_probe and 3 put_reduce for mlkv_put_grad, mlkv_put_grad_sgd and
  * mlkv_put; 4 tier_mark, 5 tier_plan and 6 tier_copy for mlkv_lookahead on a
  * tiered table; with radix dedup (mlkv_set_dedup) a put runs 2 put_probe,

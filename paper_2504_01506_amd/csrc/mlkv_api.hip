@@ -476,13 +476,14 @@ void mlkv_close(mlkv_table* t) {
 namespace {
 
 // Per-call scratch of a get held outside the table (the allocation-free
-// entry point): the new-key lists, the per-tile counts and the key-range
-// overflow lists. Such a get leaves the table's record of found rows alone.
+// entry point): the new-key lists, the per-tile counts, the key-range
+// overflow lists and the positions' rows. Such a get leaves the table's record of found rows alone.
 struct GetScratch {
   NewKey* newlist;
   uint32_t* tile_cnt;
   uint64_t* xkey;
   uint32_t* xslot;
+  uint32_t* pos_row;
 };
 
 // Host-side checks of a get call's arguments (nothing is queued).
@@ -525,7 +526,7 @@ GetArgs get_args(mlkv_table* t, const uint64_t* d_keys, int64_t n, float* d_out,
   a.bound = (uint32_t)std::max<int64_t>(t->bound, 0);
   a.blocked = d_blocked;
   a.pc_key = fixed ? nullptr : t->pc_key;
-  a.pc_row = fixed ? nullptr : t->pc_row;
+  a.pos_row = fixed ? fixed->pos_row : t->pc_row;
   // after a lookahead, the positions of its keys skip the probe (tables
   // without a staleness bound)
   a.pc_in = (!fixed && t->pc_lookahead && a.clock == nullptr) ? 1 : 0;
@@ -573,14 +574,16 @@ int get_call(mlkv_table* t, const uint64_t* d_keys, int64_t n, float* d_out, uin
 
 // ---- scratch of the allocation-free get ----
 // A file-scope device array, one copy per GPU, sized for kNoAllocMaxKeys keys:
-// new-key lists (16 B per key), per-tile counts, key-range lists (12 B per key).
+// new-key lists (16 B per key), per-tile counts, key-range lists (12 B per key),
+// the positions' rows (4 B per key).
 constexpr int64_t kNoAllocMaxKeys = MLKV_NOALLOC_MAX_KEYS;
 constexpr size_t kNaNewlist = 0;
 // a tile's list starts at its first position; the last tile may reach past n
 constexpr size_t kNaTileCnt = kNaNewlist + sizeof(NewKey) * ((size_t)kNoAllocMaxKeys + kGetTile);
 constexpr size_t kNaXkey = kNaTileCnt + 4096;
 constexpr size_t kNaXslot = kNaXkey + sizeof(uint64_t) * (size_t)kNoAllocMaxKeys;
-constexpr size_t kNaBytes = kNaXslot + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
+constexpr size_t kNaRow = kNaXslot + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
+constexpr size_t kNaBytes = kNaRow + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
 static_assert(kNaTileCnt + sizeof(uint32_t) * ((kNoAllocMaxKeys + kGetTileMin - 1) / kGetTileMin) <= kNaXkey,
               "tile counts fit their region");
 
@@ -607,6 +610,7 @@ int noalloc_scratch(int device, GetScratch* out) {
   out->tile_cnt = reinterpret_cast<uint32_t*>(base + kNaTileCnt);
   out->xkey = reinterpret_cast<uint64_t*>(base + kNaXkey);
   out->xslot = reinterpret_cast<uint32_t*>(base + kNaXslot);
+  out->pos_row = reinterpret_cast<uint32_t*>(base + kNaRow);
   return MLKV_OK;
 }
 
@@ -974,7 +978,7 @@ int mlkv_profile_read(mlkv_table* t, double* total_ms, int64_t* launches) {
 }
 
 const char* mlkv_kernel_name(int kernel) {
-  static const char* names[K_COUNT] = {"get_probe_gather", "assign_new", "put_probe", "put_reduce",
+  static const char* names[K_COUNT] = {"get_probe", "get_rows", "put_probe", "put_reduce",
                                        "tier_mark", "tier_plan", "tier_copy", "rsort_count",
                                        "rsort_scatter", "rsort_reduce"};
   return (kernel >= 0 && kernel < K_COUNT) ? names[kernel] : nullptr;

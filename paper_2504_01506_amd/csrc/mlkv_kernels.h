@@ -9,10 +9,10 @@
 
 namespace mlkv {
 
-constexpr int kGetTile = 256;    // keys per probe_gather block at most (one per lane)
+constexpr int kGetTile = 256;    // keys per get_probe block at most (one per lane)
 constexpr int kGetTileMin = 64;  // ... and at least, unless the batch is smaller
 
-// Positions per get_probe_gather block for a batch of n keys on a device of
+// Positions per get_probe block for a batch of n keys on a device of
 // `cus` compute units: the blocks come in whole rounds of one per CU, with
 // equal tiles, so that no CU runs a block more than another.
 inline int get_tile_len(int64_t n, int cus) {
@@ -37,8 +37,8 @@ constexpr int kErrAbsent = -5;
 
 // Kernels of the library, for per-launch timing.
 enum KernelId : int {
-  K_GET_PROBE_GATHER = 0,
-  K_ASSIGN_NEW = 1,
+  K_GET_PROBE = 0,
+  K_GET_ROWS = 1,
   K_PUT_PROBE = 2,
   K_PUT_REDUCE = 3,
   K_TIER_MARK = 4,
@@ -84,7 +84,7 @@ struct LaunchHook {
 // then takes each range's keys from its list instead of searching every
 // tile's list. The cut points serve a call with the same G; any sorted set of
 // them is correct, the last call's keep the ranges about even.
-constexpr int kMaxRanges = 512;  // ranges of a get call at most (its row-assignment blocks, two per CU)
+constexpr int kMaxRanges = 512;  // ranges of a get call at most (its row-assignment blocks)
 struct RangeLists {
   NewKey* list = nullptr;      // [entries]: range q's keys from q * cap on; nullptr: no lists
   uint64_t entries = 0;
@@ -119,17 +119,47 @@ struct GetArgs {
   uint64_t cepoch;
   uint32_t bound;
   uint8_t* blocked;
-  // per position: the key found present and its row (the key is the empty
-  // key where the position held no present key); a later put reads them.
-  // nullptr: not recorded
+  // per position: the key found present (the empty key where the position
+  // held no present key); with its row below, a later put reads it. nullptr:
+  // not recorded
   uint64_t* pc_key;
-  uint32_t* pc_row;
-  // 1: a position whose key equals pc_key[i] takes pc_row[i] without probing
+  uint32_t* pos_row;  // per position: its key's row, kPendingRow for a key new in the call
+  // 1: a position whose key equals pc_key[i] takes pos_row[i] without probing
   // (a present key's row never changes, so any recorded pair stays true);
   // not with a staleness clock
   int pc_in;
   RangeLists rl;
   int cus;  // compute units of the device
+};
+
+// What the second get kernel copies out, and the new keys its first blocks
+// assign rows to.
+struct GetRowsArgs {
+  float* out;  // nullptr: nothing is copied
+  const uint64_t* keys;
+  const uint32_t* rows;  // per position (kPendingRow: the key is new in the call)
+  const uint8_t* blocked;
+  int64_t n;
+  uint64_t seed;
+  RowStore store;
+  uint32_t magic;  // ceil(2^32 / units of 16 bytes per row)
+};
+struct AssignArgs {
+  Bucket* idx;
+  const NewKey* newlist;
+  const uint32_t* tile_cnt;
+  int ntiles;
+  int tile_size;
+  float* state;
+  int64_t capacity;
+  Ctrl* ctrl;
+  uint64_t epoch;
+  uint64_t* xkey;
+  uint32_t* xslot;
+  unsigned long long* clock;
+  uint64_t cepoch;
+  RangeLists rl;
+  uint32_t blocks;  // blocks that assign rows (the key ranges)
 };
 
 struct PutArgs {
@@ -228,13 +258,9 @@ struct RsSrc {
   const uint32_t* total;  // later passes: items in all
 };
 
-hipError_t launch_assign(const GetArgs& a, int ntiles, int tlen, int grid, const RangeLists& rl, hipStream_t st,
-                         const LaunchHook& hook);
 hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits, uint32_t* cnt, int rtiles,
                              int stride, uint64_t* dst, uint32_t* total_out, hipStream_t st,
                              const LaunchHook& hook);
-template <class M>
-hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHook& hook);
 template <class M>
 hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase);
 hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook);

@@ -34,6 +34,17 @@ __device__ __forceinline__ void store_vec(float* p, const typename VecT<VEC>::T&
   }
 }
 
+template <int VEC>
+__device__ __forceinline__ void store_vec_nt(float* p, const typename VecT<VEC>::T& v) {
+  if constexpr (VEC == 4) {
+    __builtin_nontemporal_store(
+        Words4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)},
+        reinterpret_cast<Words4*>(p));
+  } else {
+    __builtin_nontemporal_store(v, p);
+  }
+}
+
 // Loads W consecutive 32-bit words (W = 1, 2, 4 or 8; 16-byte aligned when W >= 4).
 template <int W>
 __device__ __forceinline__ void load_words(uint32_t* dst, const uint32_t* src) {
@@ -63,74 +74,26 @@ __device__ __forceinline__ typename VecT<VEC>::T init_vec(uint64_t s0, int col) 
   return v;
 }
 
-// The wave copies the rows of its 64 positions into `out`: rows of keys that
-// were present are read from the table (how = 1), rows of keys new in this
-// call are generated from their seed (how = 0; they equal what the table will
-// hold), and positions of blocked keys are not written (how = 2, only with
-// kTrack: skipping stores costs registers, so tables without a staleness
-// bound use a variant without it).
-template <class M, bool kTrack>
-__device__ __forceinline__ void wave_emit_rows(float* __restrict__ out, const RowStore& store,
-                                               int D, int64_t wave_base, int64_t n, int how,
-                                               uint32_t row, uint64_t s0, int lane) {
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, RPW = M::RPW;
-  constexpr int ITERS = 64 / RPW;
-  constexpr int UNITS = ITERS * K;
-  constexpr int CH = UNITS < 16 ? UNITS : 16;
-  const int g = lane / LPR;
-  const int q = lane % LPR;
-#pragma unroll 1
-  for (int u0 = 0; u0 < UNITS; u0 += CH) {
-    typename VecT<VEC>::T v[CH];
-    uint32_t skip = 0;  // units whose position is blocked
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const int uu = u0 + u;
-      const int it = uu / K;
-      const int k = uu % K;
-      const int r = it * RPW + g;
-      const uint32_t rr = __shfl(row, r, 64);
-      const int hh = __shfl(how, r, 64);
-      const uint64_t ss = __shfl((unsigned long long)s0, r, 64);
-      const int col = M::col(k, q, D);
-      const int64_t p = wave_base + r;
-      if constexpr (kTrack) skip |= (hh == 2 ? 1u : 0u) << u;
-      if (uu < UNITS && p < n && M::on(k, q, D)) {
-        if (hh == 1) v[u] = load_vec<VEC>(store.ptr(rr) + col);
-        else if (hh == 0) v[u] = init_vec<VEC>(ss, col);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const int uu = u0 + u;
-      const int it = uu / K;
-      const int k = uu % K;
-      const int r = it * RPW + g;
-      const int col = M::col(k, q, D);
-      const int64_t p = wave_base + r;
-      if (uu < UNITS && p < n && M::on(k, q, D) && (!kTrack || !((skip >> u) & 1u)))
-        store_vec<VEC>(out + (size_t)p * (size_t)D + col, v[u]);
-    }
-  }
-}
-
-// kPcIn: a position whose key equals pc_key[i] takes pc_row[i] without
+#ifndef MLKV_MAP
+// Get, first kernel: each position's key is looked up (inserted if missing)
+// and its row left in row[i] (kPendingRow: the key is new in the call); the
+// second kernel copies the rows. Bound by the latency of the dependent loads
+// key -> bucket line, so it carries nothing else: without the row copy it
+// needs half the registers and has twice the waves in flight.
+// kPcIn: a position whose key equals pc_key[i] takes row[i] without
 // probing (an instance of its own, so that other gets run unchanged)
-template <class M, bool kTrack, bool kPcIn>
-__global__ __launch_bounds__(kGetTile) void k_get_probe_gather(
+template <bool kTrack, bool kPcIn>
+__global__ __launch_bounds__(kGetTile) void k_get_probe(
     Bucket* __restrict__ idx, uint32_t nb_log2, const uint64_t* __restrict__ keys, int64_t n,
-    float* __restrict__ out, const RowStore store, int D, uint64_t seed,
     NewKey* __restrict__ newlist, uint32_t* __restrict__ tile_cnt, Ctrl* ctrl, uint64_t epoch,
     unsigned long long* __restrict__ clock, uint64_t cepoch, uint32_t bound, uint8_t* __restrict__ blocked,
-    uint64_t* __restrict__ pc_key, uint32_t* __restrict__ pc_row, int tlen, const RangeLists rl,
+    uint64_t* __restrict__ pc_key, uint32_t* __restrict__ rows, int tlen, const RangeLists rl,
     uint32_t nranges) {
   __shared__ uint32_t s_cnt;
   __shared__ uint64_t s_nkey[kGetTile];  // the tile's new keys and their slots
   __shared__ uint32_t s_nslot[kGetTile];
   __shared__ uint64_t s_cuts[kMaxRanges - 1];
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
   // the block's tile: tlen (<= kGetTile) positions, so that every CU gets the
   // same number of positions
   const int64_t base = (int64_t)blockIdx.x * tlen;
@@ -149,7 +112,7 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe_gather(
     } else {
       if constexpr (kPcIn) {
         const uint64_t ck = pc_key[i];
-        const uint32_t cr = pc_row[i];
+        const uint32_t cr = rows[i];
         if (ck == key) {
           pr = {0u, cr, P_HIT};
           recorded = true;
@@ -169,11 +132,10 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe_gather(
   }
   // a key present before the call, with its row, for a put of the same
   // batch: a key's row never changes once assigned, so the pair stays valid
-  if (i < end && pc_key != nullptr && !recorded) {
-    pc_key[i] = pr.status == P_HIT ? key : kEmptyKey;
-    pc_row[i] = pr.row;
+  if (i < end && !recorded) {
+    if (pc_key != nullptr) pc_key[i] = pr.status == P_HIT ? key : kEmptyKey;
+    rows[i] = pr.row;
   }
-  int how = pr.status == P_HIT ? 1 : 0;
   if (kTrack && i < end) {
     // bounded staleness: a present key is served while its count before the
     // call is at most the bound. Serving it stamps the word with the call's
@@ -191,12 +153,7 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe_gather(
         else *cw = (cepoch << kClockBits) | ((w & kClockCount) + 1);
       }
     }
-    if (blk) how = 2;
     blocked[i] = blk ? 1 : 0;
-  }
-  if (out != nullptr) {
-    const uint64_t s0 = splitmix_mix(key ^ seed);
-    wave_emit_rows<M, kTrack>(out, store, D, base + wave * 64, end, how, pr.row, s0, lane);
   }
   __syncthreads();
   // the tile's list of new keys, in ascending key order (each at its rank)
@@ -225,6 +182,8 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe_gather(
     if (tid == 0) ctrl->rl_epoch = epoch;
   }
 }
+
+#endif  // MLKV_MAP
 
 // ===========================================================================
 // Streaming every new key of the call through LDS (used to rank new keys).
@@ -303,15 +262,18 @@ __device__ __forceinline__ int call_verdict(Ctrl* ctrl, uint64_t epoch, uint64_t
 }
 
 // ===========================================================================
-// Get, second kernel: assign rows to the call's new keys (ascending key order),
-// write their initial rows and zero accumulators; or roll the call back.
+// Get, second kernel: the rows of the call's positions are copied out, then
+// its first blocks assign rows to the call's new keys (ascending key order),
+// write their initial rows and zero accumulators; or roll the call back. The
+// copy reads only rows that were present before the call and generates those
+// of new keys from their seed, so neither part waits for the other.
 // ===========================================================================
-constexpr int kAssignThreads = 256;
-constexpr int kAssignBatch = 8;
+constexpr int kAssignThreads = 512;
+constexpr int kAssignBatch = 4;
 constexpr int kAssignMine = kAssignBatch * kAssignThreads;
 // With few new keys each block ranks its tiles' keys against all of them,
-// streamed through LDS once per NT tiles of the call: about 13 us plus 44 ns
-// per (new key x NT tiles) on MI355X (55 us at 256 new keys of a 213k-key,
+// streamed through LDS once per 256 tiles of the call: about 13 us plus 44 ns
+// per (new key x 256 tiles) on MI355X (55 us at 256 new keys of a 213k-key,
 // 832-tile batch; 1.4 ms at 8192), while key ranges take 44-50 us from a few
 // hundred keys up when each block must search every tile's list for its
 // range, and far less with range lists (those calls always take them). The
@@ -327,7 +289,7 @@ constexpr int kRangeCap = 3072;      // keys of a block's key range ranked in LD
 // into the lists, n > 0 entries). Threads take kSearchTiles tiles at a time
 // and search both bounds in all of them together (branch-free binary search,
 // each step one load per bound and tile in flight).
-constexpr int kSearchTiles = 16;
+constexpr int kSearchTiles = 4;
 template <int NT, class Emit>
 __device__ __forceinline__ uint64_t search_tile_lists(const NewKey* __restrict__ newlist,
                                                       const uint32_t* __restrict__ tile_cnt, int ntiles,
@@ -365,9 +327,9 @@ __device__ __forceinline__ uint64_t search_tile_lists(const NewKey* __restrict__
 // partner lies in the same thread run in registers; the others exchange
 // through LDS, alternating between buf0 and buf1 (NT * kSortPT keys each), so
 // one barrier per such stage suffices.
-constexpr int kSortPT = 8;
+constexpr int kSortPT = 4;
 template <int NT>
-__device__ __forceinline__ void sort_keys_8pt(uint64_t (&v)[kSortPT], uint64_t* buf0, uint64_t* buf1) {
+__device__ __forceinline__ void sort_keys(uint64_t (&v)[kSortPT], uint64_t* buf0, uint64_t* buf1) {
   constexpr uint32_t N = (uint32_t)NT * kSortPT;
   const uint32_t t = threadIdx.x;
   auto reg_stage = [&](auto J, uint32_t k) {
@@ -401,7 +363,7 @@ __device__ __forceinline__ void sort_keys_8pt(uint64_t (&v)[kSortPT], uint64_t* 
         v[r] = (asc == low) ? (v[r] < p ? v[r] : p) : (v[r] > p ? v[r] : p);
       }
     }
-    if (k >= 8) reg_stage(std::integral_constant<uint32_t, 4>{}, k);
+    static_assert(kSortPT == 4, "the stages within a thread");
     if (k >= 4) reg_stage(std::integral_constant<uint32_t, 2>{}, k);
     reg_stage(std::integral_constant<uint32_t, 1>{}, k);
   }
@@ -415,8 +377,8 @@ __device__ __forceinline__ unsigned long long new_row_clock(uint64_t cepoch) {
 // A failed get call gives back the counts it raised: every row stamped with
 // its epoch loses one, and the stamp (needed only within the call) is cleared.
 __device__ __forceinline__ void rollback_clocks(unsigned long long* __restrict__ clock, uint64_t nrows,
-                                                uint64_t cepoch) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+                                                uint64_t cepoch, uint32_t blocks) {
+  const uint64_t stride = (uint64_t)blocks * blockDim.x;
   for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += stride) {
     const unsigned long long w = clock[r];
     if ((w >> kClockBits) == cepoch) clock[r] = (w & kClockCount) - 1;
@@ -473,11 +435,19 @@ __device__ __forceinline__ void write_new_rows(const KP ks, const SP sl, const R
 }
 
 #ifndef MLKV_MAP
-__global__ __launch_bounds__(kAssignThreads) void k_assign_new(
-    Bucket* __restrict__ idx, const NewKey* __restrict__ newlist, const uint32_t* __restrict__ tile_cnt,
-    int ntiles, int tile_size, const RowStore store, float* __restrict__ state, int D,
-    uint64_t seed, int64_t capacity, Ctrl* ctrl, uint64_t epoch, uint64_t* __restrict__ xkey,
-    uint32_t* __restrict__ xslot, unsigned long long* __restrict__ clock, uint64_t cepoch, const RangeLists rl) {
+__device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& store, uint64_t seed) {
+  Bucket* __restrict__ const idx = a.idx;
+  const NewKey* __restrict__ const newlist = a.newlist;
+  const uint32_t* __restrict__ const tile_cnt = a.tile_cnt;
+  const int ntiles = a.ntiles, tile_size = a.tile_size, D = store.D;
+  float* __restrict__ const state = a.state;
+  Ctrl* const ctrl = a.ctrl;
+  const uint64_t epoch = a.epoch, cepoch = a.cepoch;
+  const int64_t capacity = a.capacity;
+  uint64_t* __restrict__ const xkey = a.xkey;
+  uint32_t* __restrict__ const xslot = a.xslot;
+  unsigned long long* __restrict__ const clock = a.clock;
+  const RangeLists& rl = a.rl;
   constexpr int NT = kAssignThreads;
   __shared__ unsigned long long s_w64[NT / 64];
   __shared__ uint32_t s_w[NT / 64];
@@ -496,11 +466,11 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
   const bool any_new = ctrl->new_epoch == epoch;
   const uint64_t M = any_new ? count_new_keys<NT>(tile_cnt, ntiles, s_w64) : 0ull;
   const int err = call_verdict(ctrl, epoch, size0, M, capacity, ctrl->bad_epoch, ctrl->overflow_epoch);
-  if (err && clock != nullptr) rollback_clocks(clock, size0, cepoch);
+  if (err && clock != nullptr) rollback_clocks(clock, size0, cepoch, a.blocks);
   if (M == 0) return;
 
   if (err) {  // undo this call's insertions: the index returns to its state before the call
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    for (int t = blockIdx.x; t < ntiles; t += a.blocks) {
       const uint32_t c = tile_cnt[t];
       for (uint32_t j = threadIdx.x; j < c; j += NT) {
         const uint32_t slot = newlist[(size_t)t * tile_size + j].slot;
@@ -513,7 +483,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
   // the probe kernel filed the new keys by range (RangeLists): ranking them
   // by range then costs little for any number of them
   const bool listed = rl.list != nullptr && ctrl->rl_epoch == epoch && ctrl->rl_overflow_epoch != epoch;
-  if (listed || M * (uint64_t)((ntiles + NT - 1) / NT) > kAssignDirectWork) {
+  if (listed || M * (uint64_t)((ntiles + 255) / 256) > kAssignDirectWork) {
     // ---- many new keys: key ranges. Block g ranks the new keys of the g-th
     // key range among themselves, after the count of new keys below the
     // range. The probe kernel has filed the keys by range when cut points for
@@ -524,7 +494,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
     // points from it, which give block g the keys in [lo, hi); a binary
     // search of both bounds in every tile's sorted list of new keys counts
     // the keys below lo and finds the block's own. No block waits for another.
-    const uint32_t g = blockIdx.x, G = gridDim.x;
+    const uint32_t g = blockIdx.x, G = a.blocks;
     uint64_t* s_key = s_buf;                                                 // [kRangeCap]
     uint32_t* s_sr = reinterpret_cast<uint32_t*>(s_buf + kRangeCap);        // [kRangeCap]
     uint16_t* s_ord = reinterpret_cast<uint16_t*>(s_sr + kRangeCap);        // [kRangeCap]
@@ -572,7 +542,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
       // sorted sample (with fewer new keys than samples a key is sampled more
       // than once, and equal cut points give an empty range); eight sample
       // gaps per range keep the largest range near twice the mean
-      sort_keys_8pt<NT>(v, s_buf, s_buf + S);
+      sort_keys<NT>(v, s_buf, s_buf + S);
       {
         const uint32_t r1 = (uint32_t)((uint64_t)g * S / G), r2 = (uint32_t)((uint64_t)(g + 1) * S / G);
   #pragma unroll
@@ -772,21 +742,21 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
   }
 
   // ---- few new keys: this block owns the tiles t = blockIdx.x (mod
-  // gridDim.x); it takes them kAssignBatch at a time (thread j holds entry j
+  // a.blocks); it takes them kAssignBatch at a time (thread j holds entry j
   // of each tile) and ranks their keys against all M new keys of the call.
   uint64_t* s_chunk = s_buf;                                              // [kChunk]
   uint64_t* s_key = s_buf + kChunk;                                       // [kAssignMine]
   uint32_t* s_slot = reinterpret_cast<uint32_t*>(s_key + kAssignMine);    // [kAssignMine]
   uint32_t* s_rank = s_slot + kAssignMine;                                // [kAssignMine]
-  static_assert(kGetTile == NT, "one thread per entry of a probe tile");
-  for (int tb = blockIdx.x; tb < ntiles; tb += gridDim.x * kAssignBatch) {
+  constexpr int kTilesAt = kAssignMine / kGetTile;  // tiles taken at a time, kGetTile entries each
+  for (int tb = blockIdx.x; tb < ntiles; tb += a.blocks * kTilesAt) {
     uint32_t have = 0;
 #pragma unroll
     for (int b = 0; b < kAssignBatch; ++b) {
-      const int t = tb + b * (int)gridDim.x;
+      const int m = b * NT + (int)threadIdx.x;
+      const int t = tb + m / kGetTile * (int)a.blocks;
       const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      const uint32_t j = threadIdx.x;
-      const int m = b * NT + (int)j;
+      const uint32_t j = m % kGetTile;
       if (j < c) {
         const NewKey nk = newlist[(size_t)t * tile_size + j];
         s_key[m] = nk.key;
@@ -821,13 +791,82 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign_new(
       if (clock != nullptr) clock[row] = new_row_clock(cepoch);
     }
     // initial rows, a wave per row
-    for (int b = 0; b < kAssignBatch; ++b) {
-      const int t = tb + b * (int)gridDim.x;
+    for (int b = 0; b < kTilesAt; ++b) {
+      const int t = tb + b * (int)a.blocks;
       const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      write_init_rows<NT>(s_key + b * NT, s_rank + b * NT, c, size0, store, D, seed);
+      write_init_rows<NT>(s_key + b * kGetTile, s_rank + b * kGetTile, c, size0, store, D, seed);
     }
     __syncthreads();
   }
+}
+
+// Copies the block's share of the positions' rows into `out`: kCopyUnits
+// units of 16 bytes per thread, consecutive threads on consecutive units of
+// the output, whatever the width of a row, so that no lane idles on a row's
+// end. Rows of keys present before the call are read from the table, rows of
+// keys new in it are generated from their seed (they equal what the table
+// will hold), rows of blocked positions are left alone (kTrack).
+// Bound by HBM. As a part of the probe kernel, where a wave copied the rows of
+// its own 64 positions with 4 to 64 lanes a row, 150k rows of dim 400 took 178
+// us with the probe and 1M of dim 128 took 274; apart they take 11 + 97 and 46
+// + 189 (and dim 64, 213k rows, 12 + 17 against 24, where the launch of the
+// row assignment, 4.8 us, is saved). Two units a thread; four are 4 to 8 %
+// slower at these widths. An output of kStreamOut bytes does not stay in the 32
+// MB of L2 anyway and goes around it (non-temporal), which leaves the caches
+// to the rows and to the kernels that follow: two DLRM steps 199 -> 186 us,
+// two of dim 400 640 -> 595.
+constexpr int kCopyThreads = kAssignThreads;
+constexpr int kCopyUnits = 2;
+constexpr uint64_t kStreamOut = 32ull << 20;
+constexpr uint64_t kCopyBlocks = 1ull << 22;  // blocks at most (a launch holds fewer than 2^32 threads)
+template <int VEC, bool kTrack, bool kStream>
+__device__ __forceinline__ void copy_rows(const GetRowsArgs& a) {
+  constexpr uint32_t PER = kCopyThreads * kCopyUnits;
+  using V = typename VecT<VEC>::T;
+  const int D = a.store.D;
+  const uint32_t Q = VEC == 4 ? (uint32_t)(D + 3) / 4u : (uint32_t)D;  // units of a row
+  const uint64_t total = (uint64_t)a.n * Q;
+  for (uint64_t first = (uint64_t)blockIdx.x * PER; first < total; first += (uint64_t)gridDim.x * PER) {
+    const uint64_t p0 = first / Q;  // (block-uniform)
+    const uint32_t rem = (uint32_t)(first - p0 * Q);
+    V v[kCopyUnits];
+    uint64_t p[kCopyUnits];
+    int col[kCopyUnits];
+    uint32_t row[kCopyUnits];
+    bool on[kCopyUnits];
+#pragma unroll
+    for (int u = 0; u < kCopyUnits; ++u) {
+      const uint32_t e = rem + (uint32_t)u * kCopyThreads + threadIdx.x;  // < Q + PER
+      // e / Q by magic = ceil(2^32 / Q): exact, since e * (magic * Q - 2^32) < (Q + PER) * Q < 2^32
+      const uint32_t d = Q == 1 ? e : (uint32_t)(((uint64_t)e * a.magic) >> 32);
+      p[u] = p0 + d;
+      const int c = (int)(e - d * Q) * VEC;
+      col[u] = VEC == 1 || c < D - VEC ? c : D - VEC;  // the last unit of a row: its last four columns
+      on[u] = p[u] < (uint64_t)a.n;
+      row[u] = on[u] ? a.rows[p[u]] : kPendingRow;
+      if constexpr (kTrack) on[u] = on[u] && a.blocked[p[u]] == 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kCopyUnits; ++u)
+      if (row[u] != kPendingRow) v[u] = load_vec<VEC>(a.store.ptr(row[u]) + col[u]);
+#pragma unroll
+    for (int u = 0; u < kCopyUnits; ++u)
+      if (on[u] && row[u] == kPendingRow) v[u] = init_vec<VEC>(splitmix_mix(a.keys[p[u]] ^ a.seed), col[u]);
+#pragma unroll
+    for (int u = 0; u < kCopyUnits; ++u) {
+      if (!on[u]) continue;
+      float* o = a.out + (size_t)p[u] * (size_t)D + col[u];
+      if constexpr (kStream) store_vec_nt<VEC>(o, v[u]);
+      else store_vec<VEC>(o, v[u]);
+    }
+  }
+}
+
+// At most 80 registers (six waves per SIMD): the copy needs the waves.
+template <int VEC, bool kTrack, bool kStream>
+__global__ __launch_bounds__(kAssignThreads, 6) void k_get_rows(const GetRowsArgs ra, const AssignArgs aa) {
+  if (ra.out != nullptr) copy_rows<VEC, kTrack, kStream>(ra);
+  if (blockIdx.x < aa.blocks) assign_new(aa, ra.store, ra.seed);
 }
 #endif  // MLKV_MAP
 
@@ -2876,13 +2915,59 @@ __global__ __launch_bounds__(256) void k_read_clock(const unsigned long long* __
 // Launchers
 // ===========================================================================
 #ifndef MLKV_MAP
-hipError_t launch_assign(const GetArgs& a, int ntiles, int tlen, int grid, const RangeLists& rl, hipStream_t st,
-                         const LaunchHook& hook) {
-  hook(K_ASSIGN_NEW, 0, st);
-  hipLaunchKernelGGL(k_assign_new, dim3(grid), dim3(kAssignThreads), 0, st, a.idx, a.newlist, a.tile_cnt, ntiles,
-                     tlen, a.store, a.state, a.D, a.seed, a.capacity, a.ctrl, a.epoch, a.xkey, a.xslot, a.clock,
-                     a.cepoch, rl);
-  hook(K_ASSIGN_NEW, 1, st);
+hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
+  const int tlen = get_tile_len(a.n, a.cus);
+  const int64_t ntiles = (a.n + tlen - 1) / tlen;
+  const uint32_t ranges = (uint32_t)std::min<int64_t>(ntiles, kMaxRanges);  // row assignment: a block per key range
+  RangeLists rl = a.rl;
+  if (rl.list != nullptr) rl.cap = (uint32_t)std::min<uint64_t>(rl.entries / ranges, 0xFFFFFFFFull);
+  hook(K_GET_PROBE, 0, st);
+  auto kern = a.clock != nullptr ? k_get_probe<true, false> : a.pc_in ? k_get_probe<false, true> : k_get_probe<false, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kGetTile), 0, st, a.idx, a.nb_log2, a.keys, a.n, a.newlist,
+                     a.tile_cnt, a.ctrl, a.epoch, a.clock, a.cepoch, a.bound, a.blocked, a.pc_key, a.pos_row, tlen,
+                     rl, ranges);
+  hook(K_GET_PROBE, 1, st);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int vec = a.D >= 4 ? 4 : 1;
+  const uint64_t units = (uint64_t)(a.D + vec - 1) / vec;  // of a row
+  const uint64_t per_block = (uint64_t)kCopyThreads * kCopyUnits;
+  const uint64_t blocks =
+      a.out != nullptr ? std::min<uint64_t>(((uint64_t)a.n * units + per_block - 1) / per_block, kCopyBlocks) : 0;
+  GetRowsArgs r;
+  r.out = a.out;
+  r.keys = a.keys;
+  r.rows = a.pos_row;
+  r.blocked = a.blocked;
+  r.n = a.n;
+  r.seed = a.seed;
+  r.store = a.store;
+  r.magic = units > 1 ? (uint32_t)((0x100000000ull + units - 1) / units) : 0u;
+  AssignArgs s;
+  s.idx = a.idx;
+  s.newlist = a.newlist;
+  s.tile_cnt = a.tile_cnt;
+  s.ntiles = (int)ntiles;
+  s.tile_size = tlen;
+  s.state = a.state;
+  s.capacity = a.capacity;
+  s.ctrl = a.ctrl;
+  s.epoch = a.epoch;
+  s.xkey = a.xkey;
+  s.xslot = a.xslot;
+  s.clock = a.clock;
+  s.cepoch = a.cepoch;
+  s.rl = rl;
+  s.blocks = ranges;
+  const unsigned grid = (unsigned)std::max<uint64_t>(blocks, ranges);
+  const bool track = a.clock != nullptr;
+  hook(K_GET_ROWS, 0, st);
+  const bool stream = (uint64_t)a.n * (uint64_t)a.D * sizeof(float) >= kStreamOut;
+  auto rows = vec != 4 ? (track ? k_get_rows<1, true, false> : k_get_rows<1, false, false>)
+              : stream ? (track ? k_get_rows<4, true, true> : k_get_rows<4, false, true>)
+                       : (track ? k_get_rows<4, true, false> : k_get_rows<4, false, false>);
+  hipLaunchKernelGGL(rows, dim3(grid), dim3(kAssignThreads), 0, st, r, s);
+  hook(K_GET_ROWS, 1, st);
   return hipGetLastError();
 }
 
@@ -2903,25 +2988,6 @@ hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits
   return hipGetLastError();
 }
 #endif  // MLKV_MAP
-
-template <class M>
-hipError_t launch_get_t(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
-  const int tlen = get_tile_len(a.n, a.cus);
-  const int64_t ntiles = (a.n + tlen - 1) / tlen;
-  const int grid = (int)std::min<int64_t>(ntiles, kMaxRanges);  // row assignment: one block per key range
-  RangeLists rl = a.rl;
-  if (rl.list != nullptr) rl.cap = (uint32_t)std::min<uint64_t>(rl.entries / (uint64_t)grid, 0xFFFFFFFFull);
-  hook(K_GET_PROBE_GATHER, 0, st);
-  auto kern = a.clock != nullptr ? k_get_probe_gather<M, true, false>
-                                  : a.pc_in ? k_get_probe_gather<M, false, true> : k_get_probe_gather<M, false, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kGetTile), 0, st, a.idx, a.nb_log2, a.keys, a.n,
-                     a.out, a.store, a.D, a.seed, a.newlist, a.tile_cnt, a.ctrl, a.epoch, a.clock, a.cepoch,
-                     a.bound, a.blocked, a.pc_key, a.pc_row, tlen, rl, (uint32_t)grid);
-  hook(K_GET_PROBE_GATHER, 1, st);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_assign(a, (int)ntiles, tlen, grid, rl, st, hook);
-}
 
 // Lets kernel `f` (an instance of a reduce kernel) use `bytes` of dynamic
 // LDS on the current device; `done` remembers the devices where that is set.
@@ -3041,11 +3107,9 @@ hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook
 }
 
 #ifdef MLKV_MAP
-template hipError_t launch_get_t<MLKV_MAP>(const GetArgs&, hipStream_t, const LaunchHook&);
 template hipError_t launch_put_t<MLKV_MAP>(const PutArgs&, hipStream_t, const LaunchHook&, int);
 #else
-#define MLKV_EXTERN(M)                                                                          \
-  extern template hipError_t launch_get_t<M>(const GetArgs&, hipStream_t, const LaunchHook&);   \
+#define MLKV_EXTERN(M) \
   extern template hipError_t launch_put_t<M>(const PutArgs&, hipStream_t, const LaunchHook&, int);
 MLKV_MAPS(MLKV_EXTERN)
 
@@ -3059,10 +3123,6 @@ static hipError_t dispatch_map(int D, F f) {
   if (D <= 256) return f(MapD256{});
   if (D <= 512) return f(MapD512{});
   return f(MapD1024{});
-}
-
-hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
-  return dispatch_map(a.D, [&](auto m) { return launch_get_t<decltype(m)>(a, st, hook); });
 }
 
 hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
