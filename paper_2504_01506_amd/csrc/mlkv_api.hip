@@ -63,6 +63,7 @@ struct mlkv_table {
   uint64_t* items = nullptr;
   uint32_t* meta = nullptr;
   uint64_t* spill = nullptr;
+  void* units = nullptr;       // a put's units (PutUnits)
   uint64_t spill_words = 0;
   uint32_t* rs_cnt = nullptr;  // radix dedup: per-tile digit counts and the item total
   int dedup = kDedupHash;
@@ -126,7 +127,7 @@ void free_scratch_set(const ScratchSet& s) {
 ScratchSet current_set(mlkv_table* t) {
   ScratchSet s;
   s.ptrs = {t->newlist, t->tile_cnt, t->items, t->meta, t->spill, t->partials, t->pc_key, t->pc_row,
-            t->rs_cnt, t->miss, t->plan_slot, t->mid_xkey, t->mid_xslot, t->rl_list, t->rl_cnt, t->rl_cuts};
+            t->rs_cnt, t->units, t->miss, t->plan_slot, t->mid_xkey, t->mid_xslot, t->rl_list, t->rl_cnt, t->rl_cuts};
   return s;
 }
 
@@ -148,6 +149,7 @@ void clear_workspace_ptrs(mlkv_table* t) {
   t->meta = nullptr;
   t->spill = nullptr;
   t->rs_cnt = nullptr;
+  t->units = nullptr;
   t->ws_n = 0;
   t->spill_words = 0;
 }
@@ -174,27 +176,37 @@ int release_retired(mlkv_table* t) {
 }
 
 // Partitions of a put call of n keys: a power of two, at most kMaxParts,
-// with at most kPartTarget keys each on average before in-tile merging.
+// with at most kPartTarget keys each on average before in-tile merging. Two
+// grouping blocks run on a CU at a time. Fewer, larger partitions are a little
+// faster while no block meets more items than its LDS holds (two steps of 1M
+// lookups at dim 128: 1222 us with 512 partitions, 1244 with 1024), but a hot
+// key brings an item per put tile, and with skewed keys some partitions then
+// overflow (1M lookups, dim 16, Zipf 1.1: 876 us against 436).
 uint32_t part_bits(int64_t n) {
   uint32_t pb = 0;
   while ((1 << pb) < kMaxParts && ((int64_t)kPartTarget << pb) < n) ++pb;
   return pb;
 }
 
-// Partitions used by a put call: as part_bits (never more; the partition
-// metadata holds kMaxParts per tile), but one partition per CU, up to twice
-// the target each, when that keeps the grouping blocks to one round. A small
-// batch keeps its few large partitions: a block's grouping costs about the
-// same for fewer items, and more blocks measured slower.
-uint32_t call_part_bits(int64_t n, int cus) {
-  uint32_t pb = part_bits(n);
-  if (pb > 0 && (1 << pb) > cus && (1 << (pb - 1)) >= cus && (int64_t)(2 * kPartTarget) * cus >= n) --pb;
-  return pb;
+// A put's units for calls of up to n keys, as one buffer.
+size_t unit_bytes(int64_t n) {
+  return (size_t)n * (sizeof(uint4) + sizeof(uint64_t) + sizeof(uint32_t)) +
+         ((size_t)n / kLongNarrow + 1) * sizeof(uint4);
+}
+
+PutUnits units_of(const mlkv_table* t) {
+  PutUnits u;
+  u.multi = static_cast<uint4*>(t->units);
+  u.lng = u.multi + t->ws_n;
+  u.single = reinterpret_cast<uint64_t*>(u.lng + t->ws_n / kLongNarrow + 1);
+  u.mitem = reinterpret_cast<uint32_t*>(u.single + t->ws_n);
+  u.long_over = kLongNarrow;
+  return u;
 }
 
 // Scratch for calls of up to n keys: new-key lists, per-tile counts, the
 // partitioned items, partition metadata, the spill area, in-tile sums, the
-// grouped partitions and the last get's rows by position. A larger set
+// units of the update and the last get's rows by position. A larger set
 // replaces the current one without waiting for the device: the old set is
 // retired behind an event recorded on `st` (the work queued before uses it)
 // and freed by mlkv_sync, mlkv_reserve or mlkv_close. The new row cache is
@@ -225,6 +237,7 @@ int ensure_workspace(mlkv_table* t, int64_t n, hipStream_t st) {
       (e = dev_alloc(&t->items, sizeof(uint64_t) * (size_t)slots)) != hipSuccess ||
       (e = dev_alloc(&t->meta, sizeof(uint32_t) * (size_t)kMaxParts * (size_t)put_tiles)) != hipSuccess ||
       (e = dev_alloc(&t->spill, sizeof(uint64_t) * (size_t)spill_words)) != hipSuccess ||
+      (e = dev_alloc(reinterpret_cast<char**>(&t->units), unit_bytes(want))) != hipSuccess ||
       // radix counts: 2^kRsMaxBits digit rows of (radix tiles rounded up to 4), then the item total
       (e = dev_alloc(&t->rs_cnt, sizeof(uint32_t) * (((size_t)(put_tiles + 3) / 4 + 4) * (1u << kRsMaxBits) + 64))) !=
           hipSuccess ||
@@ -722,7 +735,7 @@ int check_put(mlkv_table* t, const uint64_t* d_keys, const float* src, int64_t n
 
 // The launch arguments of a put of n > 0 keys with the table's epoch.
 PutArgs put_args(mlkv_table* t, const uint64_t* d_keys, const float* src, int64_t n, int op, float lr, float eps) {
-  const uint32_t pb = call_part_bits(n, t->cus);
+  const uint32_t pb = part_bits(n);
   // keys per put_probe tile: a multiple of 64, at most kPutTile, so that the
   // tiles cover every CU when the batch is small
   const int64_t per_cu = (n + t->cus - 1) / t->cus;
@@ -750,6 +763,9 @@ PutArgs put_args(mlkv_table* t, const uint64_t* d_keys, const float* src, int64_
   a.tile_cnt = t->tile_cnt;
   a.spill = t->spill;
   a.spill_words = t->spill_words;
+  a.units = units_of(t);
+  a.xkey = t->mid_xkey;  // (a put beside a get, which uses them then, inserts nothing)
+  a.xslot = t->mid_xslot;
   a.ctrl = t->ctrl;
   a.epoch = t->epoch;
   a.clock = t->clock;
@@ -978,9 +994,9 @@ int mlkv_profile_read(mlkv_table* t, double* total_ms, int64_t* launches) {
 }
 
 const char* mlkv_kernel_name(int kernel) {
-  static const char* names[K_COUNT] = {"get_probe", "get_rows", "put_probe", "put_reduce",
+  static const char* names[K_COUNT] = {"get_probe", "get_rows", "put_probe", "put_group",
                                        "tier_mark", "tier_plan", "tier_copy", "rsort_count",
-                                       "rsort_scatter", "rsort_reduce"};
+                                       "rsort_scatter", "put_apply"};
   return (kernel >= 0 && kernel < K_COUNT) ? names[kernel] : nullptr;
 }
 

@@ -11,7 +11,8 @@ constexpr uint32_t kPendingRow = 0xFFFFFFFFu;
 constexpr int kSlots = 8;          // slots per bucket
 constexpr int kMaxProbe = 4096;    // buckets visited before a call reports overflow
 
-// One bucket = one 128-byte line: 8 key tags, the 8 row ids, 8 spare words.
+// One bucket = one 128-byte line: 8 key tags, the 8 row ids, 8 spare words (all
+// ones but while an upsert inserts the slot's key, see k_put_probe).
 struct __align__(128) Bucket {
   uint64_t key[kSlots];
   uint32_t row[kSlots];
@@ -95,6 +96,10 @@ struct Ctrl {
   unsigned long long tier_evicted;  // rows whose slot was given to another row
   unsigned long long tier_written;  // evicted rows written back (dirty)
   unsigned long long tier_filled;   // slots holding a row
+  // a put's units (see PutUnits), in lines of their own: singles | items of
+  // sums << 32, and multis | longs << 32
+  __align__(128) unsigned long long unit_single;
+  __align__(128) unsigned long long unit_multi;
 };
 
 // ---------------------------------------------------------------------------

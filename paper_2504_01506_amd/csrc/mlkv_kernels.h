@@ -26,10 +26,16 @@ inline int get_tile_len(int64_t n, int cus) {
 constexpr int kPutTile = 1024;   // keys per put_probe block
 constexpr int kPutThreads = 1024; // threads of a put_probe block
 constexpr int kMaxParts = 4096;  // partitions (MSD digits) per put call
-constexpr int kRedCap = 3072;    // partition items grouped in LDS by a put_reduce block
+constexpr int kRedCap = 3072;    // partition items grouped in LDS by a put_group block
 constexpr int kRedHash = 4096;   // LDS hash slots for that grouping (load <= 0.75)
 constexpr int kPartTarget = 1024; // put keys per partition the partition count aims for
-constexpr int kPresumMin = 2;    // a key repeated this often in a put_probe tile is summed there
+// A key repeated this often in a put_probe tile is summed there (twice, where
+// rows have at most 32 floats). A key seen twice costs a row of fp64 written and
+// read in place of its two fp32 rows: from 3 repeats on, two DLRM steps (dim 64)
+// take 185.0 us against 187.8, two of 1M lookups at dim 128 1241 against 1244;
+// two of 131k at dim 32 take 126.5 against 125.6. From 4 on hot keys cost more:
+// 189.3 at dim 64.
+constexpr int kPresumMinWide = 3;
 
 // Error code a kernel latches when a put whose probe ran ahead of a get met a
 // key that was not in the table before the two calls (reported as MLKV_EINVAL).
@@ -40,13 +46,13 @@ enum KernelId : int {
   K_GET_PROBE = 0,
   K_GET_ROWS = 1,
   K_PUT_PROBE = 2,
-  K_PUT_REDUCE = 3,
+  K_PUT_GROUP = 3,
   K_TIER_MARK = 4,
   K_TIER_PLAN = 5,
   K_TIER_COPY = 6,
   K_RSORT_COUNT = 7,
   K_RSORT_SCATTER = 8,
-  K_RSORT_REDUCE = 9,
+  K_PUT_APPLY = 9,
   K_COUNT = 10
 };
 
@@ -159,7 +165,53 @@ struct AssignArgs {
   unsigned long long* clock;
   uint64_t cepoch;
   RangeLists rl;
+  const float* values;  // an upsert's value rows (the new rows are written from them), else nullptr
   uint32_t blocks;  // blocks that assign rows (the key ranges)
+};
+
+// The update of a put call as units, one per distinct key (see k_put_group).
+// Items of a unit that one lane group adds up, at most; a block takes longer
+// ones. Rows of up to 32 floats have 32 lane groups in a block and more: 13.7
+// us against 15.7 with 16 (131k lookups, dim 32), 10.5 against 12.4 (dim 10);
+// at dim 128 a block has 8, and 8 items are 363 us against 340 with 16 (32:
+// 344; dim 64, 213k lookups: 34 us against 29).
+constexpr uint32_t kLongNarrow = 8, kLongWide = 16;
+constexpr uint32_t kUnitFresh = 1u << 31;   // the unit's tag is an index slot (a key new in the call)
+struct PutUnits {
+  uint64_t* single;  // [n] keys with one gradient (or value) row: the item
+  uint4* multi;      // [n] keys with a sum of at most long_over items: {tag, items | kUnitFresh, first item, 0}
+  uint4* lng;        // [n / kLongNarrow] keys with a longer one
+  uint32_t* mitem;   // [n] their items (the low 31 bits)
+  uint32_t long_over;
+};
+
+struct PutGroupArgs {
+  const uint64_t* items;
+  const uint32_t* meta;
+  int ntiles;
+  PutUnits units;
+  Ctrl* ctrl;
+  uint64_t epoch;
+  int64_t capacity;
+  uint64_t* spill;
+  uint64_t spill_words;
+  // an upsert:
+  const float* values;
+  unsigned long long* clock;
+  uint32_t magic;  // ceil(2^32 / units of 16 bytes per row)
+};
+
+struct PutApplyArgs {
+  const Bucket* idx;
+  const float* grads;
+  const double* partials;
+  PutUnits units;
+  const Ctrl* ctrl;
+  float* state;
+  unsigned long long* clock;
+  int op;
+  float lr;
+  float eps;
 };
 
 struct PutArgs {
@@ -185,6 +237,9 @@ struct PutArgs {
   uint32_t* tile_cnt;
   uint64_t* spill;
   uint64_t spill_words;
+  PutUnits units;
+  uint64_t* xkey;   // as for a get (GetArgs)
+  uint32_t* xslot;
   Ctrl* ctrl;
   uint64_t epoch;
   unsigned long long* clock;  // per-row staleness words, or nullptr when not tracked
@@ -262,7 +317,9 @@ hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits
                              int stride, uint64_t* dst, uint32_t* total_out, hipStream_t st,
                              const LaunchHook& hook);
 template <class M>
-hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase);
+hipError_t launch_put_probe_t(const PutArgs& a, int pb, hipStream_t st, const LaunchHook& hook);
+template <class M>
+hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_tier_lookahead(const TierArgs& a, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase = kPutAll);

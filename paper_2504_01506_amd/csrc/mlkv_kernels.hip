@@ -24,6 +24,17 @@ __device__ __forceinline__ typename VecT<VEC>::T load_vec(const float* p) {
   }
 }
 
+// As load_vec, for rows read once (kStream): around the caches.
+template <int VEC, bool kStream>
+__device__ __forceinline__ typename VecT<VEC>::T load_vec_once(const float* p) {
+  if constexpr (VEC == 4 && kStream) {
+    const Words4 v = __builtin_nontemporal_load(reinterpret_cast<const Words4*>(p));
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+  } else {
+    return load_vec<VEC>(p);
+  }
+}
+
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const typename VecT<VEC>::T& v) {
   if constexpr (VEC == 4) {
@@ -79,13 +90,17 @@ __device__ __forceinline__ typename VecT<VEC>::T init_vec(uint64_t s0, int col) 
 // and its row left in row[i] (kPendingRow: the key is new in the call); the
 // second kernel copies the rows. Bound by the latency of the dependent loads
 // key -> bucket line, so it carries nothing else: without the row copy it
-// needs half the registers and has twice the waves in flight.
+// needs half the registers and has twice the waves in flight. Only a row of
+// kNarrowUnits accesses or fewer (VEC > 0) is copied here, by its key's lane:
+// the second kernel's pass over the positions costs more then (two steps of
+// the 2^20-operation key-value mix, rows of 16 bytes: 164 us against 168).
 // kPcIn: a position whose key equals pc_key[i] takes row[i] without
 // probing (an instance of its own, so that other gets run unchanged)
-template <bool kTrack, bool kPcIn>
+constexpr uint32_t kNarrowUnits = 1;
+template <int VEC, bool kTrack, bool kPcIn>
 __global__ __launch_bounds__(kGetTile) void k_get_probe(
     Bucket* __restrict__ idx, uint32_t nb_log2, const uint64_t* __restrict__ keys, int64_t n,
-    NewKey* __restrict__ newlist, uint32_t* __restrict__ tile_cnt, Ctrl* ctrl, uint64_t epoch,
+    float* __restrict__ out, const RowStore store, uint64_t seed, NewKey* __restrict__ newlist, uint32_t* __restrict__ tile_cnt, Ctrl* ctrl, uint64_t epoch,
     unsigned long long* __restrict__ clock, uint64_t cepoch, uint32_t bound, uint8_t* __restrict__ blocked,
     uint64_t* __restrict__ pc_key, uint32_t* __restrict__ rows, int tlen, const RangeLists rl,
     uint32_t nranges) {
@@ -136,6 +151,7 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe(
     if (pc_key != nullptr) pc_key[i] = pr.status == P_HIT ? key : kEmptyKey;
     rows[i] = pr.row;
   }
+  bool served = i < end;
   if (kTrack && i < end) {
     // bounded staleness: a present key is served while its count before the
     // call is at most the bound. Serving it stamps the word with the call's
@@ -154,6 +170,21 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe(
       }
     }
     blocked[i] = blk ? 1 : 0;
+    served = !blk;
+  }
+  if constexpr (VEC > 0) {
+    if (served) {
+      const int D = store.D;
+      const float* w = pr.status == P_HIT ? store.ptr(pr.row) : nullptr;
+      const uint64_t s0 = splitmix_mix(key ^ seed);
+#pragma unroll
+      for (uint32_t u = 0; u < kNarrowUnits; ++u) {
+        const int c = (int)u * VEC;
+        if (c >= D) break;
+        const int col = VEC == 1 || c < D - VEC ? c : D - VEC;
+        store_vec<VEC>(out + (size_t)i * (size_t)D + col, w != nullptr ? load_vec<VEC>(w + col) : init_vec<VEC>(s0, col));
+      }
+    }
   }
   __syncthreads();
   // the tile's list of new keys, in ascending key order (each at its rank)
@@ -269,8 +300,7 @@ __device__ __forceinline__ int call_verdict(Ctrl* ctrl, uint64_t epoch, uint64_t
 // of new keys from their seed, so neither part waits for the other.
 // ===========================================================================
 constexpr int kAssignThreads = 512;
-constexpr int kAssignBatch = 4;
-constexpr int kAssignMine = kAssignBatch * kAssignThreads;
+constexpr int kAssignMine = 2048;  // list entries a block ranks directly at a time
 // With few new keys each block ranks its tiles' keys against all of them,
 // streamed through LDS once per 256 tiles of the call: about 13 us plus 44 ns
 // per (new key x 256 tiles) on MI355X (55 us at 256 new keys of a 213k-key,
@@ -290,7 +320,7 @@ constexpr int kRangeCap = 3072;      // keys of a block's key range ranked in LD
 // and search both bounds in all of them together (branch-free binary search,
 // each step one load per bound and tile in flight).
 constexpr int kSearchTiles = 4;
-template <int NT, class Emit>
+template <int NT, int TM, class Emit>
 __device__ __forceinline__ uint64_t search_tile_lists(const NewKey* __restrict__ newlist,
                                                       const uint32_t* __restrict__ tile_cnt, int ntiles,
                                                       int tile_size, uint64_t lo, uint64_t hi, Emit emit) {
@@ -304,8 +334,8 @@ __device__ __forceinline__ uint64_t search_tile_lists(const NewKey* __restrict__
       a[u] = 0;  // keys below lo
       b[u] = 0;  // keys below hi
     }
-    // a tile holds at most kGetTile (a power of two) keys
-    for (uint32_t step = (uint32_t)kGetTile; step >= 1; step >>= 1) {
+    // a tile holds at most TM (a power of two) keys
+    for (uint32_t step = (uint32_t)TM; step >= 1; step >>= 1) {
 #pragma unroll
       for (int u = 0; u < kSearchTiles; ++u) {
         const NewKey* l = newlist + (size_t)(t0 + u * NT) * tile_size;
@@ -322,22 +352,22 @@ __device__ __forceinline__ uint64_t search_tile_lists(const NewKey* __restrict__
   return below;
 }
 
-// Ascending bitonic sort of NT * kSortPT keys, thread t holding the
-// elements kSortPT t .. kSortPT t + kSortPT - 1 in v. Compare-exchanges whose
-// partner lies in the same thread run in registers; the others exchange
-// through LDS, alternating between buf0 and buf1 (NT * kSortPT keys each), so
-// one barrier per such stage suffices.
-constexpr int kSortPT = 4;
-template <int NT>
-__device__ __forceinline__ void sort_keys(uint64_t (&v)[kSortPT], uint64_t* buf0, uint64_t* buf1) {
-  constexpr uint32_t N = (uint32_t)NT * kSortPT;
+// Ascending bitonic sort of NT * PT keys, thread t holding the elements PT t
+// .. PT t + PT - 1 in v. Compare-exchanges whose partner lies in the same
+// thread run in registers; the others exchange through LDS, alternating
+// between buf0 and buf1 (NT * PT keys each), so one barrier per such stage
+// suffices.
+template <int NT, int PT>
+__device__ __forceinline__ void sort_keys(uint64_t (&v)[PT], uint64_t* buf0, uint64_t* buf1) {
+  static_assert(PT == 2 || PT == 4, "the stages within a thread");
+  constexpr uint32_t N = (uint32_t)NT * PT;
   const uint32_t t = threadIdx.x;
   auto reg_stage = [&](auto J, uint32_t k) {
     constexpr uint32_t j = decltype(J)::value;
 #pragma unroll
-    for (uint32_t r = 0; r < kSortPT; ++r) {
+    for (uint32_t r = 0; r < PT; ++r) {
       if ((r & j) == 0) {
-        const bool asc = ((t * kSortPT + r) & k) == 0;
+        const bool asc = ((t * PT + r) & k) == 0;
         const uint64_t a = v[r], b = v[r + j];
         if ((a > b) == asc) {
           v[r] = b;
@@ -348,23 +378,24 @@ __device__ __forceinline__ void sort_keys(uint64_t (&v)[kSortPT], uint64_t* buf0
   };
   bool second = false;
   for (uint32_t k = 2; k <= N; k <<= 1) {
-    for (uint32_t j = k >> 1; j >= kSortPT; j >>= 1) {
+    for (uint32_t j = k >> 1; j >= PT; j >>= 1) {
       uint64_t* b = second ? buf1 : buf0;
       second = !second;
 #pragma unroll
-      for (uint32_t r = 0; r < kSortPT; ++r) b[r * NT + t] = v[r];
+      for (uint32_t r = 0; r < PT; ++r) b[r * NT + t] = v[r];
       lds_barrier();
-      const uint32_t pt = t ^ (j / kSortPT);
+      const uint32_t pt = t ^ (j / PT);
 #pragma unroll
-      for (uint32_t r = 0; r < kSortPT; ++r) {
-        const uint32_t i = t * kSortPT + r;
+      for (uint32_t r = 0; r < PT; ++r) {
+        const uint32_t i = t * PT + r;
         const uint64_t p = b[r * NT + pt];
         const bool asc = (i & k) == 0, low = (i & j) == 0;
         v[r] = (asc == low) ? (v[r] < p ? v[r] : p) : (v[r] > p ? v[r] : p);
       }
     }
-    static_assert(kSortPT == 4, "the stages within a thread");
-    if (k >= 4) reg_stage(std::integral_constant<uint32_t, 2>{}, k);
+    if constexpr (PT >= 4) {
+      if (k >= 4) reg_stage(std::integral_constant<uint32_t, 2>{}, k);
+    }
     reg_stage(std::integral_constant<uint32_t, 1>{}, k);
   }
 }
@@ -416,26 +447,103 @@ __device__ __forceinline__ void write_init_rows(const KP ks, const RP rk, uint32
   }
 }
 
+// The rows of an upsert's new keys, as write_init_rows: row base + rk[j] takes
+// the value row of position ks[j].
+template <int NT, class KP, class RP>
+__device__ __forceinline__ void write_value_rows(const KP ks, const RP rk, uint32_t m, uint64_t base,
+                                                 const RowStore& store, int D, const float* __restrict__ values) {
+  constexpr uint32_t NW = NT / 64;
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (uint32_t j0 = wave; j0 < m; j0 += NW * kInitRows) {
+    float* w[kInitRows];
+    const float* v[kInitRows];
+#pragma unroll
+    for (int r = 0; r < kInitRows; ++r) {
+      const uint32_t j = j0 + (uint32_t)r * NW;
+      w[r] = nullptr;
+      v[r] = nullptr;
+      if (j < m) {
+        w[r] = store.wptr((uint32_t)(base + rk[j]));
+        v[r] = values + (size_t)ks[j] * (size_t)D;
+      }
+    }
+    for (int col = (int)lane; col < D; col += 64) {
+      float x[kInitRows];
+#pragma unroll
+      for (int r = 0; r < kInitRows; ++r)
+        if (w[r] != nullptr) x[r] = v[r][col];
+#pragma unroll
+      for (int r = 0; r < kInitRows; ++r)
+        if (w[r] != nullptr) w[r][col] = x[r];
+    }
+  }
+}
+
+// The last position of an upsert's new key, from the spare word of its index
+// slot (see k_put_probe), which is put back.
+__device__ __forceinline__ uint64_t take_position(Bucket* __restrict__ idx, uint32_t slot) {
+  uint32_t* w = &idx[slot / kSlots].aux[slot % kSlots];
+  const uint32_t pos = ~*w;
+  *w = 0xFFFFFFFFu;
+  return pos;
+}
+
 // Rows for the new keys ks[0, m) (index slots sl[...]) whose ranks among all
 // new keys of the call are base + rk[...]: index row ids, zero accumulators,
-// initial rows (written along rows).
+// initial rows, or an upsert's value rows (written along rows).
 template <int NT, class KP, class SP, class RP>
-__device__ __forceinline__ void write_new_rows(const KP ks, const SP sl, const RP rk, uint32_t m, uint64_t base,
+__device__ __forceinline__ void write_new_rows(KP ks, const SP sl, const RP rk, uint32_t m, uint64_t base,
                                                Bucket* __restrict__ idx, const RowStore& store,
                                                float* __restrict__ state, int D, uint64_t seed,
-                                               unsigned long long* __restrict__ clock, uint64_t cepoch) {
+                                               unsigned long long* __restrict__ clock, uint64_t cepoch,
+                                               const float* __restrict__ values) {
   for (uint32_t j = threadIdx.x; j < m; j += NT) {
     const uint32_t slot = sl[j];
     const uint32_t row = (uint32_t)(base + rk[j]);
     idx[slot / kSlots].row[slot % kSlots] = row;
     state[row] = 0.0f;
     if (clock != nullptr) clock[row] = new_row_clock(cepoch);
+    if (values != nullptr) ks[j] = take_position(idx, slot);
   }
-  write_init_rows<NT>(ks, rk, m, base, store, D, seed);
+  if (values != nullptr) {
+    __syncthreads();
+    write_value_rows<NT>(ks, rk, m, base, store, D, values);
+  } else {
+    write_init_rows<NT>(ks, rk, m, base, store, D, seed);
+  }
 }
 
 #ifndef MLKV_MAP
-__device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& store, uint64_t seed) {
+// Position, in the tiles' lists laid end to end, of sample k of S out of M
+// new keys: a hashed place in the k-th of S equal shares. The lists are
+// sorted, so evenly spaced positions take the same few quantiles of every
+// tile's list when the tiles hold equally many new keys (a table being
+// loaded); one range then holds nearly half of the keys.
+__device__ __forceinline__ uint64_t sample_at(uint64_t k, uint64_t M, uint32_t S) {
+  const uint64_t lo = k * M / S, width = (k + 1) * M / S - lo;
+  uint32_t h = (uint32_t)k * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0x85EBCA77u;
+  h ^= h >> 13;
+  return lo + (((uint64_t)h * width) >> 32);
+}
+
+// LDS of a block that assigns rows (NT threads).
+template <int NT>
+struct AssignLds {
+  uint64_t buf[kChunk + 2 * kAssignMine];  // 48 KiB; the two ranking methods lay it out differently
+  unsigned long long w64[NT / 64];
+  uint64_t cut[2];
+  __align__(16) uint32_t pref[NT + 1];
+  uint32_t w[NT / 64];
+  uint32_t nc;
+};
+
+// Rows for the call's M new keys, from size0 on in ascending key order (or,
+// with `err`, their index entries emptied again), by the first a.blocks
+// blocks of a kernel of NT threads. A probe tile lists at most TM new keys.
+template <int NT, int TM>
+__device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& store, uint64_t seed, uint64_t size0,
+                                           uint64_t M, int err, AssignLds<NT>& lds) {
   Bucket* __restrict__ const idx = a.idx;
   const NewKey* __restrict__ const newlist = a.newlist;
   const uint32_t* __restrict__ const tile_cnt = a.tile_cnt;
@@ -443,30 +551,19 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
   float* __restrict__ const state = a.state;
   Ctrl* const ctrl = a.ctrl;
   const uint64_t epoch = a.epoch, cepoch = a.cepoch;
-  const int64_t capacity = a.capacity;
   uint64_t* __restrict__ const xkey = a.xkey;
   uint32_t* __restrict__ const xslot = a.xslot;
   unsigned long long* __restrict__ const clock = a.clock;
   const RangeLists& rl = a.rl;
-  constexpr int NT = kAssignThreads;
-  __shared__ unsigned long long s_w64[NT / 64];
-  __shared__ uint32_t s_w[NT / 64];
-  __shared__ __align__(16) uint32_t s_pref[NT + 1];
-  __shared__ uint32_t s_nc;
-  __shared__ uint64_t s_cut[2];
-  // one LDS buffer of 48 KiB; the two ranking methods lay it out differently
-  __shared__ uint64_t s_buf[kChunk + 2 * kAssignMine];
-  static_assert(kRangeCap * 14 <= (int)sizeof(s_buf) && kRangeSamples * 12 <= (int)sizeof(s_buf), "LDS");
-  static_assert(kRangeSamples == NT * kSortPT && kRangeCap <= 65536, "sample and range sizes");
-
-  // the next call's range counts start at zero (this call's are read below)
-  if (rl.list != nullptr && blockIdx.x == 0)
-    for (int e = threadIdx.x; e < kMaxRanges; e += NT) rl.cnt_next[e] = 0u;
-  const uint64_t size0 = ctrl->size[epoch & 1];
-  const bool any_new = ctrl->new_epoch == epoch;
-  const uint64_t M = any_new ? count_new_keys<NT>(tile_cnt, ntiles, s_w64) : 0ull;
-  const int err = call_verdict(ctrl, epoch, size0, M, capacity, ctrl->bad_epoch, ctrl->overflow_epoch);
-  if (err && clock != nullptr) rollback_clocks(clock, size0, cepoch, a.blocks);
+  unsigned long long* const s_w64 = lds.w64;
+  uint32_t* const s_w = lds.w;
+  uint32_t* const s_pref = lds.pref;
+  uint32_t& s_nc = lds.nc;
+  uint64_t* const s_cut = lds.cut;
+  uint64_t* const s_buf = lds.buf;
+  constexpr int kSortPT = kRangeSamples / NT;
+  static_assert(kRangeCap * 14 <= (int)sizeof(lds.buf) && kRangeSamples * 16 <= (int)sizeof(lds.buf), "LDS");
+  static_assert(kRangeSamples == NT * kSortPT && kRangeCap <= 65536 && kRangeCap % NT == 0, "sample and range sizes");
   if (M == 0) return;
 
   if (err) {  // undo this call's insertions: the index returns to its state before the call
@@ -475,6 +572,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
       for (uint32_t j = threadIdx.x; j < c; j += NT) {
         const uint32_t slot = newlist[(size_t)t * tile_size + j].slot;
         idx[slot / kSlots].key[slot % kSlots] = kEmptyKey;
+        idx[slot / kSlots].aux[slot % kSlots] = 0xFFFFFFFFu;
       }
     }
     return;
@@ -489,8 +587,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
     // range. The probe kernel has filed the keys by range when cut points for
     // this many ranges were left (RangeLists): the range's keys are its list,
     // the keys below it the lists before. Otherwise every block takes the
-    // same sample of the new keys (sample k is the new key at position
-    // floor(k M / S) of the tiles' lists laid end to end) and the same cut
+    // same sample of the new keys (sample_at) and the same cut
     // points from it, which give block g the keys in [lo, hi); a binary
     // search of both bounds in every tile's sorted list of new keys counts
     // the keys below lo and finds the block's own. No block waits for another.
@@ -523,11 +620,12 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
         for (int t = tb; t < te; ++t) mine += tile_cnt[t];
         uint32_t tot;
         uint64_t pre = block_exclusive_scan<NT>(mine, s_w, &tot);
-        uint64_t k = (pre * S + M - 1) / M;  // first sample at or after pre
+        uint64_t k = pre * S / M;  // the sample of pre's share
         for (int t = tb; t < te && k < S; ++t) {
           const uint32_t c = tile_cnt[t];
           for (; k < S; ++k) {
-            const uint64_t gk = k * M / S;
+            const uint64_t gk = sample_at(k, M, S);
+            if (gk < pre) continue;
             if (gk >= pre + c) break;
             s_sat[k] = (uint32_t)t * (uint32_t)tile_size + (uint32_t)(gk - pre);
           }
@@ -536,16 +634,16 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
       }
       __syncthreads();
       uint64_t v[kSortPT];
-  #pragma unroll
+#pragma unroll
       for (uint32_t u = 0; u < kSortPT; ++u) v[u] = newlist[s_sat[threadIdx.x + u * NT]].key;
       // the cut points: the samples of rank g S / G and (g + 1) S / G of the
       // sorted sample (with fewer new keys than samples a key is sampled more
       // than once, and equal cut points give an empty range); eight sample
       // gaps per range keep the largest range near twice the mean
-      sort_keys<NT>(v, s_buf, s_buf + S);
+      sort_keys<NT, kSortPT>(v, s_buf, s_buf + S);
       {
         const uint32_t r1 = (uint32_t)((uint64_t)g * S / G), r2 = (uint32_t)((uint64_t)(g + 1) * S / G);
-  #pragma unroll
+#pragma unroll
         for (uint32_t u = 0; u < kSortPT; ++u) {
           if (threadIdx.x * kSortPT + u == r1) s_cut[0] = v[u];
           if (threadIdx.x * kSortPT + u == r2) s_cut[1] = v[u];
@@ -557,7 +655,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
       hi = g + 1 == G ? kEmptyKey : s_cut[1];
       // keys in [lo, hi) first go to LDS: key, slot (later the rank), and
       // their order by local sub-range
-      below = search_tile_lists<NT>(newlist, tile_cnt, ntiles, tile_size, lo, hi, [&](uint32_t off, uint32_t cnt) {
+      below = search_tile_lists<NT, TM>(newlist, tile_cnt, ntiles, tile_size, lo, hi, [&](uint32_t off, uint32_t cnt) {
         const uint32_t at = atomicAdd(&s_nc, cnt);
         for (uint32_t e = 0; e < cnt && at + e < (uint32_t)kRangeCap; ++e) {
           s_key[at + e] = newlist[off + e].key;
@@ -666,10 +764,14 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
 #pragma unroll
       for (int u = 0; u < kRangeCap / NT; ++u) {
         const uint32_t j = threadIdx.x + u * NT;
-        if (j < c) s_sr[j] = rk[u];
+        if (j < c) {
+          if (a.values != nullptr) s_key[j] = take_position(idx, s_sr[j]);
+          s_sr[j] = rk[u];
+        }
       }
       __syncthreads();
-      write_init_rows<NT>(s_key, s_sr, c, base, store, D, seed);
+      if (a.values != nullptr) write_value_rows<NT>(s_key, s_sr, c, base, store, D, a.values);
+      else write_init_rows<NT>(s_key, s_sr, c, base, store, D, seed);
     } else {
       // more keys in the range than LDS holds: gather them in global scratch
       // at [below, below + c), which no other block's range overlaps, then
@@ -684,7 +786,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
           xslot[below + j] = nk.slot;
         }
       } else {
-        search_tile_lists<NT>(newlist, tile_cnt, ntiles, tile_size, lo, hi, [&](uint32_t off, uint32_t cnt) {
+        search_tile_lists<NT, TM>(newlist, tile_cnt, ntiles, tile_size, lo, hi, [&](uint32_t off, uint32_t cnt) {
           const uint32_t at = atomicAdd(&s_nc, cnt);
           for (uint32_t e = 0; e < cnt; ++e) {
             const NewKey nk = newlist[off + e];
@@ -733,7 +835,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
           }
         }
         __syncthreads();
-        write_new_rows<NT>(s_mk, s_ms, s_mr, m, base, idx, store, state, D, seed, clock, cepoch);
+        write_new_rows<NT>(s_mk, s_ms, s_mr, m, base, idx, store, state, D, seed, clock, cepoch, a.values);
         __syncthreads();
       }
     }
@@ -748,15 +850,16 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
   uint64_t* s_key = s_buf + kChunk;                                       // [kAssignMine]
   uint32_t* s_slot = reinterpret_cast<uint32_t*>(s_key + kAssignMine);    // [kAssignMine]
   uint32_t* s_rank = s_slot + kAssignMine;                                // [kAssignMine]
-  constexpr int kTilesAt = kAssignMine / kGetTile;  // tiles taken at a time, kGetTile entries each
+  constexpr int kAssignBatch = kAssignMine / NT;
+  constexpr int kTilesAt = kAssignMine / TM;  // tiles taken at a time, TM entries each
   for (int tb = blockIdx.x; tb < ntiles; tb += a.blocks * kTilesAt) {
     uint32_t have = 0;
 #pragma unroll
     for (int b = 0; b < kAssignBatch; ++b) {
       const int m = b * NT + (int)threadIdx.x;
-      const int t = tb + m / kGetTile * (int)a.blocks;
+      const int t = tb + m / TM * (int)a.blocks;
       const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      const uint32_t j = m % kGetTile;
+      const uint32_t j = m % TM;
       if (j < c) {
         const NewKey nk = newlist[(size_t)t * tile_size + j];
         s_key[m] = nk.key;
@@ -789,12 +892,15 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
       idx[slot / kSlots].row[slot % kSlots] = row;
       state[row] = 0.0f;
       if (clock != nullptr) clock[row] = new_row_clock(cepoch);
+      if (a.values != nullptr) s_key[m] = take_position(idx, slot);
     }
-    // initial rows, a wave per row
+    if (a.values != nullptr) __syncthreads();
+    // initial or value rows, a wave per row
     for (int b = 0; b < kTilesAt; ++b) {
       const int t = tb + b * (int)a.blocks;
       const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      write_init_rows<NT>(s_key + b * kGetTile, s_rank + b * kGetTile, c, size0, store, D, seed);
+      if (a.values != nullptr) write_value_rows<NT>(s_key + b * TM, s_rank + b * TM, c, size0, store, D, a.values);
+      else write_init_rows<NT>(s_key + b * TM, s_rank + b * TM, c, size0, store, D, seed);
     }
     __syncthreads();
   }
@@ -866,7 +972,18 @@ __device__ __forceinline__ void copy_rows(const GetRowsArgs& a) {
 template <int VEC, bool kTrack, bool kStream>
 __global__ __launch_bounds__(kAssignThreads, 6) void k_get_rows(const GetRowsArgs ra, const AssignArgs aa) {
   if (ra.out != nullptr) copy_rows<VEC, kTrack, kStream>(ra);
-  if (blockIdx.x < aa.blocks) assign_new(aa, ra.store, ra.seed);
+  if (blockIdx.x >= aa.blocks) return;
+  __shared__ AssignLds<kAssignThreads> lds;
+  Ctrl* const ctrl = aa.ctrl;
+  // the next call's range counts start at zero (this call's are read by assign_new)
+  if (aa.rl.list != nullptr && blockIdx.x == 0)
+    for (int e = threadIdx.x; e < kMaxRanges; e += kAssignThreads) aa.rl.cnt_next[e] = 0u;
+  const uint64_t size0 = ctrl->size[aa.epoch & 1];
+  const uint64_t M =
+      ctrl->new_epoch == aa.epoch ? count_new_keys<kAssignThreads>(aa.tile_cnt, aa.ntiles, lds.w64) : 0ull;
+  const int err = call_verdict(ctrl, aa.epoch, size0, M, aa.capacity, ctrl->bad_epoch, ctrl->overflow_epoch);
+  if (err && aa.clock != nullptr) rollback_clocks(aa.clock, size0, aa.cepoch, aa.blocks);
+  assign_new<kAssignThreads, kGetTile>(aa, ra.store, ra.seed, size0, M, err, lds);
 }
 #endif  // MLKV_MAP
 
@@ -913,7 +1030,7 @@ constexpr int kTileHash = 2 * kPutTile;  // LDS hash slots per tile
 template <class M, bool kAhead>
 __global__ __launch_bounds__(kPutThreads) void k_put_probe(
     Bucket* __restrict__ idx, uint32_t nb_log2, const uint64_t* __restrict__ keys,
-    const float* __restrict__ grads, int64_t n, int tlen, int D, int op, int pb, int ntiles,
+    const float* __restrict__ grads, int64_t n, int tlen, int D, int op, uint32_t dup_min, int pb, int ntiles,
     uint64_t* __restrict__ items,
     uint32_t* __restrict__ meta, double* __restrict__ partials, NewKey* __restrict__ newlist,
     uint32_t* __restrict__ tile_cnt, Ctrl* ctrl, uint64_t epoch, const uint64_t* __restrict__ pc_key,
@@ -938,7 +1055,11 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
   const int tile = blockIdx.x;
   const int64_t base = (int64_t)tile * tlen;        // batch position of the tile's entry 0
   const int64_t sbase = (int64_t)tile * kPutTile;   // the tile's slots in items / newlist
-  if (tile == 0 && tid == 0) ctrl->spill_next = 0;
+  if (tile == 0 && tid == 0) {
+    ctrl->spill_next = 0;
+    ctrl->unit_single = 0;
+    ctrl->unit_multi = 0;
+  }
   for (int d = tid; d < NP; d += NT) s_hist[d] = 0;
   for (int h = tid; h < kTileHash; h += NT) {
     s_hkey[h] = ~0ull;
@@ -1005,7 +1126,6 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
   // assignment keeps the last position; a sum adds the key's gradient rows
   // here, in fp64), the entries of the others stay items of their own, which
   // the key's first entry emits together in position order
-  const uint32_t dup_min = op == kOpAssign ? 2u : (uint32_t)kPresumMin;
   uint32_t cnt[KPT];
   bool dup[KPT], merged[KPT], owner[KPT];
   uint32_t n_own = 0, l_own = 0;
@@ -1190,7 +1310,8 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
     valid[kk] = pr[kk].status == P_HIT || pr[kk].status == P_NEW_MINE || pr[kk].status == P_NEW_OTHER;
     if (pr[kk].status == P_NEW_MINE) {
       const uint32_t j = atomicAdd(&s_cnt, 1u);
-      newlist[(size_t)sbase + j] = NewKey{key[kk], pr[kk].slot, 0u};
+      s_hkey[j] = key[kk];  // (the tile's hash table is no longer read)
+      s_hcnt[j] = pr[kk].slot;
       ctrl->new_epoch = epoch;
     }
     const bool fresh = pr[kk].status != P_HIT;
@@ -1210,6 +1331,12 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
     d[kk] = 0;
     r[kk] = 0;
     if (emit[kk]) {
+      // an upsert's new key: its last position goes to the spare word of its
+      // index slot (complemented: an unused word is all ones)
+      if (!kAhead && op == kOpAssign && item_fresh(x[kk])) {
+        const uint32_t slot = item_tag(x[kk]);
+        atomicMin(&idx[slot / kSlots].aux[slot % kSlots], ~item_pos(x[kk]));
+      }
       d[kk] = group_partition(item_group(x[kk]), pb);
       r[kk] = atomicAdd(&s_hist[d[kk]], ne[kk]);
     }
@@ -1253,7 +1380,17 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
       dst[0] = merged[kk] && op != kOpAssign ? (x[kk] | kItemSummed) : x[kk];
     }
   }
-  if (!kAhead && tid == 0) tile_cnt[tile] = s_cnt;  // ahead of a get, the counts are the get's
+  if constexpr (!kAhead) {  // ahead of a get, the lists and counts are the get's
+    // the tile's list of new keys, in ascending key order (each at its rank)
+    const uint32_t c = s_cnt;
+    for (uint32_t j = tid; j < c; j += NT) {
+      const uint64_t k = s_hkey[j];
+      uint32_t at = 0;
+      for (uint32_t e = 0; e < c; ++e) at += s_hkey[e] < k ? 1u : 0u;
+      newlist[(size_t)sbase + at] = NewKey{k, s_hcnt[j], 0u};
+    }
+    if (tid == 0) tile_cnt[tile] = c;
+  }
   // keys summed in chunks: add the chunks' partial sums in order
   if (op != kOpAssign && chunked) {
     __syncthreads();
@@ -1280,7 +1417,7 @@ __global__ __launch_bounds__(kPutThreads) void k_put_probe(
 }
 
 // ---------------------------------------------------------------------------
-// Segment sums and row updates (shared by put_reduce and its spill path)
+// Row updates
 // ---------------------------------------------------------------------------
 
 // Sum over the LPR lanes of a lane group (LPR a power of two, groups aligned);
@@ -1366,77 +1503,13 @@ struct SegmentOps {
       }
     }
   }
-
-  // The row becomes g.
-  static __device__ __forceinline__ void assign(const V (&g)[K], float* __restrict__ wrow, int D, int q) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int col = M::col(k, q, D);
-      if (M::on(k, q, D)) store_vec<VEC>(wrow + col, g[k]);
-    }
-  }
-
-  // The update of op for one row; w and G are the row's current values
-  // (not read for kOpAssign, G only for kOpAdagrad).
-  static __device__ __forceinline__ void update(int op, const V (&g)[K], V (&w)[K], float G,
-                                                float* __restrict__ wrow, float* __restrict__ state,
-                                                uint32_t row, int D, int q, bool d_pow2, double inv_d, float lr,
-                                                float eps) {
-    if (op == kOpAdagrad) adagrad(g, w, G, wrow, state, row, D, q, d_pow2, inv_d, lr, eps);
-    else if (op == kOpSgd) sgd(g, w, wrow, D, q, lr);
-    else assign(g, wrow, D, q);
-  }
-
-  static __device__ __forceinline__ void zero(double (&acc)[K][VEC]) {
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[k][x] = 0.0;
-  }
-
-  // g = fp32(acc) over the fp64 partials row at position pos (that row is no
-  // longer read once its segment is summed).
-  static __device__ __forceinline__ void store_g(const double (&acc)[K][VEC], const double* partials,
-                                                 uint32_t pos, int D, int q) {
-    float* gp = reinterpret_cast<float*>(const_cast<double*>(partials) + (size_t)pos * (size_t)D);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int col = M::col(k, q, D);
-      if (M::on(k, q, D)) {
-        V v;
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) VecT<VEC>::set(v, x, (float)acc[k][x]);
-        store_vec<VEC>(gp + col, v);
-      }
-    }
-  }
-};
-
-struct RedCtx {
-  int op;
-  Bucket* idx;
-  const float* grads;
-  const double* partials;
-  RowStore store;
-  float* state;
-  int D;
-  uint64_t seed;
-  float lr;
-  float eps;
-  uint64_t size0;
-  unsigned long long* clock;  // staleness words, or nullptr
 };
 
 // A put completes one served get on the row (bounded staleness, Sec.
-// III-C1): its count drops by one, never below 0. One lane per row.
-__device__ __forceinline__ void put_clock(unsigned long long* __restrict__ clock, uint32_t row) {
-  const unsigned long long w = clock[row];
-  if ((w & kClockCount) != 0) clock[row] = w - 1;
-}
-
-// The same from the low 32 bits of the word, loaded ahead with the row: they
-// hold the count (a nonzero count drops without borrowing from the epoch
-// bits above it, so only the low word is written).
+// III-C1): its count drops by one, never below 0. One lane per row, from the
+// low 32 bits of the word, loaded ahead with the row: they hold the count (a
+// nonzero count drops without borrowing from the epoch bits above it, so only
+// the low word is written).
 static_assert(kClockBits < 32, "the count fits the low word of a staleness word");
 __device__ __forceinline__ uint32_t clock_low(const unsigned long long* __restrict__ clock, uint32_t row) {
   return reinterpret_cast<const uint32_t*>(clock + row)[0];  // little-endian: the low word comes first
@@ -1445,387 +1518,155 @@ __device__ __forceinline__ void put_clock_low(unsigned long long* __restrict__ c
   if ((lo & (uint32_t)kClockCount) != 0u) reinterpret_cast<uint32_t*>(clock + row)[0] = lo - 1u;
 }
 
-// Run-length encodes items sorted by value: seg[s] = first item of segment s,
-// seg[S] = mp, sid[j] = segment of item j. Returns S (block-uniform).
-template <int NT, class IP, class SP, class DP>
-__device__ __forceinline__ uint32_t encode_segments(IP it, uint32_t mp, SP seg, DP sid, uint32_t* s_w) {
-  uint32_t S = 0;
-  for (uint32_t b0 = 0; b0 < mp; b0 += NT) {
-    const uint32_t j = b0 + threadIdx.x;
-    const uint32_t head = (j < mp) && (j == 0 || item_group(it[j]) != item_group(it[j - 1])) ? 1u : 0u;
-    uint32_t tot;
-    const uint32_t pre = block_exclusive_scan<NT>(head, s_w, &tot);
-    if (head) seg[S + pre] = j;
-    if (j < mp) sid[j] = S + pre + head - 1;
-    S += tot;
-  }
-  if (threadIdx.x == 0) seg[S] = mp;
-  __syncthreads();
-  return S;
+// The row of a unit's key: its tag, or, for a key new in the call, the row
+// its index slot holds by now.
+__device__ __forceinline__ uint32_t unit_row(const Bucket* __restrict__ idx, uint32_t tag, bool fresh) {
+  return fresh ? idx[tag / kSlots].row[tag % kSlots] : tag;
 }
 
-// Keys new in this call (fresh items) get their rows: row = size + rank of
-// the key among all new keys of the call. The block's new keys (up to NT at a
-// time) are sorted in LDS; every new key of the call, streamed through LDS,
-// adds one to the count of the first of them above it, and a key's rank is
-// the sum of the counts up to its own position. Initial row and zero
-// accumulator are written, and the row replaces the slot in the segment's
-// first item, whose "fresh" bit stays set. s_chunk: at least (kChunk + NT)
-// 64-bit words plus NT + 1 32-bit words of LDS.
-template <int NT, class IP, class SP>
-__device__ __forceinline__ void resolve_new_rows(IP it, SP seg, uint32_t S, const RedCtx& c,
-                                                 const NewKey* __restrict__ newlist,
-                                                 const uint32_t* __restrict__ tile_cnt, int ntiles,
-                                                 uint32_t* s_pref, uint32_t* s_w,
-                                                 unsigned long long* s_w64, uint64_t* s_chunk) {
-  uint64_t* s_pk = s_chunk + kChunk;                          // [NT] the batch's new keys, sorted
-  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_pk + NT);  // [NT + 1] counts, then their prefix
-  for (uint32_t s0 = 0; s0 < S; s0 += NT) {
-    const uint32_t s = s0 + threadIdx.x;
-    bool pend = false;
-    uint32_t slot = 0;
-    uint64_t x = 0;
-    if (s < S) {
-      x = it[seg[s]];
-      pend = item_fresh(x);
-      slot = item_tag(x);
-    }
-    uint32_t np;
-    const uint32_t pi = block_exclusive_scan<NT>(pend ? 1u : 0u, s_w, &np);
-    if (np == 0) continue;
-    const uint64_t key = pend ? c.idx[slot / kSlots].key[slot % kSlots] : 0ull;
-    uint32_t np2 = 1;
-    while (np2 < np) np2 <<= 1;
-    for (uint32_t j = threadIdx.x; j < np2; j += NT) s_pk[j] = kEmptyKey;  // no key equals it
-    for (uint32_t j = threadIdx.x; j <= np; j += NT) s_cnt[j] = 0;
-    __syncthreads();
-    if (pend) s_pk[pi] = key;
-    __syncthreads();
-    block_bitonic_sort<NT>(s_pk, np2);
-    for_each_new_key_chunk<NT>(newlist, tile_cnt, ntiles, kPutTile, s_pref, s_w, s_chunk,
-                               [&](const uint64_t* ck, uint32_t cnt) {
-                                 for (uint32_t e = threadIdx.x; e < cnt; e += NT) {
-                                   const uint64_t xk = ck[e];
-                                   uint32_t lo = 0, hi = np;  // first pending key above xk
-                                   while (lo < hi) {
-                                     const uint32_t mid = (lo + hi) >> 1;
-                                     if (s_pk[mid] <= xk) lo = mid + 1;
-                                     else hi = mid;
-                                   }
-                                   if (lo < np) atomicAdd(&s_cnt[lo], 1u);
-                                 }
-                               });
-    {
-      const uint32_t v = threadIdx.x < np ? s_cnt[threadIdx.x] : 0u;
-      uint32_t tot;
-      const uint32_t ex = block_exclusive_scan<NT>(v, s_w, &tot);
-      if (threadIdx.x < np) s_cnt[threadIdx.x] = ex + v;  // new keys below the key at this position
-      __syncthreads();
-    }
-    if (pend) {
-      uint32_t lo = 0, hi = np - 1;  // the key's own position
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (s_pk[mid] < key) lo = mid + 1;
-        else hi = mid;
-      }
-      const uint32_t rank = s_cnt[lo];
-      const uint32_t row = (uint32_t)(c.size0 + rank);
-      c.idx[slot / kSlots].row[slot % kSlots] = row;
-      it[seg[s]] = make_item(true, row, item_low31(x));
-      const uint64_t s0k = splitmix_mix(key ^ c.seed);
-      float* w = c.store.wptr(row);
-      for (int col = 0; col < c.D; ++col) w[col] = init_elem(s0k, col);
-      c.state[row] = 0.0f;
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-}
-
-// Update, phase A: the fp64 sum of every segment that needs one (more than
-// one item, or an in-tile sum as its only item) over items [0, mA), written
-// as fp32 g over the partials row of the segment's first item. Each lane
-// group takes an equal contiguous slice of the items and walks it in batches
-// (all gradient rows of a batch are loaded together). The piece of a segment
-// that began before the slice goes to s_part[group]; after a barrier, the
-// group where a cut segment began adds the pieces of the following groups in
-// slice order.
-template <class M, int NT, class IP, class SP, class DP>
-__device__ __forceinline__ void sum_segments(IP it, SP seg, DP sid, uint32_t mA, const RedCtx& c,
-                                             double* s_part) {
-  using Ops = SegmentOps<M>;
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, RPW = M::RPW;
-  constexpr int NG = (NT / 64) * RPW;
-  constexpr int B = (K * VEC >= 8) ? 2 : 4;
-  using V = typename VecT<VEC>::T;
-  const int lane = threadIdx.x & 63;
-  const int g = lane / LPR;
-  const int q = lane % LPR;
-  const int gid = (threadIdx.x >> 6) * RPW + g;
-  const int D = c.D;
-
-  const uint32_t L = (mA + NG - 1) / NG;
-  const uint32_t lo = min(mA, (uint32_t)gid * L);
-  const uint32_t hi = min(mA, lo + L);
-
-  double acc[K][VEC];
-  Ops::zero(acc);
-  for (uint32_t j0 = lo; j0 < hi; j0 += B) {
-    V gv[B][K];
-    double pv[B][K][VEC];
-    uint32_t first[B];
-    bool use[B], ends[B], owned[B], summ[B];
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const uint32_t j = j0 + u;
-      use[u] = false;
-      ends[u] = false;
-      owned[u] = false;
-      summ[u] = false;
-      first[u] = 0;
-      if (j < hi) {
-        const uint64_t x = it[j];
-        const uint32_t sj = sid[j];
-        const uint32_t b = seg[sj], e = seg[sj + 1];
-        summ[u] = item_summed(x);
-        use[u] = (e - b > 1) || summ[u];
-        ends[u] = e == j + 1;
-        owned[u] = b >= lo;
-        first[u] = b;
-        if (use[u]) {
-          if (summ[u]) {
-            const double* pr = c.partials + (size_t)item_pos(x) * (size_t)D;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int col = M::col(k, q, D);
-#pragma unroll
-              for (int v = 0; v < VEC; ++v)
-                if (M::on(k, q, D)) pv[u][k][v] = pr[col + v];
-            }
-          } else {
-            const float* gr = c.grads + (size_t)item_pos(x) * (size_t)D;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int col = M::col(k, q, D);
-              if (M::on(k, q, D)) gv[u][k] = load_vec<VEC>(gr + col);
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      if (!use[u]) continue;
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        if (M::on(k, q, D)) {
-#pragma unroll
-          for (int x = 0; x < VEC; ++x)
-            acc[k][x] += summ[u] ? pv[u][k][x] : (double)VecT<VEC>::get(gv[u][k], x);
-        }
-      }
-      if (ends[u]) {
-        if (owned[u]) {
-          Ops::store_g(acc, c.partials, item_pos(it[first[u]]), D, q);
-        } else {
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-            const int col = M::col(k, q, D);
-#pragma unroll
-            for (int x = 0; x < VEC; ++x)
-              if (M::on(k, q, D)) s_part[(size_t)gid * D + col + x] = acc[k][x];
-          }
-        }
-        Ops::zero(acc);
-      }
-    }
-  }
-  // the slice ends inside a segment
-  uint32_t tail = 0xFFFFFFFFu;
-  if (lo < hi) {
-    const uint32_t sl = sid[hi - 1];
-    if (seg[sl + 1] > hi) {
-      if (seg[sl] >= lo) {
-        tail = sl;
-      } else {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int col = M::col(k, q, D);
-#pragma unroll
-          for (int x = 0; x < VEC; ++x)
-            if (M::on(k, q, D)) s_part[(size_t)gid * D + col + x] = acc[k][x];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  if (tail != 0xFFFFFFFFu) {
-    const uint32_t end = seg[tail + 1];
-    for (uint32_t h = gid + 1; h < (uint32_t)NG && h * L < end; ++h) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int col = M::col(k, q, D);
-#pragma unroll
-        for (int x = 0; x < VEC; ++x)
-          if (M::on(k, q, D)) acc[k][x] += s_part[(size_t)h * D + col + x];
-      }
-    }
-    Ops::store_g(acc, c.partials, item_pos(it[seg[tail]]), D, q);
-  }
-  __syncthreads();
-}
-
-// Update, phase B: one Adagrad step per segment. Segments are dealt to lane
-// groups in turn (group gid takes gid, gid + NG, ...), so the groups of a
-// wave update rows together. g is read from the partials row phase A wrote,
-// or from the segment's only gradient row.
-template <class M, int NT, class IP, class SP>
-__device__ __forceinline__ void update_segments(IP it, SP seg, uint32_t S, const RedCtx& c) {
-  using Ops = SegmentOps<M>;
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, RPW = M::RPW;
-  constexpr int NG = (NT / 64) * RPW;
-  constexpr int BB = (K * VEC >= 8) ? 2 : 4;
-  using V = typename VecT<VEC>::T;
-  const int lane = threadIdx.x & 63;
-  const int g = lane / LPR;
-  const int q = lane % LPR;
-  const int gid = (threadIdx.x >> 6) * RPW + g;
-  const int D = c.D;
-  const bool d_pow2 = (D & (D - 1)) == 0;
-  const double inv_d = 1.0 / (double)D;
-
-  for (uint32_t s0 = gid; s0 < S; s0 += (uint32_t)NG * BB) {
-    V gf[BB][K], w[BB][K];
-    float G[BB];
-    uint32_t row[BB];
-#pragma unroll
-    for (int u = 0; u < BB; ++u) {
-      const uint32_t s = s0 + u * NG;
-      G[u] = 0.0f;
-      row[u] = 0;
-      if (s < S) {
-        const uint32_t b = seg[s];
-        const uint64_t x = it[b];
-        row[u] = item_tag(x);
-        const bool from_a = c.op != kOpAssign && ((seg[s + 1] - b > 1) || item_summed(x));
-        // an assignment takes the value row at the key's last position
-        const uint32_t pos = c.op == kOpAssign ? item_pos(it[seg[s + 1] - 1]) : item_pos(x);
-        const float* src = from_a ? reinterpret_cast<const float*>(c.partials + (size_t)pos * (size_t)D)
-                                  : c.grads + (size_t)pos * (size_t)D;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int col = M::col(k, q, D);
-          if (M::on(k, q, D)) {
-            gf[u][k] = load_vec<VEC>(src + col);
-            w[u][k] = load_vec<VEC>(c.store.ptr(row[u]) + col);
-          }
-        }
-        if (c.op == kOpAdagrad) G[u] = c.state[row[u]];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < BB; ++u) {
-      if (s0 + u * NG < S) {
-        Ops::update(c.op, gf[u], w[u], G[u], c.store.wptr(row[u]), c.state, row[u], D, q, d_pow2, inv_d, c.lr,
-                    c.eps);
-        if (c.clock != nullptr && q == 0) put_clock(c.clock, row[u]);
-      }
-    }
-  }
-}
-
+#ifndef MLKV_MAP
 // ---------------------------------------------------------------------------
-// Put, second kernel: one block per partition. The block gathers the
-// partition's items, groups them by key in LDS with each key's items in
-// ascending position, gives keys new in the call their rows, then sums every
-// key's gradient rows in fp64 and applies the update to its row. A partition
-// larger than the block's LDS share takes the global spill path.
+// Put, second kernel: one block per partition. It gathers the partition's
+// items, groups them by key in LDS with each key's items in ascending
+// position, and leaves the call's update as units, one per distinct key, in
+// three lists of the whole call (PutUnits): keys with one gradient row
+// (`single`, the item itself), keys whose items need a sum (`multi`: tag,
+// number of items, where its items start in `mitem`) and those with more than
+// long_over items (`lng`). Every unit is independent of the others, so the
+// order of the lists, which depends on the blocks' timing, changes no result.
+// The first blocks then assign rows to the keys the call inserted.
+// An upsert (kUpsert) needs no units: the block writes the value row of each
+// present key's last position itself, and the rows of new keys are written
+// where they are assigned.
+//
+// Bound by the latency of LDS and of the barriers between its steps. Grouping
+// and updating in one kernel of a block per CU (125 registers, 145 KB of LDS)
+// left HBM idle while it grouped, and segments cut between its lane groups
+// were added up by one of them in a serial chain (10 to 28 us at dims 10 to
+// 16). Apart, this kernel runs two blocks per CU at 64 registers, and the
+// update kernel below streams with every wave the chip holds. Both together
+// against the one kernel, us: 213k lookups of dim 64 18 + 29 / 52, 131k of dim
+// 32 16 + 14 / 42, 106k of dim 10 15 + 10 / 47, 4096 of dim 16 12 + 10 / 28, 150k
+// of dim 400 16 + 132 / 184, 1M of dim 128 37 + 303 / 413.
 // ---------------------------------------------------------------------------
-template <class M>
-struct ReduceCfg {
-  static constexpr int DMAX = M::LPR * M::K * M::VEC;
-  // the pieces of segments cut between lane groups (one fp64 row per group,
-  // NT * K * VEC doubles) take 32 KiB at every row map
-  static constexpr int NT = DMAX <= 256 ? 1024 : DMAX <= 512 ? 512 : 256;
-  static constexpr int NG = (NT / 64) * M::RPW;
-  // gradient rows a lane group has in flight in the sums, and rows it
-  // updates at a time for keys seen once (at 1024 threads a lane has 128
-  // registers: four rows in flight fit them without spilling)
-  static constexpr int B = (M::K * M::VEC >= 16) ? 2 : (M::K * M::VEC >= 8 || NT >= 1024) ? 4 : 8;
-  static constexpr int BS = B;
-};
-
 constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-constexpr int kMaxGroups = 256;  // lane groups of a reduce block at most
-// Segments of more than kLongSeg items are put in order through a bitmask of
-// their items' places in the gathered list (at most kMaskSegs of them per
+constexpr int kGroupThreads = 1024;
+// Units of more than kRankMask items are put in order through a bitmask of
+// their items' places in the gathered list (at most kMaskUnits of them per
 // partition; others compare their items pairwise).
-constexpr uint32_t kLongSeg = 32;
-constexpr int kMaskSegs = 32;
+constexpr uint32_t kRankMask = 32;
+constexpr int kMaskUnits = 16;
 constexpr int kMaskWords = kRedCap / 32;
 
-// Dynamic LDS of a reduce block, in bytes. The first region (gathered items
-// and grouping tables) is dead once the items are grouped; it then holds a
-// chunk of new keys (rows for keys new in the call) and after that the
-// pieces of cut segments.
-template <int NT>
-struct ReduceLds {
-  static constexpr size_t it = 0;                                    // u64[kRedCap] gather order
-  static constexpr size_t hidx = it + 8 * (size_t)kRedCap;            // u32[kRedHash]
-  static constexpr size_t hcnt = hidx + 4 * (size_t)kRedHash;         // u32[kRedHash]
-  static constexpr size_t inv = hcnt + 4 * (size_t)kRedHash;          // u16[kRedHash]
-  static constexpr size_t slot = inv + 2 * (size_t)kRedHash;          // u16[kRedCap]
-  static constexpr size_t ord = slot + 2 * (size_t)kRedCap;           // u16[kRedCap]
-  static constexpr size_t reuse = align16(ord + 2 * (size_t)kRedCap);  // end of the reused region
-  static constexpr size_t srt = reuse;                                // u64[kRedCap] grouped items
-  static constexpr size_t seg = srt + 8 * (size_t)kRedCap;            // u32[kRedCap + 1]
-  static constexpr size_t sid = align16(seg + 4 * ((size_t)kRedCap + 1));  // u16[kRedCap]
-  static constexpr size_t lid = align16(sid + 2 * (size_t)kRedCap);   // u16[kRedCap] mask of each segment
-  static constexpr size_t mask = align16(lid + 2 * (size_t)kRedCap);  // u32[kMaskSegs][kMaskWords]
-  static constexpr size_t pref = align16(mask + 4 * (size_t)kMaskSegs * kMaskWords);  // u32[NT + 1]
-  static constexpr size_t w = align16(pref + 4 * ((size_t)NT + 1));   // u32[NT / 64]
-  static constexpr size_t w64 = align16(w + 4 * (size_t)(NT / 64));   // u64[NT / 64]
-  static constexpr size_t misc = align16(w64 + 8 * (size_t)(NT / 64));  // u32[8]
-  static constexpr size_t base = misc + 32;                           // u64
-  static constexpr size_t slo = base + 16;                            // u32[kMaxGroups + 1]
-  static constexpr size_t total = align16(slo + 4 * ((size_t)kMaxGroups + 1));
+// Dynamic LDS of a grouping block, in bytes (two blocks per CU).
+struct GroupLds {
+  static constexpr size_t it = 0;                                  // u64[kRedCap] gather order
+  static constexpr size_t hidx = it + 8 * (size_t)kRedCap;         // u32[kRedHash] first item, then a fill cursor
+  static constexpr size_t hcnt = hidx + 4 * (size_t)kRedHash;      // u32[kRedHash] items, then start | items << 16
+  static constexpr size_t slot = hcnt + 4 * (size_t)kRedHash;      // u16[kRedCap] hash slot of each item
+  static constexpr size_t ord = slot + 2 * (size_t)kRedCap;        // u16[kRedCap] items by unit
+  static constexpr size_t lid = ord + 2 * (size_t)kRedCap;         // u8[kRedHash] mask of each unit
+  static constexpr size_t mask = lid + (size_t)kRedHash;           // u32[kMaskUnits][kMaskWords]
+  static constexpr size_t w64 = mask + 4 * (size_t)kMaskUnits * kMaskWords;  // u64[kGroupThreads / 64]
+  static constexpr size_t w = w64 + 8 * (size_t)(kGroupThreads / 64);        // u32[kGroupThreads / 64]
+  static constexpr size_t misc = align16(w + 4 * (size_t)(kGroupThreads / 64));  // u64[2], u32[8]
+  static constexpr size_t grouping = misc + 48;
+  static constexpr size_t total = grouping > sizeof(AssignLds<kGroupThreads>) ? align16(grouping)
+                                                                             : align16(sizeof(AssignLds<kGroupThreads>));
+  static constexpr size_t pref = hidx;  // u32[kGroupThreads], before the grouping
+  static_assert(total <= 80 * 1024, "two blocks per CU");
 };
 
-// Groups a partition's items by key in LDS.
-// In:  it[0, mp), the partition's items in the order put_probe's tiles
-//      listed them: tiles ascending, and within a tile a key's items
-//      together in ascending position; so the items of each key appear in
-//      position order (an in-tile sum is one item at the first position it
-//      covers).
-// Out: srt[0, mp) = the items grouped into segments, one per key, each
-//      segment's items in ascending position; segments [0, SA) need a sum
-//      (more than one item, or an in-tile sum as the only item) and hold the
-//      items [0, MA); segments [SA, S) are single items that need none.
-//      seg[s] = first item of segment s, seg[S] = mp; sid[i] = segment of
-//      item i; info = {S, SA, MA, any key new in the call}.
-// Segment order: keys go to an LDS hash table with linear probing. The set of
-// occupied slots does not depend on the order of insertion, only which key
-// sits where inside a run of occupied slots does; keys are therefore given
-// the slots of their run in ascending order, and segments follow these
-// places. Every order above thus depends only on the set of items.
-template <int NT>
-__device__ __forceinline__ void group_by_key(const uint64_t* it, uint32_t mp, uint64_t* srt, uint32_t* seg,
-                                             uint16_t* sid, uint32_t* hidx, uint32_t* hcnt, uint16_t* inv,
-                                             uint16_t* slot, uint16_t* ord, uint16_t* lid, uint32_t* mask,
-                                             unsigned long long* s_w64, uint32_t* info) {
-  constexpr int IPT = (kRedCap + NT - 1) / NT;
+// Units a block has counted: singles, multis, longs and items of multis and
+// longs, 16 bits each (a block groups at most kRedCap < 2^16 items).
+__device__ __forceinline__ uint64_t pack_unit(uint32_t single, uint32_t multi, uint32_t lng, uint32_t items) {
+  return (uint64_t)single | ((uint64_t)multi << 16) | ((uint64_t)lng << 32) | ((uint64_t)items << 48);
+}
+
+// Exclusive prefix of v within the block's waves plus a base per wave taken
+// from *s_tot (cleared before), so that every thread's share of the total is
+// its own; the order of the waves is any. No barrier.
+__device__ __forceinline__ uint64_t claim_u64(uint64_t v, unsigned long long* s_tot) {
+  const int lane = threadIdx.x & 63;
+  unsigned long long x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  unsigned long long base = 0;
+  if (lane == 63) base = atomicAdd(s_tot, x);
+  return __shfl(base, 63, 64) + x - v;
+}
+
+// Claims the block's entries in the call's lists: s_base[0..3] = first entry
+// among singles, multis, longs and items. One thread; two additions per block,
+// to different lines: additions to one line take about 10 ns each, whoever
+// makes them (four counters in one line: 10 us more for 256 blocks).
+__device__ __forceinline__ void claim_units(Ctrl* ctrl, uint64_t tot, uint32_t* s_base) {
+  const uint64_t ns = tot & 0xFFFFu, nm = (tot >> 16) & 0xFFFFu, nl = (tot >> 32) & 0xFFFFu, ni = tot >> 48;
+  const unsigned long long a = atomicAdd(&ctrl->unit_single, (unsigned long long)(ns | (ni << 32)));
+  const unsigned long long b = nm | nl ? atomicAdd(&ctrl->unit_multi, (unsigned long long)(nm | (nl << 32))) : 0ull;
+  s_base[0] = (uint32_t)a;
+  s_base[1] = (uint32_t)b;
+  s_base[2] = (uint32_t)(b >> 32);
+  s_base[3] = (uint32_t)(a >> 32);
+}
+
+// Where a thread's next unit of each class goes.
+struct UnitCursor {
+  uint32_t c[4];
+  __device__ __forceinline__ UnitCursor(uint64_t pre, const uint32_t* s_base) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = s_base[k] + ((uint32_t)(pre >> (16 * k)) & 0xFFFFu);
+  }
+};
+
+// Writes the unit of the key of item x with n items (the first at c[3]).
+__device__ __forceinline__ void emit_unit(const PutUnits& u, UnitCursor& at, uint64_t x, uint32_t n, bool single) {
+  if (single) {
+    u.single[at.c[0]++] = x;
+    return;
+  }
+  const uint4 e = make_uint4(item_tag(x), n | (item_fresh(x) ? kUnitFresh : 0u), at.c[3], 0u);
+  if (n > u.long_over) u.lng[at.c[2]++] = e;
+  else u.multi[at.c[1]++] = e;
+  at.c[3] += n;
+}
+
+// Groups the items it[0, mp) of a partition by key (see k_put_group) and
+// writes their units. it: the partition's items in the order put_probe's tiles
+// listed them: tiles ascending, and within a tile a key's items together in
+// ascending position; so the items of each key appear in position order (an
+// in-tile sum is one item at the first position it covers).
+__device__ __forceinline__ void group_by_key(unsigned char* lds, uint32_t mp, const PutUnits& u, Ctrl* ctrl) {
+  using L = GroupLds;
+  constexpr int NT = kGroupThreads;
+  constexpr int IPT = kRedCap / NT;
   constexpr int HPT = kRedHash / NT;
-  static_assert(kRedHash % NT == 0 && kRedCap < kRedHash && kRedHash <= 65536, "grouping table sizes");
+  static_assert(kRedCap % NT == 0 && HPT == 4 && kRedCap < kRedHash && kRedHash <= 65536, "grouping table sizes");
   constexpr uint32_t kNone = 0xFFFFFFFFu;
   constexpr uint32_t kMask = kRedHash - 1;
+  const uint64_t* it = reinterpret_cast<const uint64_t*>(lds + L::it);
+  uint32_t* hidx = reinterpret_cast<uint32_t*>(lds + L::hidx);
+  uint32_t* hcnt = reinterpret_cast<uint32_t*>(lds + L::hcnt);
+  uint16_t* slot = reinterpret_cast<uint16_t*>(lds + L::slot);
+  uint16_t* ord = reinterpret_cast<uint16_t*>(lds + L::ord);
+  uint8_t* lid = lds + L::lid;
+  uint32_t* mask = reinterpret_cast<uint32_t*>(lds + L::mask);
+  unsigned long long* s_tot = reinterpret_cast<unsigned long long*>(lds + L::misc);
+  uint32_t* s_base = reinterpret_cast<uint32_t*>(lds + L::misc + 16);
+  uint32_t* s_masks = s_base + 4;
   const int tid = threadIdx.x;
-  for (int h = tid; h < kRedHash; h += NT) {
-    hidx[h] = kNone;
-    hcnt[h] = 0u;
+  for (int h = tid; h < kRedHash / 4; h += NT) {
+    reinterpret_cast<uint4*>(hidx)[h] = make_uint4(kNone, kNone, kNone, kNone);
+    reinterpret_cast<uint4*>(hcnt)[h] = make_uint4(0u, 0u, 0u, 0u);
   }
-  for (int w = tid; w < kMaskSegs * kMaskWords; w += NT) mask[w] = 0u;
-  if (tid == 0) info[4] = 0u;  // masks handed out
+  for (int w = tid; w < kMaskUnits * kMaskWords; w += NT) mask[w] = 0u;
+  if (tid == 0) {
+    *s_tot = 0ull;
+    *s_masks = 0u;
+  }
   lds_barrier();
 
   // 1. one slot per key (the first item to take it), and its item count
@@ -1846,124 +1687,399 @@ __device__ __forceinline__ void group_by_key(const uint64_t* it, uint32_t mp, ui
   }
   lds_barrier();
 
-  // 2. the place of each key within its run of occupied slots (a run always
-  // ends: fewer items than slots)
-#pragma unroll
-  for (int q = 0; q < HPT; ++q) {
-    const uint32_t h = tid * HPT + q;
-    const uint32_t j = hidx[h];
-    if (j != kNone) {
-      const uint64_t key = item_group(it[j]);
-      uint32_t cs = h;
-      while (hidx[(cs - 1) & kMask] != kNone) cs = (cs - 1) & kMask;
-      uint32_t r = 0;
-      for (uint32_t c = cs; hidx[c] != kNone; c = (c + 1) & kMask) r += item_group(it[hidx[c]]) < key ? 1u : 0u;
-      inv[(cs + r) & kMask] = (uint16_t)h;
-    }
-  }
-  lds_barrier();
-
-  // 3. segment numbers and first items, places in order, segments that need
-  // a sum first (one scan of three counts of 21 bits each)
-  uint32_t cnt[HPT], hs[HPT];
-  bool need[HPT], occ[HPT];
+  // 2. the unit of each occupied slot, and where its items start
+  uint64_t x[HPT];
+  uint32_t n[HPT];
+  bool one[HPT];
   uint64_t mine = 0;
-  bool fresh = false;
+  {
+    const uint4 hi = reinterpret_cast<const uint4*>(hidx)[tid], hc = reinterpret_cast<const uint4*>(hcnt)[tid];
+    const uint32_t j[HPT] = {hi.x, hi.y, hi.z, hi.w};
+    const uint32_t c[HPT] = {hc.x, hc.y, hc.z, hc.w};
 #pragma unroll
-  for (int q = 0; q < HPT; ++q) {
-    const uint32_t pl = tid * HPT + q;
-    occ[q] = hidx[pl] != kNone;  // occupied places are the occupied slots
-    need[q] = false;
-    cnt[q] = 0;
-    hs[q] = 0;
-    if (occ[q]) {
-      hs[q] = inv[pl];
-      const uint64_t x = it[hidx[hs[q]]];
-      cnt[q] = hcnt[hs[q]];
-      need[q] = cnt[q] > 1 || item_summed(x);
-      fresh |= item_fresh(x);
-      mine += need[q] ? (1ull | ((uint64_t)cnt[q] << 21)) : (1ull << 42);
+    for (int q = 0; q < HPT; ++q) {
+      n[q] = j[q] != kNone ? c[q] : 0u;
+      x[q] = j[q] != kNone ? it[j[q]] : 0ull;
+      one[q] = n[q] == 1u && !item_summed(x[q]);
+      if (n[q] == 0u) continue;
+      mine += one[q] ? pack_unit(1, 0, 0, 0) : n[q] > u.long_over ? pack_unit(0, 0, 1, n[q]) : pack_unit(0, 1, 0, n[q]);
     }
   }
-  uint64_t tot;
-  const uint64_t pre = block_exclusive_scan_u64<NT>(mine, s_w64, &tot);  // barriers: every read above is done
-  constexpr uint64_t F = (1ull << 21) - 1;
-  const uint32_t SA = (uint32_t)(tot & F), MA = (uint32_t)((tot >> 21) & F), S = SA + (uint32_t)(tot >> 42);
-  uint32_t sa = (uint32_t)(pre & F), ia = (uint32_t)((pre >> 21) & F), sb = (uint32_t)(pre >> 42);
+  const uint64_t pre = claim_u64(mine, s_tot);
+  uint32_t off = (uint32_t)(pre >> 48);
 #pragma unroll
   for (int q = 0; q < HPT; ++q) {
-    if (occ[q]) {
-      uint32_t s, off;
-      if (need[q]) {
-        s = sa++;
-        off = ia;
-        ia += cnt[q];
-      } else {
-        s = SA + sb;
-        off = MA + sb;
-        ++sb;
+    const uint32_t h = (uint32_t)tid * HPT + q;
+    hidx[h] = 0u;  // fill cursor
+    if (n[q] == 0u) continue;
+    hcnt[h] = one[q] ? 0u : off | (n[q] << 16);
+    uint32_t l = 0xFFu;
+    if (!one[q]) {
+      off += n[q];
+      if (n[q] > kRankMask) {
+        l = atomicAdd(s_masks, 1u);  // which mask a unit gets does not matter
+        if (l >= (uint32_t)kMaskUnits) l = 0xFFu;
       }
-      seg[s] = off;
-      hcnt[hs[q]] = off | (s << 16);
-      hidx[hs[q]] = 0u;  // fill cursor
-      uint32_t l = 0xFFFFu;
-      if (cnt[q] > kLongSeg) {
-        l = atomicAdd(&info[4], 1u);  // which mask a long segment gets does not matter
-        if (l >= (uint32_t)kMaskSegs) l = 0xFFFFu;
-      }
-      lid[s] = (uint16_t)l;
     }
+    lid[h] = (uint8_t)l;
   }
-  if (tid == 0) {
-    seg[S] = mp;
-    info[0] = S;
-    info[1] = SA;
-    info[2] = MA;
-  }
-  const bool any_fresh = __syncthreads_or(fresh ? 1 : 0) != 0;
-  if (tid == 0) info[3] = any_fresh ? 1u : 0u;
+  lds_barrier();  // every wave has claimed its share of *s_tot
+  if (tid == 0) claim_units(ctrl, *s_tot, s_base);
 
-  // 4. drop each item into its segment (any order within it); a long
-  // segment also marks its items' places in its mask
-  uint32_t sg[IPT];
+  // 3. drop each item of a sum into its unit (any order within it); a long
+  // unit also marks its items' places in its mask
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
     const uint32_t j = tid + k * NT;
-    sg[k] = 0;
     if (j < mp) {
-      const uint32_t v = hcnt[slot[j]];
-      sg[k] = v >> 16;
-      ord[(v & 0xFFFFu) + atomicAdd(&hidx[slot[j]], 1u)] = (uint16_t)j;
-      const uint32_t l = lid[sg[k]];
-      if (l != 0xFFFFu) atomicOr(&mask[l * kMaskWords + (j >> 5)], 1u << (j & 31));
+      const uint32_t h = slot[j], v = hcnt[h];
+      if (v != 0u) {
+        ord[(v & 0xFFFFu) + atomicAdd(&hidx[h], 1u)] = (uint16_t)j;
+        const uint32_t l = lid[h];
+        if (l != 0xFFu) atomicOr(&mask[l * kMaskWords + (j >> 5)], 1u << (j & 31));
+      }
     }
   }
   lds_barrier();
-  // 5. each item at its rank within its segment: the number of the segment's
-  // items at earlier places (the items of a key come in position order)
+  // 4. units to the call's lists
+  UnitCursor at(pre, s_base);
+#pragma unroll
+  for (int q = 0; q < HPT; ++q)
+    if (n[q] != 0u) emit_unit(u, at, x[q], n[q], one[q]);
+  // 5. each item of a sum at its rank within its unit: the number of the
+  // unit's items at earlier places (the items of a key come in position order)
+  const uint32_t mbase = s_base[3];
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
     const uint32_t j = tid + k * NT;
     if (j < mp) {
-      const uint32_t b = seg[sg[k]], e = seg[sg[k] + 1];
+      const uint32_t h = slot[j], v = hcnt[h];
+      if (v == 0u) continue;
+      const uint32_t b = v & 0xFFFFu, c = v >> 16;
       uint32_t r = 0;
-      if (e - b > 1) {
-        const uint32_t l = lid[sg[k]];
-        if (l != 0xFFFFu) {
+      if (c > 1) {
+        const uint32_t l = lid[h];
+        if (l != 0xFFu) {
           const uint32_t* mw = mask + l * kMaskWords;
           const uint32_t wj = j >> 5;
           for (uint32_t w = 0; w < wj; ++w) r += __popc(mw[w]);
           r += __popc(mw[wj] & ((1u << (j & 31)) - 1u));
         } else {
-          for (uint32_t i = b; i < e; ++i) r += ord[i] < j ? 1u : 0u;
+          for (uint32_t i = b; i < b + c; ++i) r += ord[i] < j ? 1u : 0u;
         }
       }
-      srt[b + r] = it[j];
-      sid[b + r] = (uint16_t)sg[k];
+      u.mitem[mbase + b + r] = item_low31(it[j]);
+    }
+  }
+}
+
+// Writes the value rows of an upsert's keys s < S: at(s) is the item of key
+// s's last position (a fresh one is skipped). As the row copy of a get,
+// consecutive threads move consecutive units of the keys' rows. S * units of a
+// row < 2^20.
+constexpr int kValueUnits = 4;
+template <int NT, int VEC, bool kClk, class At>
+__device__ __forceinline__ void write_values(uint32_t S, const PutGroupArgs& a, const RowStore& store, At at) {
+  constexpr uint32_t U = kValueUnits;
+  using V = typename VecT<VEC>::T;
+  const int D = store.D;
+  const uint32_t Q = VEC == 4 ? (uint32_t)(D + 3) / 4u : (uint32_t)D;  // units of a row
+  const uint32_t total = S * Q;
+  for (uint32_t e0 = threadIdx.x; e0 < total; e0 += NT * U) {
+    V v[U];
+    uint32_t row[U], cl[U];
+    int col[U];
+    bool on[U];
+#pragma unroll
+    for (uint32_t k = 0; k < U; ++k) {
+      const uint32_t e = e0 + k * NT;
+      // e / Q by magic = ceil(2^32 / Q): exact, since e * (magic * Q - 2^32) < 2^20 * Q <= 2^28 (Q <= 256)
+      const uint32_t d = Q == 1 ? e : (uint32_t)(((uint64_t)e * a.magic) >> 32);
+      const int c = (int)(e - d * Q) * VEC;
+      col[k] = VEC == 1 || c < D - VEC ? c : D - VEC;  // the last unit of a row: its last four columns
+      const uint64_t x = e < total ? at(d) : 0ull;
+      on[k] = e < total && !item_fresh(x);
+      row[k] = item_tag(x);
+      cl[k] = 0;
+      if (on[k]) {
+        v[k] = load_vec<VEC>(a.values + (size_t)item_pos(x) * (size_t)D + col[k]);
+        if (kClk && c == 0) cl[k] = clock_low(a.clock, row[k]);
+      }
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < U; ++k) {
+      if (!on[k]) continue;
+      store_vec<VEC>(store.wptr(row[k]) + col[k], v[k]);
+      if (kClk) put_clock_low(a.clock, row[k], cl[k]);  // (cl is 0 for all but a row's first unit)
+    }
+  }
+}
+
+// An upsert of the items it[0, mp) of a partition: an LDS hash table from key
+// to its last position, then a row write per key.
+template <int VEC, bool kClk>
+__device__ __forceinline__ void upsert_last(unsigned char* lds, uint32_t mp, const PutGroupArgs& a,
+                                            const RowStore& store) {
+  using L = GroupLds;
+  constexpr int NT = kGroupThreads;
+  constexpr int IPT = kRedCap / NT;
+  constexpr int HPT = kRedHash / NT;
+  static_assert(kRedCap * 256 <= (1 << 20), "write_values");
+  constexpr uint32_t kNone = 0xFFFFFFFFu;
+  constexpr uint32_t kMask = kRedHash - 1;
+  uint64_t* it = reinterpret_cast<uint64_t*>(lds + L::it);
+  uint32_t* hidx = reinterpret_cast<uint32_t*>(lds + L::hidx);
+  uint32_t* hlast = reinterpret_cast<uint32_t*>(lds + L::hcnt);
+  unsigned long long* s_tot = reinterpret_cast<unsigned long long*>(lds + L::misc);
+  const int tid = threadIdx.x;
+  for (int h = tid; h < kRedHash / 4; h += NT) {
+    reinterpret_cast<uint4*>(hidx)[h] = make_uint4(kNone, kNone, kNone, kNone);
+    reinterpret_cast<uint4*>(hlast)[h] = make_uint4(0u, 0u, 0u, 0u);
+  }
+  if (tid == 0) *s_tot = 0ull;
+  lds_barrier();
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const uint32_t j = tid + k * NT;
+    if (j < mp) {
+      const uint64_t x = it[j];
+      const uint64_t gr = item_group(x);
+      uint32_t h = (uint32_t)index_hash(gr) & kMask;
+      while (true) {
+        const uint32_t old = atomicCAS(&hidx[h], kNone, j);
+        if (old == kNone || item_group(it[old]) == gr) break;
+        h = (h + 1) & kMask;
+      }
+      atomicMax(&hlast[h], item_pos(x) + 1u);
     }
   }
   lds_barrier();
+  // the items of the keys' last positions, at the front of it (in any order)
+  uint64_t x[HPT];
+  uint32_t n = 0;
+  {
+    const uint4 hi = reinterpret_cast<const uint4*>(hidx)[tid], hl = reinterpret_cast<const uint4*>(hlast)[tid];
+    const uint32_t j[HPT] = {hi.x, hi.y, hi.z, hi.w};
+    const uint32_t l[HPT] = {hl.x, hl.y, hl.z, hl.w};
+#pragma unroll
+    for (int q = 0; q < HPT; ++q)
+      if (j[q] != kNone) x[n++] = (it[j[q]] & ~0x7FFFFFFFull) | (uint64_t)(l[q] - 1u);
+  }
+  uint32_t to = (uint32_t)claim_u64(n, s_tot);
+  lds_barrier();  // every item has been read, every share claimed
+#pragma unroll
+  for (uint32_t q = 0; q < (uint32_t)HPT; ++q)
+    if (q < n) it[to + q] = x[q];
+  lds_barrier();
+  write_values<NT, VEC, kClk>((uint32_t)*s_tot, a, store, [&](uint32_t s) { return it[s]; });
 }
+
+// Run-length encodes items sorted by value: seg[s] = first item of segment s,
+// seg[S] = mp. Returns S (block-uniform).
+template <int NT, class IP, class SP>
+__device__ __forceinline__ uint32_t encode_segments(IP it, uint32_t mp, SP seg, uint32_t* s_w) {
+  uint32_t S = 0;
+  for (uint32_t b0 = 0; b0 < mp; b0 += NT) {
+    const uint32_t j = b0 + threadIdx.x;
+    const uint32_t head = (j < mp) && (j == 0 || item_group(it[j]) != item_group(it[j - 1])) ? 1u : 0u;
+    uint32_t tot;
+    const uint32_t pre = block_exclusive_scan<NT>(head, s_w, &tot);
+    if (head) seg[S + pre] = j;
+    S += tot;
+  }
+  if (threadIdx.x == 0) seg[S] = mp;
+  __syncthreads();
+  return S;
+}
+
+// The units of items sorted by key it[0, m), S segments starting at seg[s]
+// (seg[S] = m); a segment's items keep their order.
+template <int NT, class IP, class SP>
+__device__ __forceinline__ void units_of_sorted(IP it, SP seg, uint32_t S, const PutUnits& u, Ctrl* ctrl,
+                                                unsigned long long* s_tot, uint32_t* s_base) {
+  for (uint32_t s0 = 0; s0 < S; s0 += NT) {
+    const uint32_t s = s0 + threadIdx.x;
+    if (threadIdx.x == 0) *s_tot = 0ull;
+    __syncthreads();
+    uint32_t n = 0, b = 0;
+    uint64_t x = 0;
+    bool one = false;
+    if (s < S) {
+      b = seg[s];
+      n = seg[s + 1] - b;
+      x = it[b];
+      one = n == 1 && !item_summed(x);
+    }
+    // the packed counts hold 2^16 items: a unit of many claims its items by itself
+    constexpr uint32_t kBig = 64;
+    static_assert(kBig * NT <= (1 << 16), "packed item counts");
+    const bool big = !one && n >= kBig;
+    uint64_t mine = 0;
+    if (s < S)
+      mine = one ? pack_unit(1, 0, 0, 0)
+                 : n > u.long_over ? pack_unit(0, 0, 1, big ? 0u : n) : pack_unit(0, 1, 0, n);
+    const uint64_t pre = claim_u64(mine, s_tot);
+    __syncthreads();
+    if (threadIdx.x == 0) claim_units(ctrl, *s_tot, s_base);
+    __syncthreads();
+    if (s < S) {
+      UnitCursor at(pre, s_base);
+      if (big) at.c[3] = (uint32_t)(atomicAdd(&ctrl->unit_single, (unsigned long long)n << 32) >> 32);
+      const uint32_t to = at.c[3];
+      emit_unit(u, at, x, n, one);
+      if (!one)
+        for (uint32_t j = 0; j < n; ++j) u.mitem[to + j] = item_low31(it[b + j]);
+    }
+    __syncthreads();
+  }
+}
+
+// An upsert of items sorted by key, then position (see units_of_sorted).
+template <int NT, int VEC, bool kClk, class IP, class SP>
+__device__ __forceinline__ void upsert_sorted(IP it, SP seg, uint32_t S, const PutGroupArgs& a,
+                                              const RowStore& store) {
+  for (uint32_t s0 = 0; s0 < S; s0 += NT)
+    write_values<NT, VEC, kClk>(min((uint32_t)NT, S - s0), a, store,
+                                [&](uint32_t s) { return it[seg[s0 + s + 1] - 1]; });
+}
+
+// Partition larger than the block's LDS share: the same steps on a global
+// scratch area (bitonic sort in place).
+template <bool kUpsert, int VEC, bool kClk>
+__device__ __forceinline__ void group_partition_global(const PutGroupArgs& a, const RowStore& store, uint32_t p, uint32_t mp, uint32_t* s_w,
+                                                      uint64_t* s_misc) {
+  constexpr int NT = kGroupThreads;
+  uint32_t P2 = 1;
+  while (P2 < mp) P2 <<= 1;
+  if (threadIdx.x == 0) {
+    const uint64_t need = 2ull * P2 + 2;
+    const uint64_t b = atomicAdd(&a.ctrl->spill_next, (unsigned long long)need);
+    s_misc[0] = (b + need <= a.spill_words) ? b : ~0ull;
+  }
+  __syncthreads();
+  const uint64_t base = s_misc[0];
+  __syncthreads();
+  if (base == ~0ull) {  // cannot happen when the spill area holds 4n words
+    if (threadIdx.x == 0) atomicCAS(&a.ctrl->latched, 0, -4);
+    return;
+  }
+  uint64_t* it = a.spill + base;
+  uint32_t* seg = reinterpret_cast<uint32_t*>(a.spill + base + P2);
+  uint32_t dst = 0;
+  for (int t0 = 0; t0 < a.ntiles; t0 += NT) {
+    const int t = t0 + (int)threadIdx.x;
+    const uint32_t mt = t < a.ntiles ? a.meta[(size_t)p * a.ntiles + t] : 0u;
+    const uint32_t off = mt & 0xFFFFu, cnt = mt >> 16;
+    uint32_t tot;
+    const uint32_t pre = block_exclusive_scan<NT>(cnt, s_w, &tot);
+    for (uint32_t j = 0; j < cnt; ++j) it[dst + pre + j] = a.items[(size_t)t * kPutTile + off + j];
+    dst += tot;
+  }
+  for (uint32_t j = mp + threadIdx.x; j < P2; j += NT) it[j] = ~0ull;
+  __syncthreads();
+  block_bitonic_sort<NT>(it, P2);
+  const uint32_t S = encode_segments<NT>(it, mp, seg, s_w);
+  if constexpr (kUpsert) upsert_sorted<NT, VEC, kClk>(it, seg, S, a, store);
+  else units_of_sorted<NT>(it, seg, S, a.units, a.ctrl, reinterpret_cast<unsigned long long*>(s_misc),
+                           reinterpret_cast<uint32_t*>(s_misc + 2));
+}
+
+// The verdict of a put call (see call_verdict); a put whose probe ran ahead
+// of a get marks its errors in fields of its own.
+struct PutVerdict {
+  uint64_t size0, M;
+  int err;
+};
+template <int NT>
+__device__ __forceinline__ PutVerdict put_verdict(Ctrl* ctrl, uint64_t epoch, int64_t capacity,
+                                                  const uint32_t* tile_cnt, int ntiles, unsigned long long* s_w64) {
+  PutVerdict v;
+  v.size0 = ctrl->size[epoch & 1];
+  const uint64_t new_e = ctrl->new_epoch, ovf_e = ctrl->overflow_epoch;
+  const uint64_t bad_e = ctrl->apput_bad_epoch == epoch ? epoch : ctrl->bad_epoch;
+  const uint64_t abs_e = ctrl->apput_absent_epoch;
+  v.M = new_e == epoch ? count_new_keys<NT>(tile_cnt, ntiles, s_w64) : 0ull;
+  v.err = call_verdict(ctrl, epoch, v.size0, v.M, capacity, bad_e, ovf_e, abs_e);
+  return v;
+}
+
+template <bool kUpsert, int VEC, bool kClk>
+__global__ __launch_bounds__(kGroupThreads, 8) void k_put_group(const PutGroupArgs a, const AssignArgs aa,
+                                                                const RowStore store, uint64_t seed) {
+  using L = GroupLds;
+  constexpr int NT = kGroupThreads;
+  constexpr int IPT = kRedCap / NT;
+  extern __shared__ __align__(16) unsigned char s_raw[];
+  uint64_t* s_it = reinterpret_cast<uint64_t*>(s_raw + L::it);
+  uint32_t* s_pref = reinterpret_cast<uint32_t*>(s_raw + L::pref);
+  uint32_t* s_w = reinterpret_cast<uint32_t*>(s_raw + L::w);
+  unsigned long long* s_w64 = reinterpret_cast<unsigned long long*>(s_raw + L::w64);
+
+  const uint32_t p = blockIdx.x;
+  const int tid = threadIdx.x, ntiles = a.ntiles;
+  const uint32_t* pm = a.meta + (size_t)p * ntiles;
+  const bool one_chunk = ntiles <= NT;  // common case: one thread per tile
+  const uint32_t mt0 = one_chunk && tid < ntiles ? pm[tid] : 0u;
+
+  // entries of this partition in every tile
+  uint32_t mp, pre0 = 0;
+  if (one_chunk) {
+    pre0 = block_exclusive_scan<NT>(mt0 >> 16, s_w, &mp);
+  } else {
+    uint64_t mp64 = 0;
+    for (int t = tid; t < ntiles; t += NT) mp64 += pm[t] >> 16;
+    mp = (uint32_t)block_sum_u64<NT>(mp64, s_w64);
+  }
+  const PutVerdict v = put_verdict<NT>(a.ctrl, a.epoch, a.capacity, aa.tile_cnt, ntiles, s_w64);
+
+  if (!v.err && mp > (uint32_t)kRedCap) {
+    group_partition_global<kUpsert, VEC, kClk>(a, store, p, mp, s_w, reinterpret_cast<uint64_t*>(s_raw + L::misc));
+  } else if (!v.err && mp > 0) {
+    // ---- gather the partition's items into LDS, tile order ----
+    uint32_t dst = 0;
+    for (int t0 = 0; t0 < ntiles; t0 += NT) {
+      const int nt = min(NT, ntiles - t0);
+      uint32_t mt = mt0, pre = pre0, tot = mp;
+      if (!one_chunk) {
+        mt = tid < nt ? pm[t0 + tid] : 0u;
+        pre = block_exclusive_scan<NT>(mt >> 16, s_w, &tot);
+      }
+      s_pref[tid] = pre | (mt << 16);  // items before this tile | offset in the tile
+      __syncthreads();
+      uint64_t x[IPT];
+#pragma unroll
+      for (int e = 0; e < IPT; ++e) {
+        const uint32_t k = tid + e * NT;
+        x[e] = 0;
+        if (k < tot) {
+          int lo = 0, hi = nt - 1;
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if ((s_pref[mid] & 0xFFFFu) <= k) lo = mid;
+            else hi = mid - 1;
+          }
+          const uint32_t pe = s_pref[lo];
+          x[e] = a.items[(size_t)(t0 + lo) * kPutTile + (pe >> 16) + (k - (pe & 0xFFFFu))];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < IPT; ++e) {
+        const uint32_t k = tid + e * NT;
+        if (k < tot) s_it[dst + k] = x[e];
+      }
+      dst += tot;
+      __syncthreads();
+    }
+    if constexpr (kUpsert) upsert_last<VEC, kClk>(s_raw, mp, a, store);
+    else group_by_key(s_raw, mp, a.units, a.ctrl);
+  }
+  if (v.M != 0 && p < aa.blocks) {
+    __syncthreads();  // the grouping's LDS is free
+    assign_new<NT, kPutTile>(aa, store, seed, v.size0, v.M, v.err, *reinterpret_cast<AssignLds<NT>*>(s_raw));
+  }
+}
+
+#endif  // MLKV_MAP
 
 // One lane's VEC elements of a row, fp32 (a gradient row) or fp64 (an in-tile
 // sum), as loaded.
@@ -1978,7 +2094,7 @@ struct RawRow<1> {
   uint2 lo;
 };
 
-template <int VEC>
+template <int VEC, bool kStream>
 __device__ __forceinline__ void load_raw(RawRow<VEC>& r, const float* __restrict__ grads,
                                          const double* __restrict__ partials, size_t off, bool summed) {
   if constexpr (VEC == 4) {
@@ -1987,7 +2103,9 @@ __device__ __forceinline__ void load_raw(RawRow<VEC>& r, const float* __restrict
       r.lo = p[0];
       r.hi = p[1];
     } else {
-      r.lo = *reinterpret_cast<const Words4*>(grads + off);
+      const Words4* p = reinterpret_cast<const Words4*>(grads + off);
+      if constexpr (kStream) r.lo = __builtin_nontemporal_load(p);
+      else r.lo = *p;
     }
   } else {
     if (summed) r.lo = *reinterpret_cast<const uint2*>(partials + off);
@@ -2014,535 +2132,189 @@ __device__ __forceinline__ void add_raw(double* acc, const RawRow<VEC>& r, bool 
   }
 }
 
-// One update step (op of c) for the rows rw[u] with on[u], given their summed
-// gradients gq[u]: the rows (and accumulators) of the N keys are loaded
-// together, updated and written back; a bounded table's counts drop (kClk:
-// the table has staleness words).
-template <class M, int N, bool kClk>
-__device__ __forceinline__ void update_rows(const bool (&on)[N], const uint32_t (&rw)[N],
-                                            const typename VecT<M::VEC>::T (&gq)[N][M::K], const RedCtx& c, int q,
-                                            bool d_pow2, double inv_d) {
-  constexpr int VEC = M::VEC, K = M::K;
-  using V = typename VecT<VEC>::T;
-  const int D = c.D;
-  V w[N][K];
-  float G[N];
-  float* wr[N];
-  uint32_t cl[N];  // low words of the rows' staleness words (bounded tables)
-  const bool clk = kClk && q == 0;
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
-    G[u] = 0.0f;
-    wr[u] = nullptr;
-    cl[u] = 0u;
-    if (on[u]) {
-      wr[u] = c.store.wptr(rw[u]);
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int col = M::col(k, q, D);
-        if (M::on(k, q, D)) w[u][k] = load_vec<VEC>(wr[u] + col);
-      }
-      if (c.op == kOpAdagrad) G[u] = c.state[rw[u]];
-      if (clk) cl[u] = clock_low(c.clock, rw[u]);
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < N; ++u)
-    if (on[u]) {
-      SegmentOps<M>::update(c.op, gq[u], w[u], G[u], wr[u], c.state, rw[u], D, q, d_pow2, inv_d, c.lr, c.eps);
-      if (clk) put_clock_low(c.clock, rw[u], cl[u]);
-    }
-}
+// ---------------------------------------------------------------------------
+// Put, third kernel: the update of every unit (Adagrad or SGD). First the long
+// units, a block each: its lane groups take the unit's items in turn, and
+// their fp64 sums are added in a fixed order (across the wave's groups, then
+// across waves). Then the other sums, a lane group each, items in order; then
+// the keys seen once, kApplyRows of them a group at a time. Which block takes
+// which unit changes no result.
+// Bound by HBM: gradient rows and in-tile sums in, table rows in and out.
+// ---------------------------------------------------------------------------
+constexpr int kApplyThreads = 256;
+template <class M>
+struct ApplyCfg {
+  static constexpr int B = (M::K * M::VEC >= 8) ? 2 : 4;       // rows of a sum a group has in flight
+  static constexpr int BS = (M::K * M::VEC >= 8) ? 1 : 2;      // keys seen once it updates at a time
+  // gradient rows of 256 bytes and more are read around the caches; shorter
+  // ones share their lines with other keys' rows
+  static constexpr bool kStream = M::LPR * M::VEC >= 64;
+  static constexpr int WAVES = (M::K * M::VEC >= 16) ? 3 : (M::K * M::VEC >= 8) ? 4 : 5;  // per SIMD
+};
 
-// Sums and updates of a grouped partition (update op != kOpAssign).
-// Lane group gid takes an even share [lo, hi) of the items of segments that
-// need a sum and walks it B items at a time (their gradient rows, and the row
-// and accumulator of each segment starting among them, loaded together),
-// accumulating in fp64; a segment that starts and ends in the share is updated
-// as soon as it ends. The part of a segment begun in an earlier share goes to
-// LDS (a group has at most one); after a barrier, the group where a segment
-// cut between shares began adds the later parts in share order and updates
-// it. Each group also updates an even share of the keys seen once (g is their
-// gradient row).
-template <class M, int NT, bool kClk>
-__device__ __forceinline__ void sum_and_update(const uint64_t* srt, const uint32_t* seg, const uint16_t* sid,
-                                               uint32_t S, uint32_t SA, uint32_t MA, const RedCtx& c,
-                                               double* s_piece, uint32_t* s_slo) {
+template <class M, bool kClk>
+__global__ __launch_bounds__(kApplyThreads, ApplyCfg<M>::WAVES) void k_put_apply(const PutApplyArgs a,
+                                                                                const RowStore store) {
   using Ops = SegmentOps<M>;
-  using Cfg = ReduceCfg<M>;
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K;
-  constexpr int NG = Cfg::NG, B = Cfg::B, BS = Cfg::BS, DMAX = Cfg::DMAX;
-  static_assert(NG <= kMaxGroups, "lane groups");
+  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, RPW = M::RPW;
+  constexpr int NW = kApplyThreads / 64, NG = NW * RPW;
+  constexpr int B = ApplyCfg<M>::B, BS = ApplyCfg<M>::BS, DMAX = LPR * K * VEC;
+  constexpr bool kStream = ApplyCfg<M>::kStream;
   using V = typename VecT<VEC>::T;
-  const int lane = threadIdx.x & 63;
+  __shared__ double s_sum[NW][DMAX];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int q = lane % LPR;
-  const int gid = (threadIdx.x >> 6) * M::RPW + lane / LPR;
-  const int D = c.D;
+  const int gid = wave * RPW + lane / LPR;
+  const int D = store.D;
   const bool d_pow2 = (D & (D - 1)) == 0;
   const double inv_d = 1.0 / (double)D;
+  const bool adagrad = a.op == kOpAdagrad;
+  const bool clk = kClk && q == 0;
 
-  for (int h = threadIdx.x; h <= NG; h += NT) s_slo[h] = (uint32_t)((uint64_t)MA * h / NG);
-  lds_barrier();
-  const uint32_t lo = s_slo[gid], hi = s_slo[gid + 1];
-
-  auto put_piece = [&](const double (&a)[K][VEC]) {
-    double* dst = s_piece + (size_t)gid * DMAX;
+  // the row of a unit, loaded ahead of its update
+  V w[K];
+  float G = 0.0f;
+  uint32_t cl = 0u;
+  auto load_row = [&](uint32_t row, const float* wr) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int col = M::col(k, q, D);
-#pragma unroll
-      for (int x = 0; x < VEC; ++x)
-        if (M::on(k, q, D)) dst[col + x] = a[k][x];
-    }
+    for (int k = 0; k < K; ++k)
+      if (M::on(k, q, D)) w[k] = load_vec<VEC>(wr + M::col(k, q, D));
+    if (adagrad) G = a.state[row];
+    if (clk) cl = clock_low(a.clock, row);
   };
-  auto to_f32 = [&](V (&g)[K], const double (&a)[K][VEC]) {
+  auto update = [&](const double (&acc)[K][VEC], uint32_t row, float* wr) {
+    V g[K];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-      for (int x = 0; x < VEC; ++x) VecT<VEC>::set(g[k], x, (float)a[k][x]);
+      for (int x = 0; x < VEC; ++x) VecT<VEC>::set(g[k], x, (float)acc[k][x]);
+    if (adagrad) Ops::adagrad(g, w, G, wr, a.state, row, D, q, d_pow2, inv_d, a.lr, a.eps);
+    else Ops::sgd(g, w, wr, D, q, a.lr);
+    if (clk) put_clock_low(a.clock, row, cl);
   };
-  // ---- segments that need a sum ----
-  // The row and accumulator of a segment this group owns are loaded with the
-  // batch that holds its first item; at most one segment is open at a time.
+  // adds items [j, end) by steps of `step` to acc, B of them in flight
   double acc[K][VEC];
-  Ops::zero(acc);
-  V wc[K];
-  float Gc = 0.0f;
-  uint32_t Cc = 0u;  // low word of the open segment's staleness word (bounded tables)
-  const bool clk = kClk && q == 0;
-  uint32_t rowc = 0;
-  float* wrc = nullptr;
-  bool last_ends = true, last_owned = true;
-  uint32_t last_end = 0;
-  for (uint32_t j0 = lo; j0 < hi; j0 += B) {
-    uint64_t x[B];
-    uint32_t fst[B], end[B];
-    RawRow<VEC> raw[B][K];
-    V wl[B][K];
-    float Gl[B];
-    uint32_t Cl[B];
-    float* wp[B];
+  auto add_items = [&](const uint32_t* __restrict__ items, uint32_t j, uint32_t end, uint32_t step) {
+    for (; j < end; j += B * step) {
+      RawRow<VEC> raw[B][K];
+      uint32_t x[B];
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const uint32_t j = j0 + u;
-      x[u] = 0;
-      fst[u] = 0;
-      end[u] = 0;
-      Gl[u] = 0.0f;
-      Cl[u] = 0u;
-      wp[u] = nullptr;
-      if (j < hi) {
-        x[u] = srt[j];
-        const uint32_t s = sid[j];
-        fst[u] = seg[s];
-        end[u] = seg[s + 1];
-        const bool summ = item_summed(x[u]);
-        const size_t base = (size_t)item_pos(x[u]) * (size_t)D;
+      for (int u = 0; u < B; ++u) x[u] = j + u * step < end ? items[j + u * step] : 0u;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int col = M::col(k, q, D);
-          if (M::on(k, q, D)) load_raw<VEC>(raw[u][k], c.grads, c.partials, base + col, summ);
+      for (int u = 0; u < B; ++u) {
+        if (j + u * step < end) {
+          const size_t base = (size_t)(x[u] & 0x3FFFFFFFu) * (size_t)D;
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+            if (M::on(k, q, D))
+              load_raw<VEC, kStream>(raw[u][k], a.grads, a.partials, base + M::col(k, q, D), (x[u] & (uint32_t)kItemSummed) != 0);
         }
-        if (fst[u] == j && j >= lo) {  // an owned segment starts: its row (the first item carries it)
-          const uint32_t r = item_tag(x[u]);
-          wp[u] = c.store.wptr(r);
+      }
 #pragma unroll
-          for (int k = 0; k < K; ++k) {
-            const int col = M::col(k, q, D);
-            if (M::on(k, q, D)) wl[u][k] = load_vec<VEC>(wp[u] + col);
-          }
-          if (c.op == kOpAdagrad) Gl[u] = c.state[r];
-          if (clk) Cl[u] = clock_low(c.clock, r);
+      for (int u = 0; u < B; ++u) {
+        if (j + u * step < end) {
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+            if (M::on(k, q, D)) add_raw<VEC>(acc[k], raw[u][k], (x[u] & (uint32_t)kItemSummed) != 0);
         }
       }
     }
+  };
+  auto zero = [&]() {
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const uint32_t j = j0 + u;
-      if (j < hi) {
-        if (fst[u] == j) {  // (j >= lo here)
-          rowc = item_tag(x[u]);
-          wrc = wp[u];
+    for (int k = 0; k < K; ++k)
 #pragma unroll
-          for (int k = 0; k < K; ++k) wc[k] = wl[u][k];
-          Gc = Gl[u];
-          Cc = Cl[u];
-        }
-        const bool summ = item_summed(x[u]);
+      for (int x = 0; x < VEC; ++x) acc[k][x] = 0.0;
+  };
+
+  // ---- long units ----
+  const uint32_t nl = (uint32_t)(a.ctrl->unit_multi >> 32);
+  for (uint32_t e = blockIdx.x; e < nl; e += gridDim.x) {
+    const uint4 t = a.units.lng[e];
+    const uint32_t n = t.y & ~kUnitFresh;
+    uint32_t row = 0;
+    float* wr = nullptr;
+    if (gid == 0) {
+      row = unit_row(a.idx, t.x, (t.y & kUnitFresh) != 0);
+      wr = store.wptr(row);
+      load_row(row, wr);
+    }
+    zero();
+    add_items(a.units.mitem + t.z, gid, n, NG);
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          if (M::on(k, q, D)) add_raw<VEC>(acc[k], raw[u][k], summ);
-        }
-        last_ends = end[u] == j + 1;
-        last_owned = fst[u] >= lo;
-        last_end = end[u];
-        if (last_ends) {
-          if (last_owned) {
-            V g[K];
-            to_f32(g, acc);
-            Ops::update(c.op, g, wc, Gc, wrc, c.state, rowc, D, q, d_pow2, inv_d, c.lr, c.eps);
-            if (clk) put_clock_low(c.clock, rowc, Cc);
-          } else {
-            put_piece(acc);  // the end of a segment begun in an earlier share
-          }
-          Ops::zero(acc);
-        }
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) {
+#pragma unroll
+        for (int o = LPR; o < 64; o <<= 1) acc[k][x] += __shfl_xor(acc[k][x], o, 64);
+        if (lane < LPR) s_sum[wave][(k * LPR + q) * VEC + x] = acc[k][x];
       }
     }
+    __syncthreads();
+    if (gid == 0) {
+#pragma unroll
+      for (int o = 1; o < NW; ++o)
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) acc[k][x] += s_sum[o][(k * LPR + q) * VEC + x];
+      update(acc, row, wr);
+    }
+    __syncthreads();
   }
-  const bool tail = lo < hi && !last_ends && last_owned;
-  if (lo < hi && !last_ends && !last_owned) put_piece(acc);  // the share lies inside one segment
+
+  // ---- other sums ----
+  const uint32_t groups = gridDim.x * NG, g0 = blockIdx.x * NG + gid;
+  const uint32_t nm = (uint32_t)a.ctrl->unit_multi;
+  for (uint32_t e = g0; e < nm; e += groups) {
+    const uint4 t = a.units.multi[e];
+    const uint32_t row = unit_row(a.idx, t.x, (t.y & kUnitFresh) != 0);
+    float* wr = store.wptr(row);
+    load_row(row, wr);
+    zero();
+    add_items(a.units.mitem + t.z, 0, t.y & ~kUnitFresh, 1);
+    update(acc, row, wr);
+  }
 
   // ---- keys seen once: g is the key's gradient row ----
-  {
-    const uint32_t S1 = S - SA;
-    const uint32_t k0 = SA + (uint32_t)((uint64_t)S1 * gid / NG), k1 = SA + (uint32_t)((uint64_t)S1 * (gid + 1) / NG);
-    for (uint32_t s0 = k0; s0 < k1; s0 += BS) {
-      bool on[BS];
-      uint32_t rw[BS];
-      V gq[BS][K];
-#pragma unroll
-      for (int u = 0; u < BS; ++u) {
-        const uint32_t s = s0 + u;
-        on[u] = s < k1;
-        rw[u] = 0;
-        if (on[u]) {
-          const uint64_t xs = srt[MA + (s - SA)];
-          rw[u] = item_tag(xs);
-          const float* gr = c.grads + (size_t)item_pos(xs) * (size_t)D;
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-            const int col = M::col(k, q, D);
-            if (M::on(k, q, D)) gq[u][k] = load_vec<VEC>(gr + col);
-          }
-        }
-      }
-      update_rows<M, BS, kClk>(on, rw, gq, c, q, d_pow2, inv_d);
-    }
-  }
-
-  __syncthreads();  // the pieces of cut segments are in LDS
-  if (tail) {
-    // the segment ends in share hl: add the pieces of shares gid+1 .. hl in
-    // order (an empty share holds none)
-    uint32_t hl = gid + 1;
-    while (hl + 1 < (uint32_t)NG && s_slo[hl + 1] < last_end) ++hl;
-    for (uint32_t h = gid + 1; h <= hl; ++h) {
-      if (s_slo[h] >= s_slo[h + 1]) continue;
-      const double* src = s_piece + (size_t)h * DMAX;
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const int col = M::col(k, q, D);
-#pragma unroll
-        for (int xx = 0; xx < VEC; ++xx)
-          if (M::on(k, q, D)) acc[k][xx] += src[col + xx];
-      }
-    }
-    V g[K];
-    to_f32(g, acc);  // the row, accumulator and staleness word came with the segment's first item
-    Ops::update(c.op, g, wc, Gc, wrc, c.state, rowc, D, q, d_pow2, inv_d, c.lr, c.eps);
-    if (clk) put_clock_low(c.clock, rowc, Cc);
-  }
-}
-
-// Put with the assignment op: each key's row becomes the value row at its
-// last position. Lane groups take even shares of the segments.
-// An upsert whose keys were all present before the call: each key's row
-// takes the value at the key's last position, so the partition needs no
-// grouping, only the largest position per row (an LDS hash table from row to
-// position + 1), then one write per row, lane groups taking equal shares of
-// the rows in slot order.
-constexpr uint32_t kNoRowKey = 0xFFFFFFFFu;  // an empty slot (no row has this id)
-template <class M, int NT, bool kClk>
-__device__ __forceinline__ void upsert_last(const uint64_t* __restrict__ it, uint32_t mp, const RedCtx& c,
-                                            uint32_t* s_row, uint32_t* s_last, uint16_t* s_list, uint32_t* s_w) {
-  static_assert(kRedHash == 4096 && kRedHash % NT == 0, "12-bit slot hash, whole slots per thread");
-  for (uint32_t h = threadIdx.x; h < (uint32_t)kRedHash; h += NT) {
-    s_row[h] = kNoRowKey;
-    s_last[h] = 0u;
-  }
-  __syncthreads();
-  for (uint32_t j = threadIdx.x; j < mp; j += NT) {
-    const uint64_t x = it[j];
-    const uint32_t row = item_tag(x);
-    uint32_t h = (row * 0x9E3779B1u) >> 20;
-    while (true) {
-      const uint32_t old = atomicCAS(&s_row[h], kNoRowKey, row);
-      if (old == kNoRowKey || old == row) break;
-      h = (h + 1) & (kRedHash - 1);
-    }
-    atomicMax(&s_last[h], item_pos(x) + 1u);
-  }
-  __syncthreads();
-  constexpr int PER = kRedHash / NT;
-  uint32_t occ = 0;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) occ += s_row[threadIdx.x * PER + e] != kNoRowKey ? 1u : 0u;
-  uint32_t S;
-  uint32_t at = block_exclusive_scan<NT>(occ, s_w, &S);
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    const uint32_t h = threadIdx.x * PER + e;
-    if (s_row[h] != kNoRowKey) s_list[at++] = (uint16_t)h;
-  }
-  __syncthreads();
-  using Cfg = ReduceCfg<M>;
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, NG = Cfg::NG, BS = Cfg::BS;
-  using V = typename VecT<VEC>::T;
-  const int lane = threadIdx.x & 63;
-  const int q = lane % LPR;
-  const int gid = (threadIdx.x >> 6) * M::RPW + lane / LPR;
-  const int D = c.D;
-  const uint32_t k0 = (uint32_t)((uint64_t)S * gid / NG), k1 = (uint32_t)((uint64_t)S * (gid + 1) / NG);
-  for (uint32_t s0 = k0; s0 < k1; s0 += BS) {
-    V v[BS][K];
-    uint32_t rw[BS], cl[BS];
-    const bool clk = kClk && q == 0;
+  const uint32_t ns = (uint32_t)a.ctrl->unit_single;
+  for (uint32_t e0 = g0; e0 < ns; e0 += groups * BS) {
+    V gq[BS][K], ws[BS][K];
+    float Gs[BS];
+    uint32_t rw[BS], cs[BS];
+    float* wr[BS];
 #pragma unroll
     for (int u = 0; u < BS; ++u) {
-      const uint32_t sl = s0 + u;
+      const uint32_t e = e0 + u * groups;
       rw[u] = 0;
-      cl[u] = 0u;
-      if (sl < k1) {
-        const uint32_t h = s_list[sl];
-        rw[u] = s_row[h];
-        const float* src = c.grads + (size_t)(s_last[h] - 1u) * (size_t)D;
+      Gs[u] = 0.0f;
+      cs[u] = 0u;
+      wr[u] = nullptr;
+      if (e < ns) {
+        const uint64_t x = a.units.single[e];
+        rw[u] = unit_row(a.idx, item_tag(x), item_fresh(x));
+        wr[u] = store.wptr(rw[u]);
+        const float* gr = a.grads + (size_t)item_pos(x) * (size_t)D;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
           const int col = M::col(k, q, D);
-          if (M::on(k, q, D)) v[u][k] = load_vec<VEC>(src + col);
-        }
-        if (clk) cl[u] = clock_low(c.clock, rw[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < BS; ++u) {
-      if (s0 + u >= k1) continue;
-      SegmentOps<M>::assign(v[u], c.store.wptr(rw[u]), D, q);
-      if (clk) put_clock_low(c.clock, rw[u], cl[u]);
-    }
-  }
-}
-
-template <class M, int NT, bool kClk>
-__device__ __forceinline__ void assign_segments(const uint64_t* srt, const uint32_t* seg, uint32_t S,
-                                                const RedCtx& c) {
-  using Cfg = ReduceCfg<M>;
-  constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, NG = Cfg::NG, BS = Cfg::BS;
-  using V = typename VecT<VEC>::T;
-  const int lane = threadIdx.x & 63;
-  const int q = lane % LPR;
-  const int gid = (threadIdx.x >> 6) * M::RPW + lane / LPR;
-  const int D = c.D;
-  const uint32_t k0 = (uint32_t)((uint64_t)S * gid / NG), k1 = (uint32_t)((uint64_t)S * (gid + 1) / NG);
-  for (uint32_t s0 = k0; s0 < k1; s0 += BS) {
-    V v[BS][K];
-    uint32_t rw[BS], cl[BS];
-    const bool clk = kClk && q == 0;
-#pragma unroll
-    for (int u = 0; u < BS; ++u) {
-      const uint32_t s = s0 + u;
-      rw[u] = 0;
-      cl[u] = 0u;
-      if (s < k1) {
-        rw[u] = item_tag(srt[seg[s]]);
-        const float* src = c.grads + (size_t)item_pos(srt[seg[s + 1] - 1]) * (size_t)D;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int col = M::col(k, q, D);
-          if (M::on(k, q, D)) v[u][k] = load_vec<VEC>(src + col);
-        }
-        if (clk) cl[u] = clock_low(c.clock, rw[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < BS; ++u) {
-      if (s0 + u >= k1) continue;
-      SegmentOps<M>::assign(v[u], c.store.wptr(rw[u]), D, q);
-      if (clk) put_clock_low(c.clock, rw[u], cl[u]);
-    }
-  }
-}
-
-// Partition larger than the block's LDS share: the same steps on a global
-// scratch area (bitonic sort in place).
-template <class M, int NT>
-__device__ __forceinline__ void reduce_partition_global(uint32_t p, uint32_t mp, const uint64_t* __restrict__ items,
-                                                     const uint32_t* __restrict__ meta, int ntiles,
-                                                     const RedCtx& c, const NewKey* __restrict__ newlist,
-                                                     const uint32_t* __restrict__ tile_cnt, Ctrl* ctrl,
-                                                     uint64_t* __restrict__ spill, uint64_t spill_words,
-                                                     double* s_part, uint32_t* s_pref, uint32_t* s_w,
-                                                     unsigned long long* s_w64, uint64_t* s_base) {
-  uint32_t P2 = 1;
-  while (P2 < mp) P2 <<= 1;
-  if (threadIdx.x == 0) {
-    const uint64_t need = 2ull * P2 + 2;
-    const uint64_t b = atomicAdd(&ctrl->spill_next, (unsigned long long)need);
-    *s_base = (b + need <= spill_words) ? b : ~0ull;
-  }
-  __syncthreads();
-  const uint64_t base = *s_base;
-  if (base == ~0ull) {  // cannot happen when the spill area holds 4n words
-    if (threadIdx.x == 0) atomicCAS(&ctrl->latched, 0, -4);
-    return;
-  }
-  uint64_t* it = spill + base;
-  uint32_t* seg = reinterpret_cast<uint32_t*>(spill + base + P2);
-  uint32_t* sid = seg + P2 + 1;
-  uint32_t dst = 0;
-  for (int t0 = 0; t0 < ntiles; t0 += NT) {
-    const int t = t0 + (int)threadIdx.x;
-    const uint32_t mt = t < ntiles ? meta[(size_t)p * ntiles + t] : 0u;
-    const uint32_t off = mt & 0xFFFFu, cnt = mt >> 16;
-    uint32_t tot;
-    const uint32_t pre = block_exclusive_scan<NT>(cnt, s_w, &tot);
-    for (uint32_t j = 0; j < cnt; ++j) it[dst + pre + j] = items[(size_t)t * kPutTile + off + j];
-    dst += tot;
-  }
-  for (uint32_t j = mp + threadIdx.x; j < P2; j += NT) it[j] = ~0ull;
-  __syncthreads();
-  block_bitonic_sort<NT>(it, P2);
-  const uint32_t S = encode_segments<NT>(it, mp, seg, sid, s_w);
-  resolve_new_rows<NT>(it, seg, S, c, newlist, tile_cnt, ntiles, s_pref, s_w, s_w64,
-                       reinterpret_cast<uint64_t*>(s_part));
-  if (c.op != kOpAssign) sum_segments<M, NT>(it, seg, sid, mp, c, s_part);
-  update_segments<M, NT>(it, seg, S, c);
-}
-
-// kUpsert: the instance for upserts (PutOp kOpAssign), whose partitions
-// without keys new in the call take the value at each key's last position
-// without grouping (upsert_last).
-template <class M, int NT, bool kClk, bool kUpsert>
-__global__ __launch_bounds__(NT) void k_put_reduce(
-    Bucket* __restrict__ idx, const uint64_t* __restrict__ items, const uint32_t* __restrict__ meta,
-    int ntiles, const NewKey* __restrict__ newlist, const uint32_t* __restrict__ tile_cnt,
-    const float* __restrict__ grads, double* __restrict__ partials, const RowStore store,
-    float* __restrict__ state, int D, uint64_t seed, float lr, float eps, int64_t capacity, Ctrl* ctrl,
-    uint64_t epoch, uint64_t* __restrict__ spill, uint64_t spill_words, int op,
-    unsigned long long* __restrict__ clock) {
-  using L = ReduceLds<NT>;
-  constexpr int IPT = (kRedCap + NT - 1) / NT;
-  extern __shared__ __align__(16) unsigned char s_raw[];
-  uint64_t* s_it = reinterpret_cast<uint64_t*>(s_raw + L::it);
-  uint32_t* s_hidx = reinterpret_cast<uint32_t*>(s_raw + L::hidx);
-  uint32_t* s_hcnt = reinterpret_cast<uint32_t*>(s_raw + L::hcnt);
-  uint16_t* s_inv = reinterpret_cast<uint16_t*>(s_raw + L::inv);
-  uint16_t* s_slot = reinterpret_cast<uint16_t*>(s_raw + L::slot);
-  uint16_t* s_ord = reinterpret_cast<uint16_t*>(s_raw + L::ord);
-  double* s_piece = reinterpret_cast<double*>(s_raw);       // reused region
-  uint64_t* s_chunk = reinterpret_cast<uint64_t*>(s_raw);   // reused region
-  uint64_t* s_srt = reinterpret_cast<uint64_t*>(s_raw + L::srt);
-  uint32_t* s_seg = reinterpret_cast<uint32_t*>(s_raw + L::seg);
-  uint16_t* s_sid = reinterpret_cast<uint16_t*>(s_raw + L::sid);
-  uint16_t* s_lid = reinterpret_cast<uint16_t*>(s_raw + L::lid);
-  uint32_t* s_mask = reinterpret_cast<uint32_t*>(s_raw + L::mask);
-  uint32_t* s_pref = reinterpret_cast<uint32_t*>(s_raw + L::pref);
-  uint32_t* s_w = reinterpret_cast<uint32_t*>(s_raw + L::w);
-  unsigned long long* s_w64 = reinterpret_cast<unsigned long long*>(s_raw + L::w64);
-  uint32_t* s_info = reinterpret_cast<uint32_t*>(s_raw + L::misc);
-  uint64_t* s_base = reinterpret_cast<uint64_t*>(s_raw + L::base);
-  uint32_t* s_slo = reinterpret_cast<uint32_t*>(s_raw + L::slo);
-
-  const uint32_t p = blockIdx.x;
-  const int tid = threadIdx.x;
-  const uint64_t size0 = ctrl->size[epoch & 1];
-  const uint64_t new_e = ctrl->new_epoch, ovf_e = ctrl->overflow_epoch;
-  const uint64_t bad_e = ctrl->apput_bad_epoch == epoch ? epoch : ctrl->bad_epoch;
-  const uint64_t abs_e = ctrl->apput_absent_epoch;
-  const uint32_t* pm = meta + (size_t)p * ntiles;
-  const bool one_chunk = ntiles <= NT;  // common case: one thread per tile
-  const uint32_t mt0 = one_chunk && tid < ntiles ? pm[tid] : 0u;
-
-  // entries of this partition in every tile
-  uint32_t mp, pre0 = 0;
-  if (one_chunk) {
-    pre0 = block_exclusive_scan<NT>(mt0 >> 16, s_w, &mp);
-  } else {
-    uint64_t mp64 = 0;
-    for (int t = tid; t < ntiles; t += NT) mp64 += pm[t] >> 16;
-    mp = (uint32_t)block_sum_u64<NT>(mp64, s_w64);
-  }
-
-  const uint64_t Mnew = new_e == epoch ? count_new_keys<NT>(tile_cnt, ntiles, s_w64) : 0ull;
-  const int err = call_verdict(ctrl, epoch, size0, Mnew, capacity, bad_e, ovf_e, abs_e);
-  if (mp == 0) return;
-  if (err) {
-    if (Mnew == 0) return;
-    // undo the insertions of this call whose slots fall in this partition
-    for (int t = tid; t < ntiles; t += NT) {
-      const uint32_t mt = pm[t];
-      const uint32_t off = mt & 0xFFFFu, cnt = mt >> 16;
-      for (uint32_t j = 0; j < cnt; ++j) {
-        const uint64_t x = items[(size_t)t * kPutTile + off + j];
-        if (item_fresh(x)) {
-          const uint32_t slot = item_tag(x);
-          idx[slot / kSlots].key[slot % kSlots] = kEmptyKey;
-        }
-      }
-    }
-    return;
-  }
-
-  const RedCtx c{op, idx, grads, partials, store, state, D, seed, lr, eps, size0, clock};
-  if (mp > (uint32_t)kRedCap) {
-    reduce_partition_global<M, NT>(p, mp, items, meta, ntiles, c, newlist, tile_cnt, ctrl, spill, spill_words,
-                                   s_piece, s_pref, s_w, s_w64, s_base);
-    return;
-  }
-
-  // ---- gather the partition's items into LDS, tile order ----
-  {
-    uint32_t dst = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += NT) {
-      const int nt = min(NT, ntiles - t0);
-      uint32_t mt = mt0, pre = pre0, tot = mp;
-      if (!one_chunk) {
-        mt = tid < nt ? pm[t0 + tid] : 0u;
-        pre = block_exclusive_scan<NT>(mt >> 16, s_w, &tot);
-      }
-      s_pref[tid] = pre | (mt << 16);  // items before this tile | offset in the tile
-      __syncthreads();
-      uint64_t v[IPT];
-#pragma unroll
-      for (int e = 0; e < IPT; ++e) {
-        const uint32_t k = tid + e * NT;
-        v[e] = 0;
-        if (k < tot) {
-          int lo = 0, hi = nt - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if ((s_pref[mid] & 0xFFFFu) <= k) lo = mid;
-            else hi = mid - 1;
+          if (M::on(k, q, D)) {
+            gq[u][k] = load_vec_once<VEC, kStream>(gr + col);
+            ws[u][k] = load_vec<VEC>(wr[u] + col);
           }
-          const uint32_t pe = s_pref[lo];
-          v[e] = items[(size_t)(t0 + lo) * kPutTile + (pe >> 16) + (k - (pe & 0xFFFFu))];
         }
+        if (adagrad) Gs[u] = a.state[rw[u]];
+        if (clk) cs[u] = clock_low(a.clock, rw[u]);
       }
+    }
 #pragma unroll
-      for (int e = 0; e < IPT; ++e) {
-        const uint32_t k = tid + e * NT;
-        if (k < tot) s_it[dst + k] = v[e];
-      }
-      dst += tot;
-      __syncthreads();
+    for (int u = 0; u < BS; ++u) {
+      if (wr[u] == nullptr) continue;
+      if (adagrad) Ops::adagrad(gq[u], ws[u], Gs[u], wr[u], a.state, rw[u], D, q, d_pow2, inv_d, a.lr, a.eps);
+      else Ops::sgd(gq[u], ws[u], wr[u], D, q, a.lr);
+      if (clk) put_clock_low(a.clock, rw[u], cs[u]);
     }
   }
-
-  if constexpr (kUpsert) {
-    uint32_t fresh = 0;
-    for (uint32_t j = tid; j < mp; j += NT) fresh |= item_fresh(s_it[j]) ? 1u : 0u;
-    if (__syncthreads_or((int)fresh) == 0) {
-      upsert_last<M, NT, kClk>(s_it, mp, c, s_hidx, s_hcnt, s_slot, s_w);
-      return;
-    }
-  }
-  group_by_key<NT>(s_it, mp, s_srt, s_seg, s_sid, s_hidx, s_hcnt, s_inv, s_slot, s_ord, s_lid, s_mask, s_w64, s_info);
-  const uint32_t S = s_info[0], SA = s_info[1], MA = s_info[2];
-  if (s_info[3] != 0u)
-    resolve_new_rows<NT>(s_srt, s_seg, S, c, newlist, tile_cnt, ntiles, s_pref, s_w, s_w64, s_chunk);
-  if (op == kOpAssign) assign_segments<M, NT, kClk>(s_srt, s_seg, S, c);
-  else sum_and_update<M, NT, kClk>(s_srt, s_seg, s_sid, S, SA, MA, c, s_piece, s_slo);
 }
 
 // ===========================================================================
@@ -2553,10 +2325,9 @@ __global__ __launch_bounds__(NT) void k_put_reduce(
 // capacity + index slot), in passes of at most kRsMaxBits bits, each a count
 // kernel and a scatter kernel; then blocks that take even shares of the
 // sorted items, each cut moved forward to the start of a key's run,
-// run-length encode them in LDS and apply the updates as put_reduce does.
+// run-length encode them in LDS and write the units that put_group writes.
 // Stability keeps a key's items in put-tile order, which is position order.
 // ===========================================================================
-static_assert(kPresumMin == 2, "radix dedup: one item per key and put tile");
 static_assert(kRsTile == 4 * kPutTile, "a radix tile is four put tiles");
 constexpr int kRsThreads = 1024;
 constexpr int kRsPer = kRsTile / kRsThreads;
@@ -2697,155 +2468,43 @@ __device__ __forceinline__ uint32_t rs_cut(const uint64_t* __restrict__ it, uint
   return T;
 }
 
-// Run-length encoding of m sorted items it[0, m) (whole runs of equal keys)
-// into group_by_key's output: srt, seg, sid, info = {S, SA, MA, any key new
-// in the call}; segments that need a sum first (more than one item, or an
-// in-tile sum as the only item), their items [0, MA).
-template <int NT>
-__device__ __forceinline__ void encode_runs(const uint64_t* it, uint32_t m, uint64_t* srt, uint32_t* seg,
-                                            uint16_t* sid, uint32_t* r_start, uint32_t* r_dest, uint16_t* r_new,
-                                            uint16_t* r_of, uint32_t* s_w, uint32_t* info) {
-  constexpr int IPT = (kRedCap + NT - 1) / NT;
-  const int tid = threadIdx.x;
-  if (tid == 0) info[3] = 0u;
-  // 1. runs: the thread's IPT consecutive items
-  bool head[IPT];
-  uint32_t nh = 0;
-  bool fresh = false;
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const uint32_t j = (uint32_t)tid * IPT + k;
-    head[k] = j < m && (j == 0 || item_group(it[j]) != item_group(it[j - 1]));
-    nh += head[k] ? 1u : 0u;
-    fresh |= j < m && item_fresh(it[j]);
-  }
-  uint32_t S;
-  uint32_t r = block_exclusive_scan<NT>(nh, s_w, &S);
-  if (fresh) info[3] = 1u;
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const uint32_t j = (uint32_t)tid * IPT + k;
-    if (head[k]) r_start[r++] = j;
-    if (j < m) r_of[j] = (uint16_t)(r - 1);
-  }
-  if (tid == 0) r_start[S] = m;
-  __syncthreads();
-  // 2. new places: runs that need a sum first, in order, then the others
-  bool multi[IPT];
-  uint32_t len[IPT];
-  uint32_t packed = 0;  // runs that need a sum | their items << 16
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const uint32_t q = (uint32_t)tid * IPT + k;
-    multi[k] = false;
-    len[k] = 0;
-    if (q < S) {
-      len[k] = r_start[q + 1] - r_start[q];
-      multi[k] = len[k] > 1 || item_summed(it[r_start[q]]);
-      packed += multi[k] ? (1u | (len[k] << 16)) : 0u;
-    }
-  }
-  uint32_t tot;
-  const uint32_t pre = block_exclusive_scan<NT>(packed, s_w, &tot);
-  const uint32_t SA = tot & 0xFFFFu, MA = tot >> 16;
-  uint32_t na = pre & 0xFFFFu, ia = pre >> 16;
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const uint32_t q = (uint32_t)tid * IPT + k;
-    if (q < S) {
-      uint32_t ns, nd;
-      if (multi[k]) {
-        ns = na++;
-        nd = ia;
-        ia += len[k];
-      } else {
-        ns = SA + (q - na);  // the runs before q that need no sum, each one item
-        nd = MA + (q - na);
-      }
-      r_new[q] = (uint16_t)ns;
-      r_dest[q] = nd;
-      seg[ns] = nd;
-    }
-  }
-  if (tid == 0) {
-    seg[S] = m;
-    info[0] = S;
-    info[1] = SA;
-    info[2] = MA;
-  }
-  __syncthreads();
-  // 3. every item to its place
-  for (uint32_t j = tid; j < m; j += NT) {
-    const uint32_t q = r_of[j];
-    const uint32_t d = r_dest[q] + (j - r_start[q]);
-    srt[d] = it[j];
-    sid[d] = r_new[q];
-  }
-  __syncthreads();
-}
-
-template <class M, int NT, bool kClk>
-__global__ __launch_bounds__(NT) void k_rsort_reduce(
-    Bucket* __restrict__ idx, const uint64_t* __restrict__ sorted, const uint32_t* __restrict__ total,
-    int ntiles, const NewKey* __restrict__ newlist, const uint32_t* __restrict__ tile_cnt,
-    const float* __restrict__ grads, double* __restrict__ partials, const RowStore store,
-    float* __restrict__ state, int D, uint64_t seed, float lr, float eps, int64_t capacity, Ctrl* ctrl,
-    uint64_t epoch, int op, unsigned long long* __restrict__ clock) {
-  using L = ReduceLds<NT>;
+#ifndef MLKV_MAP
+template <bool kUpsert, int VEC, bool kClk>
+__global__ __launch_bounds__(kGroupThreads) void k_rsort_group(const PutGroupArgs a,
+                                                               const uint32_t* __restrict__ total, const AssignArgs aa,
+                                                               const RowStore store, uint64_t seed) {
+  using L = GroupLds;
+  constexpr int NT = kGroupThreads;
   extern __shared__ __align__(16) unsigned char s_raw[];
   uint64_t* s_it = reinterpret_cast<uint64_t*>(s_raw + L::it);
-  uint32_t* s_rstart = reinterpret_cast<uint32_t*>(s_raw + L::hidx);  // [kRedCap + 1]
-  uint32_t* s_rdest = reinterpret_cast<uint32_t*>(s_raw + L::hcnt);
-  uint16_t* s_rnew = reinterpret_cast<uint16_t*>(s_raw + L::inv);
-  uint16_t* s_rof = reinterpret_cast<uint16_t*>(s_raw + L::slot);
-  double* s_piece = reinterpret_cast<double*>(s_raw);      // reused region
-  uint64_t* s_chunk = reinterpret_cast<uint64_t*>(s_raw);  // reused region
-  uint64_t* s_srt = reinterpret_cast<uint64_t*>(s_raw + L::srt);
-  uint32_t* s_seg = reinterpret_cast<uint32_t*>(s_raw + L::seg);
-  uint16_t* s_sid = reinterpret_cast<uint16_t*>(s_raw + L::sid);
-  uint32_t* s_pref = reinterpret_cast<uint32_t*>(s_raw + L::pref);
+  uint32_t* s_seg = reinterpret_cast<uint32_t*>(s_raw + L::hidx);  // [kRedCap + 1]
   uint32_t* s_w = reinterpret_cast<uint32_t*>(s_raw + L::w);
   unsigned long long* s_w64 = reinterpret_cast<unsigned long long*>(s_raw + L::w64);
-  uint32_t* s_info = reinterpret_cast<uint32_t*>(s_raw + L::misc);
-  uint32_t* s_slo = reinterpret_cast<uint32_t*>(s_raw + L::slo);
+  unsigned long long* s_tot = reinterpret_cast<unsigned long long*>(s_raw + L::misc);
+  uint32_t* s_base = reinterpret_cast<uint32_t*>(s_raw + L::misc + 16);
   static_assert(kRedHash >= kRedCap + 1, "run starts fit the hash region");
 
-  const uint64_t size0 = ctrl->size[epoch & 1];
-  const uint64_t new_e = ctrl->new_epoch, ovf_e = ctrl->overflow_epoch;
-  const uint64_t bad_e = ctrl->apput_bad_epoch == epoch ? epoch : ctrl->bad_epoch;
-  const uint64_t Mnew = new_e == epoch ? count_new_keys<NT>(tile_cnt, ntiles, s_w64) : 0ull;
-  const int err = call_verdict(ctrl, epoch, size0, Mnew, capacity, bad_e, ovf_e, ctrl->apput_absent_epoch);
+  const PutVerdict v = put_verdict<NT>(a.ctrl, a.epoch, a.capacity, aa.tile_cnt, a.ntiles, s_w64);
   const uint32_t T = *total;
   const uint32_t nb = gridDim.x, b = blockIdx.x;
-  const uint32_t lo = rs_cut<NT>(sorted, T, (uint32_t)((uint64_t)T * b / nb), s_info + 4);
-  const uint32_t hi = rs_cut<NT>(sorted, T, (uint32_t)((uint64_t)T * (b + 1) / nb), s_info + 4);
+  const uint32_t lo = rs_cut<NT>(a.items, T, (uint32_t)((uint64_t)T * b / nb), s_base);
+  const uint32_t hi = rs_cut<NT>(a.items, T, (uint32_t)((uint64_t)T * (b + 1) / nb), s_base);
   const uint32_t m = hi - lo;
-  if (m == 0) return;
-  if (err) {
-    // undo the insertions of this call whose keys have their runs here
-    for (uint32_t j = threadIdx.x; j < m; j += NT) {
-      const uint64_t x = sorted[lo + j];
-      if (item_fresh(x)) {
-        const uint32_t slot = item_tag(x);
-        idx[slot / kSlots].key[slot % kSlots] = kEmptyKey;
-      }
-    }
-    return;
+  if (!v.err && m > (uint32_t)kRedCap) {  // runs are at most one item per put tile; the host keeps this from happening
+    if (threadIdx.x == 0) atomicCAS(&a.ctrl->latched, 0, -4);
+  } else if (!v.err && m > 0) {
+    for (uint32_t j = threadIdx.x; j < m; j += NT) s_it[j] = a.items[lo + j];
+    __syncthreads();
+    const uint32_t S = encode_segments<NT>(s_it, m, s_seg, s_w);
+    if constexpr (kUpsert) upsert_sorted<NT, VEC, kClk>(s_it, s_seg, S, a, store);
+    else units_of_sorted<NT>(s_it, s_seg, S, a.units, a.ctrl, s_tot, s_base);
   }
-  if (m > (uint32_t)kRedCap) {  // runs are at most one item per put tile; the host keeps this from happening
-    if (threadIdx.x == 0) atomicCAS(&ctrl->latched, 0, -4);
-    return;
+  if (v.M != 0 && b < aa.blocks) {
+    __syncthreads();
+    assign_new<NT, kPutTile>(aa, store, seed, v.size0, v.M, v.err, *reinterpret_cast<AssignLds<NT>*>(s_raw));
   }
-  for (uint32_t j = threadIdx.x; j < m; j += NT) s_it[j] = sorted[lo + j];
-  __syncthreads();
-  encode_runs<NT>(s_it, m, s_srt, s_seg, s_sid, s_rstart, s_rdest, s_rnew, s_rof, s_w, s_info);
-  const uint32_t S = s_info[0], SA = s_info[1], MA = s_info[2];
-  const RedCtx c{op, idx, grads, partials, store, state, D, seed, lr, eps, size0, clock};
-  if (s_info[3] != 0u)
-    resolve_new_rows<NT>(s_srt, s_seg, S, c, newlist, tile_cnt, ntiles, s_pref, s_w, s_w64, s_chunk);
-  if (op == kOpAssign) assign_segments<M, NT, kClk>(s_srt, s_seg, S, c);
-  else sum_and_update<M, NT, kClk>(s_srt, s_seg, s_sid, S, SA, MA, c, s_piece, s_slo);
 }
+#endif  // MLKV_MAP
 
 #ifndef MLKV_MAP
 // ===========================================================================
@@ -2915,27 +2574,38 @@ __global__ __launch_bounds__(256) void k_read_clock(const unsigned long long* __
 // Launchers
 // ===========================================================================
 #ifndef MLKV_MAP
+template <int VEC>
+static auto probe_kernel(const GetArgs& a) {
+  return a.clock != nullptr ? k_get_probe<VEC, true, false>
+         : a.pc_in          ? k_get_probe<VEC, false, true>
+                            : k_get_probe<VEC, false, false>;
+}
+
 hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
   const int tlen = get_tile_len(a.n, a.cus);
   const int64_t ntiles = (a.n + tlen - 1) / tlen;
   const uint32_t ranges = (uint32_t)std::min<int64_t>(ntiles, kMaxRanges);  // row assignment: a block per key range
   RangeLists rl = a.rl;
   if (rl.list != nullptr) rl.cap = (uint32_t)std::min<uint64_t>(rl.entries / ranges, 0xFFFFFFFFull);
+  const int vec = a.D >= 4 ? 4 : 1;
+  const uint64_t units = (uint64_t)(a.D + vec - 1) / vec;  // of a row
+  const bool narrow = a.out != nullptr && units <= kNarrowUnits;
   hook(K_GET_PROBE, 0, st);
-  auto kern = a.clock != nullptr ? k_get_probe<true, false> : a.pc_in ? k_get_probe<false, true> : k_get_probe<false, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kGetTile), 0, st, a.idx, a.nb_log2, a.keys, a.n, a.newlist,
-                     a.tile_cnt, a.ctrl, a.epoch, a.clock, a.cepoch, a.bound, a.blocked, a.pc_key, a.pos_row, tlen,
-                     rl, ranges);
+  auto kern = !narrow    ? probe_kernel<0>(a)
+              : vec == 4 ? probe_kernel<4>(a)
+                         : probe_kernel<1>(a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kGetTile), 0, st, a.idx, a.nb_log2, a.keys, a.n, a.out,
+                     a.store, a.seed, a.newlist, a.tile_cnt, a.ctrl, a.epoch, a.clock, a.cepoch, a.bound, a.blocked,
+                     a.pc_key, a.pos_row, tlen, rl, ranges);
   hook(K_GET_PROBE, 1, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int vec = a.D >= 4 ? 4 : 1;
-  const uint64_t units = (uint64_t)(a.D + vec - 1) / vec;  // of a row
   const uint64_t per_block = (uint64_t)kCopyThreads * kCopyUnits;
+  const bool copy = a.out != nullptr && !narrow;
   const uint64_t blocks =
-      a.out != nullptr ? std::min<uint64_t>(((uint64_t)a.n * units + per_block - 1) / per_block, kCopyBlocks) : 0;
+      copy ? std::min<uint64_t>(((uint64_t)a.n * units + per_block - 1) / per_block, kCopyBlocks) : 0;
   GetRowsArgs r;
-  r.out = a.out;
+  r.out = copy ? a.out : nullptr;
   r.keys = a.keys;
   r.rows = a.pos_row;
   r.blocked = a.blocked;
@@ -2958,6 +2628,7 @@ hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) 
   s.clock = a.clock;
   s.cepoch = a.cepoch;
   s.rl = rl;
+  s.values = nullptr;
   s.blocks = ranges;
   const unsigned grid = (unsigned)std::max<uint64_t>(blocks, ranges);
   const bool track = a.clock != nullptr;
@@ -2989,128 +2660,45 @@ hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits
 }
 #endif  // MLKV_MAP
 
-// Lets kernel `f` (an instance of a reduce kernel) use `bytes` of dynamic
-// LDS on the current device; `done` remembers the devices where that is set.
-template <int kMaxDev>
-static hipError_t lds_attr(const void* f, int bytes, bool (&done)[kMaxDev]) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev >= 0 && dev < kMaxDev && done[dev]) return hipSuccess;
-  e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess && dev >= 0 && dev < kMaxDev) done[dev] = true;
-  return e;
-}
-
-// Whether the put_reduce instance of row map M may use its dynamic LDS on
-// each device (set once per device).
-template <class M, bool kClk, bool kUpsert>
-static hipError_t reduce_lds_attr() {
-  static bool done[64] = {};
-  constexpr int NT = ReduceCfg<M>::NT;
-  return lds_attr(reinterpret_cast<const void*>(&k_put_reduce<M, NT, kClk, kUpsert>), (int)ReduceLds<NT>::total,
-                  done);
-}
-
-// The same for the radix reduce instance of row map M.
-template <class M, bool kClk>
-static hipError_t rsort_lds_attr() {
-  static bool done[64] = {};
-  constexpr int NT = ReduceCfg<M>::NT;
-  return lds_attr(reinterpret_cast<const void*>(&k_rsort_reduce<M, NT, kClk>), (int)ReduceLds<NT>::total, done);
-}
-
 // The probe kernel of a put, with 2^pb partitions.
 template <class M>
-static hipError_t launch_put_probe(const PutArgs& a, int pb, hipStream_t st, const LaunchHook& hook) {
+hipError_t launch_put_probe_t(const PutArgs& a, int pb, hipStream_t st, const LaunchHook& hook) {
   const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
+  // an upsert keeps each key's last position; radix dedup has room for one item per key and tile
+  const uint32_t dup_min =
+      a.op == kOpAssign || a.dedup == kDedupRadix || a.D <= 32 ? 2u : (uint32_t)kPresumMinWide;
   auto kern = a.ahead ? k_put_probe<M, true> : k_put_probe<M, false>;
   hook(K_PUT_PROBE, 0, st);
   hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kPutThreads), 0, st, a.idx, a.nb_log2, a.keys, a.grads,
-                     a.n, a.tlen, a.D, a.op, pb, (int)ntiles, a.items, a.meta, a.partials, a.newlist, a.tile_cnt,
+                     a.n, a.tlen, a.D, a.op, dup_min, pb, (int)ntiles, a.items, a.meta, a.partials, a.newlist, a.tile_cnt,
                      a.ctrl, a.epoch, a.pc_key, a.pc_row);
   hook(K_PUT_PROBE, 1, st);
   return hipGetLastError();
 }
 
-// Put with radix dedup: put_probe (one partition), the radix passes, the
-// reduce over the sorted items.
+// The row updates of a put that sums gradients: about kApplyKeys keys a lane
+// group, but up to kApplyBlocks blocks per CU for batches that have a key for
+// each of their groups.
+constexpr int64_t kApplyKeys = 4, kApplyBlocks = 8;
 template <class M>
-static hipError_t launch_put_radix(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
-  constexpr int NT = ReduceCfg<M>::NT;
-  using L = ReduceLds<NT>;
-  const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
-  hipError_t e = hipSuccess;
-  if (phase != kPutAfterProbe && (e = launch_put_probe<M>(a, 0, st, hook)) != hipSuccess) return e;
-  if (phase == kPutProbe) return hipSuccess;
-  // passes of at most kRsMaxBits bits (at least 4: a sort key spans at least 4 bits)
-  const int passes = (a.rs_bits + kRsMaxBits - 1) / kRsMaxBits;
-  const int bits = (a.rs_bits + passes - 1) / passes;
-  const int rtiles = (int)((ntiles + 3) / 4);
-  const int stride = (rtiles + 3) / 4 * 4;  // a digit's row of counts, padded to 16 bytes
-  uint32_t* cnt = a.rs_cnt;
-  uint32_t* total = a.rs_cnt + (size_t)stride * (1u << bits);
-  uint64_t* buf[2] = {a.rs_buf, a.rs_buf + a.n};
-  const uint32_t cap = (uint32_t)a.capacity;
-  for (int p = 0; p < passes; ++p) {
-    RsSrc src;
-    src.src = p == 0 ? a.items : buf[(p - 1) & 1];
-    src.meta = p == 0 ? a.meta : nullptr;
-    src.ntiles = (int)ntiles;
-    src.total = total;
-    if ((e = launch_rsort_pass(src, cap, p * bits, bits, cnt, rtiles, stride, buf[p & 1],
-                               p == 0 ? total : (uint32_t*)nullptr, st, hook)) != hipSuccess)
-      return e;
-  }
-  const bool clk = a.clock != nullptr;
-  if ((e = clk ? rsort_lds_attr<M, true>() : rsort_lds_attr<M, false>()) != hipSuccess) return e;
-  // blocks: one per CU at least, at most kRsChunk sorted items each before the cuts move
-  const int64_t nb = std::max<int64_t>(a.cus, (a.n + kRsChunk - 1) / kRsChunk);
-  auto rkern = clk ? k_rsort_reduce<M, NT, true> : k_rsort_reduce<M, NT, false>;
-  hook(K_RSORT_REDUCE, 0, st);
-  hipLaunchKernelGGL(rkern, dim3((unsigned)nb), dim3(NT), L::total, st, a.idx, (const uint64_t*)buf[(passes - 1) & 1], (const uint32_t*)total,
-                     (int)ntiles, a.newlist, a.tile_cnt, a.grads, a.partials, a.store, a.state, a.D, a.seed, a.lr,
-                     a.eps, a.capacity, a.ctrl, a.epoch, a.op, a.clock);
-  hook(K_RSORT_REDUCE, 1, st);
-  return hipGetLastError();
-}
-
-template <class M>
-hipError_t launch_put_t(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
-  constexpr int NT = ReduceCfg<M>::NT;
-  using L = ReduceLds<NT>;
-  static_assert((size_t)ReduceCfg<M>::NG * ReduceCfg<M>::DMAX * sizeof(double) <= L::reuse,
-                "pieces of cut segments must fit the reused LDS region");
-  static_assert((size_t)(kChunk + NT) * sizeof(uint64_t) + (size_t)(NT + 1) * sizeof(uint32_t) <= L::reuse,
-                "new-key chunk, sorted new keys and their counts must fit the reused LDS region");
-  static_assert(L::total <= 160 * 1024, "LDS budget of a gfx950 workgroup");
-  if (a.dedup == kDedupRadix) return launch_put_radix<M>(a, st, hook, phase);
-  const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
-  const int np = 1 << a.pb;
-  hipError_t e = hipSuccess;
-  if (phase != kPutAfterProbe && (e = launch_put_probe<M>(a, a.pb, st, hook)) != hipSuccess) return e;
-  if (phase == kPutProbe) return hipSuccess;
-  const bool clk = a.clock != nullptr;  // a bounded table: puts lower the staleness counts
-  const bool ups = a.op == kOpAssign;
-  if ((e = clk ? (ups ? reduce_lds_attr<M, true, true>() : reduce_lds_attr<M, true, false>())
-               : (ups ? reduce_lds_attr<M, false, true>() : reduce_lds_attr<M, false, false>())) != hipSuccess)
-    return e;
-  auto kern = clk ? (ups ? k_put_reduce<M, NT, true, true> : k_put_reduce<M, NT, true, false>)
-                  : (ups ? k_put_reduce<M, NT, false, true> : k_put_reduce<M, NT, false, false>);
-  hook(K_PUT_REDUCE, 0, st);
-  hipLaunchKernelGGL(kern, dim3((unsigned)np), dim3(NT),
-                     L::total, st, a.idx, a.items, a.meta, (int)ntiles, a.newlist, a.tile_cnt, a.grads, a.partials,
-                     a.store, a.state, a.D, a.seed, a.lr, a.eps, a.capacity, a.ctrl, a.epoch, a.spill, a.spill_words,
-                     a.op, a.clock);
-  hook(K_PUT_REDUCE, 1, st);
+hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st, const LaunchHook& hook) {
+  constexpr int64_t NG = (kApplyThreads / 64) * M::RPW;
+  const int64_t blocks = std::max<int64_t>(std::min<int64_t>(kApplyBlocks * a.cus, (a.n + NG - 1) / NG),
+                                           (a.n + NG * kApplyKeys - 1) / (NG * kApplyKeys));
+  auto kern = a.clock != nullptr ? k_put_apply<M, true> : k_put_apply<M, false>;
+  hook(K_PUT_APPLY, 0, st);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kApplyThreads), 0, st, u, a.store);
+  hook(K_PUT_APPLY, 1, st);
   return hipGetLastError();
 }
 
 #ifdef MLKV_MAP
-template hipError_t launch_put_t<MLKV_MAP>(const PutArgs&, hipStream_t, const LaunchHook&, int);
+template hipError_t launch_put_probe_t<MLKV_MAP>(const PutArgs&, int, hipStream_t, const LaunchHook&);
+template hipError_t launch_put_apply_t<MLKV_MAP>(const PutArgs&, const PutApplyArgs&, hipStream_t, const LaunchHook&);
 #else
-#define MLKV_EXTERN(M) \
-  extern template hipError_t launch_put_t<M>(const PutArgs&, hipStream_t, const LaunchHook&, int);
+#define MLKV_EXTERN(M)                                                                                   \
+  extern template hipError_t launch_put_probe_t<M>(const PutArgs&, int, hipStream_t, const LaunchHook&); \
+  extern template hipError_t launch_put_apply_t<M>(const PutArgs&, const PutApplyArgs&, hipStream_t, const LaunchHook&);
 MLKV_MAPS(MLKV_EXTERN)
 
 template <class F>
@@ -3125,8 +2713,142 @@ static hipError_t dispatch_map(int D, F f) {
   return f(MapD1024{});
 }
 
+// Lets kernel `f` use `bytes` of dynamic LDS on the current device; `done`
+// remembers the devices where that is set.
+template <int kMaxDev>
+static hipError_t lds_attr(const void* f, int bytes, bool (&done)[kMaxDev]) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev >= 0 && dev < kMaxDev && done[dev]) return hipSuccess;
+  e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && dev >= 0 && dev < kMaxDev) done[dev] = true;
+  return e;
+}
+
+// Launches grouping kernel `kern` (an instance, with `done` of its own) with its LDS.
+template <class Kern, class... A>
+static hipError_t launch_grouping(Kern kern, bool (&done)[64], unsigned blocks, hipStream_t st, const LaunchHook& hook,
+                                  const A&... args) {
+  hipError_t e = lds_attr(reinterpret_cast<const void*>(kern), (int)GroupLds::total, done);
+  if (e != hipSuccess) return e;
+  hook(K_PUT_GROUP, 0, st);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGroupThreads), GroupLds::total, st, args...);
+  hook(K_PUT_GROUP, 1, st);
+  return hipGetLastError();
+}
+
+template <bool kUpsert, int VEC, bool kClk>
+static hipError_t launch_group_t(const PutGroupArgs& g, const uint32_t* total, const AssignArgs& s, const PutArgs& a,
+                                 unsigned blocks, hipStream_t st, const LaunchHook& hook) {
+  static bool done[64] = {}, done_sorted[64] = {};
+  if (total != nullptr)
+    return launch_grouping(k_rsort_group<kUpsert, VEC, kClk>, done_sorted, blocks, st, hook, g, total, s, a.store,
+                           a.seed);
+  return launch_grouping(k_put_group<kUpsert, VEC, kClk>, done, blocks, st, hook, g, s, a.store, a.seed);
+}
+
+// The grouping kernel of a put: over the partitions, or over the sorted items
+// (`total` of them).
+static hipError_t launch_group(const PutGroupArgs& g, const uint32_t* total, const AssignArgs& s, const PutArgs& a,
+                               unsigned blocks, hipStream_t st, const LaunchHook& hook) {
+  if (a.op != kOpAssign) return launch_group_t<false, 4, false>(g, total, s, a, blocks, st, hook);
+  const bool clk = a.clock != nullptr;
+  if (a.D >= 4)
+    return clk ? launch_group_t<true, 4, true>(g, total, s, a, blocks, st, hook)
+               : launch_group_t<true, 4, false>(g, total, s, a, blocks, st, hook);
+  return clk ? launch_group_t<true, 1, true>(g, total, s, a, blocks, st, hook)
+             : launch_group_t<true, 1, false>(g, total, s, a, blocks, st, hook);
+}
+
+// The radix passes over put_probe's items (one partition): *sorted, *total.
+static hipError_t launch_radix_sort(const PutArgs& a, hipStream_t st, const LaunchHook& hook, const uint64_t** sorted,
+                                    const uint32_t** total_out) {
+  const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
+  // passes of at most kRsMaxBits bits (at least 4: a sort key spans at least 4 bits)
+  const int passes = (a.rs_bits + kRsMaxBits - 1) / kRsMaxBits;
+  const int bits = (a.rs_bits + passes - 1) / passes;
+  const int rtiles = (int)((ntiles + 3) / 4);
+  const int stride = (rtiles + 3) / 4 * 4;  // a digit's row of counts, padded to 16 bytes
+  uint32_t* cnt = a.rs_cnt;
+  uint32_t* total = a.rs_cnt + (size_t)stride * (1u << bits);
+  uint64_t* buf[2] = {a.rs_buf, a.rs_buf + a.n};
+  for (int p = 0; p < passes; ++p) {
+    RsSrc src;
+    src.src = p == 0 ? a.items : buf[(p - 1) & 1];
+    src.meta = p == 0 ? a.meta : nullptr;
+    src.ntiles = (int)ntiles;
+    src.total = total;
+    hipError_t e = launch_rsort_pass(src, (uint32_t)a.capacity, p * bits, bits, cnt, rtiles, stride, buf[p & 1],
+                                     p == 0 ? total : (uint32_t*)nullptr, st, hook);
+    if (e != hipSuccess) return e;
+  }
+  *sorted = buf[(passes - 1) & 1];
+  *total_out = total;
+  return hipSuccess;
+}
+
 hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
-  return dispatch_map(a.D, [&](auto m) { return launch_put_t<decltype(m)>(a, st, hook, phase); });
+  const bool radix = a.dedup == kDedupRadix;
+  const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
+  hipError_t e = hipSuccess;
+  if (phase != kPutAfterProbe) {
+    e = dispatch_map(a.D, [&](auto m) { return launch_put_probe_t<decltype(m)>(a, radix ? 0 : a.pb, st, hook); });
+    if (e != hipSuccess) return e;
+  }
+  if (phase == kPutProbe) return hipSuccess;
+  PutGroupArgs g;
+  g.items = a.items;
+  g.meta = a.meta;
+  g.ntiles = (int)ntiles;
+  const int vec = a.D >= 4 ? 4 : 1;
+  const uint32_t row_units = (uint32_t)(a.D + vec - 1) / vec;
+  g.magic = row_units > 1 ? (uint32_t)((0x100000000ull + row_units - 1) / row_units) : 0u;
+  g.values = a.grads;
+  g.clock = a.clock;
+  g.units = a.units;
+  g.units.long_over = a.D <= 32 ? kLongNarrow : kLongWide;
+  g.ctrl = a.ctrl;
+  g.epoch = a.epoch;
+  g.capacity = a.capacity;
+  g.spill = a.spill;
+  g.spill_words = a.spill_words;
+  AssignArgs s;  // rows for the keys the put inserts; their staleness counts start at 0
+  s.idx = a.idx;
+  s.newlist = a.newlist;
+  s.tile_cnt = a.tile_cnt;
+  s.ntiles = (int)ntiles;
+  s.tile_size = kPutTile;
+  s.state = a.state;
+  s.capacity = a.capacity;
+  s.ctrl = a.ctrl;
+  s.epoch = a.epoch;
+  s.xkey = a.xkey;
+  s.xslot = a.xslot;
+  s.clock = nullptr;
+  s.cepoch = 0;
+  s.rl = RangeLists{};
+  s.values = a.op == kOpAssign ? a.grads : nullptr;
+  const uint32_t* total = nullptr;
+  // blocks: one per partition, or (radix) one per CU at least, at most kRsChunk
+  // sorted items each before the cuts move
+  const int64_t nb = radix ? std::max<int64_t>(a.cus, (a.n + kRsChunk - 1) / kRsChunk) : (int64_t)1 << a.pb;
+  if (radix && (e = launch_radix_sort(a, st, hook, &g.items, &total)) != hipSuccess) return e;
+  s.blocks = (uint32_t)std::min<int64_t>(nb, kMaxRanges);
+  e = launch_group(g, total, s, a, (unsigned)nb, st, hook);
+  if (e != hipSuccess || a.op == kOpAssign) return e;
+  PutApplyArgs u;
+  u.idx = a.idx;
+  u.grads = a.grads;
+  u.partials = a.partials;
+  u.units = a.units;
+  u.ctrl = a.ctrl;
+  u.state = a.state;
+  u.clock = a.clock;
+  u.op = a.op;
+  u.lr = a.lr;
+  u.eps = a.eps;
+  return dispatch_map(a.D, [&](auto m) { return launch_put_apply_t<decltype(m)>(a, u, st, hook); });
 }
 
 hipError_t launch_lookup(Bucket* idx, uint32_t nb_log2, const uint64_t* keys, int64_t n, int64_t* rows_out,

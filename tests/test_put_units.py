@@ -1,0 +1,105 @@
+"""Puts through their units (keys with one row, short sums, long sums) and
+puts that insert keys, against the CPU oracle.
+
+The grouping kernel leaves one unit per distinct key: a row seen once, a sum
+that one lane group adds (up to 8 items for rows of at most 32 floats, 16 for
+wider ones) or a longer one that a block adds; a key brings one item per put
+tile of 1024 positions. Items of a unit are ordered pairwise up to 32 of them
+and through one of 16 masks above. Bar: rows of Put and key -> row bit-exact,
+updated rows and accumulators within the harness's bound.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2504_01506_amd import mlkv
+from _harness import Pair, dev, dev_keys, log
+
+pytestmark = pytest.mark.gpu
+
+MULT = np.uint64(0x9E3779B97F4A7C15)
+TILE = 1024
+COUNTS = (1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 40)
+
+
+def _spread(ids):
+    return np.asarray(ids, dtype=np.uint64) * MULT + np.uint64(3)
+
+
+def _keys_by_tiles(rng, tiles=280):
+    """`tiles` put tiles: keys that occur in exactly c of them (once or three
+    times in each), for every c above, and keys seen once."""
+    cols = [[] for _ in range(tiles)]
+    nid = 1
+    for c in COUNTS:
+        for _ in range(60 if c >= 31 else 20):  # more units above the mask length than masks
+            for t in rng.choice(tiles, size=c, replace=False):
+                cols[t] += [nid] * (3 if nid % 3 == 0 else 1)
+            nid += 1
+    out = []
+    for t in range(tiles):
+        fill = np.arange(nid, nid + TILE - len(cols[t]))
+        nid += fill.size
+        out.append(rng.permutation(np.concatenate([np.array(cols[t], dtype=np.int64), fill])))
+    return _spread(np.concatenate(out)), nid
+
+
+@pytest.mark.parametrize("dim", [3, 32, 33, 130])
+@pytest.mark.parametrize("dedup", ["hash", "radix"])
+def test_sums_of_every_length_class(dim, dedup):
+    rng = np.random.default_rng(dim)
+    keys, nid = _keys_by_tiles(rng)
+    assert keys.size == 280 * TILE
+    pr = Pair(dim, nid + 10, dedup=dedup)
+    pr.put(keys, rng.normal(0, 0.01, size=(keys.size, dim)).astype(np.float32), 0.01, 1e-8)  # inserts every key
+    pr.put_sgd(keys, rng.normal(0, 0.01, size=(keys.size, dim)).astype(np.float32), 0.05)
+    pr.upsert(keys, rng.normal(size=(keys.size, dim)).astype(np.float32))
+    pr.put(keys, rng.normal(0, 0.01, size=(keys.size, dim)).astype(np.float32), 0.01, 1e-8)
+    pr.compare_rows()
+    log(f"[units] dim {dim} {dedup} stats={pr.stats}")
+    pr.close()
+
+
+@pytest.mark.parametrize("dim", [1, 4, 30, 130])
+@pytest.mark.parametrize("n", [300, 5000, 220_000])
+def test_upsert_inserts_keys_from_their_last_position(dim, n):
+    # new and present keys mixed, repeated within tiles and across them; then
+    # an upsert that does not fit (the table stays as it was), then one of the
+    # keys that failed
+    rng = np.random.default_rng(dim * 7 + n)
+    ids = rng.integers(1, n, size=n)
+    distinct = np.unique(ids).size
+    pr = Pair(dim, distinct + 50)
+    half = _spread(ids[: n // 2])
+    pr.upsert(half, rng.normal(size=(half.size, dim)).astype(np.float32))
+    keys = _spread(ids)
+    pr.upsert(keys, rng.normal(size=(n, dim)).astype(np.float32))
+    over = _spread(np.arange(n + 1, n + 200))
+    vals = rng.normal(size=(over.size, dim)).astype(np.float32)
+    assert pr.ora.put(over, vals) == O.EFULL
+    pr.gpu.put(dev_keys(over), dev(vals))
+    assert pr.gpu.sync() == mlkv.MLKV_EFULL
+    again = np.concatenate([over[:40], keys[:20], over[:40]])
+    pr.upsert(again, rng.normal(size=(again.size, dim)).astype(np.float32))
+    pr.compare_rows()
+    pr.check_index()
+    pr.close()
+
+
+@pytest.mark.parametrize("how", ["get", "put", "upsert"])
+def test_a_table_loaded_from_equally_full_tiles(how):
+    # every tile's list of new keys is full and sorted: the sample that cuts
+    # the key space has to take other quantiles of each of them
+    rng = np.random.default_rng(8)
+    dim, n = 4, 256 * TILE
+    pr = Pair(dim, n)
+    keys = _spread(rng.permutation(n))
+    rows = rng.normal(0, 0.01, size=(n, dim)).astype(np.float32)
+    if how == "get":
+        pr.get(keys)
+    elif how == "put":
+        pr.put(keys, rows, 0.01, 1e-8)
+    else:
+        pr.upsert(keys, rows)
+    pr.compare_rows()
+    pr.close()
