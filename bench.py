@@ -39,13 +39,14 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBPS = 8000.0
 METRIC = "embedding get+put keys/sec and achieved HBM GB/s (% of peak), 1 MI355X"
 METRIC_KV = "key-value operations/sec, 50% get / 50% put, 1 MI355X"
-KERNELS = ("get_probe", "get_rows", "put_probe", "put_group", "put_apply", "rsort_count", "rsort_scatter")
+KERNELS = ("get_probe", "get_rows", "put_probe", "put_reduce", "rsort_count", "rsort_scatter",
+           "rsort_reduce")
 
 
 def kernel_bytes(n, U, M, D, dedup="hash"):
     """Algorithmic bytes each kernel must move for one batch: n lookups, U
-    distinct keys of which M are new, rows of D fp32. The grouping and the
-    radix passes move scratch only."""
+    distinct keys of which M are new, rows of D fp32. With radix dedup the
+    reduce's bytes are rsort_reduce's; the sort passes move scratch only."""
     b = {
         # keys in, one index entry (8 B tag + 4 B row) per distinct key
         "get_probe": 8 * n + 12 * U,
@@ -56,14 +57,13 @@ def kernel_bytes(n, U, M, D, dedup="hash"):
         "put_probe": 8 * n + 12 * U,
         # gradient rows in, distinct rows read and written, accumulators read
         # and written
-        "put_apply": 4 * D * n + 8 * D * U + 8 * U,
-        "put_group": 0,
+        "put_reduce": 4 * D * n + 8 * D * U + 8 * U,
     }
     return radix_bytes(b) if dedup == "radix" else b
 
 
 def radix_bytes(b):
-    return {**b, "rsort_count": 0, "rsort_scatter": 0}
+    return {**b, "rsort_count": 0, "rsort_scatter": 0, "rsort_reduce": b["put_reduce"], "put_reduce": 0}
 
 
 def kernel_bytes_kv(nr, Ur, nw, Uw, D, dedup="hash"):
@@ -75,8 +75,7 @@ def kernel_bytes_kv(nr, Ur, nw, Uw, D, dedup="hash"):
         "get_rows": 4 * D * Ur + 4 * D * nr,
         "put_probe": 8 * nw + 12 * Uw,
         # the winning value of each key in, its row written
-        "put_apply": 8 * D * Uw,
-        "put_group": 0,
+        "put_reduce": 8 * D * Uw,
     }
     return radix_bytes(b) if dedup == "radix" else b
 

@@ -282,11 +282,11 @@ int mlkv_read_staleness(mlkv_table *t, const int64_t *d_rows, int64_t n, uint32_
 /* ---- per-kernel timing (benchmarks) ----
  * The library runs MLKV_NUM_KERNELS kernels: 0 get_probe and
  * 1 get_rows for mlkv_get, mlkv_get_bounded and mlkv_lookahead;
- * 2 put_probe, 3 put_group and 9 put_apply for mlkv_put_grad and
- * mlkv_put_grad_sgd (2 and 3 for mlkv_put); 4 tier_mark, 5 tier_plan and 6 tier_copy for
- * mlkv_lookahead on a tiered table; with radix dedup (mlkv_set_dedup) a put
- * runs 7 rsort_count and 8 rsort_scatter once per radix pass between 2 and 3.
- * While enabled, HIP events are recorded on
+ * 2 put_probe and 3 put_reduce (its grouping and update launches together)
+ * for mlkv_put_grad, mlkv_put_grad_sgd and mlkv_put; 4 tier_mark, 5 tier_plan
+ * and 6 tier_copy for mlkv_lookahead on a tiered table; with radix dedup
+ * (mlkv_set_dedup) a put runs 2 put_probe, then 7 rsort_count and
+ * 8 rsort_scatter once per radix pass, then 9 rsort_reduce. While enabled, HIP events are recorded on
  * the call's stream before and after every launch. mlkv_profile_read waits
  * for the recorded launches, writes per-kernel sums of their durations (ms)
  * and launch counts into the host arrays total_ms[MLKV_NUM_KERNELS] and

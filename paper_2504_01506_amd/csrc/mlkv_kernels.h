@@ -46,13 +46,13 @@ enum KernelId : int {
   K_GET_PROBE = 0,
   K_GET_ROWS = 1,
   K_PUT_PROBE = 2,
-  K_PUT_GROUP = 3,
+  K_PUT_REDUCE = 3,    // put_group and put_apply
   K_TIER_MARK = 4,
   K_TIER_PLAN = 5,
   K_TIER_COPY = 6,
   K_RSORT_COUNT = 7,
   K_RSORT_SCATTER = 8,
-  K_PUT_APPLY = 9,
+  K_RSORT_REDUCE = 9,  // rsort_group and put_apply
   K_COUNT = 10
 };
 
@@ -319,7 +319,7 @@ hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits
 template <class M>
 hipError_t launch_put_probe_t(const PutArgs& a, int pb, hipStream_t st, const LaunchHook& hook);
 template <class M>
-hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st, const LaunchHook& hook);
+hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st);
 hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_tier_lookahead(const TierArgs& a, hipStream_t st, const LaunchHook& hook);
 hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase = kPutAll);

@@ -2681,24 +2681,22 @@ hipError_t launch_put_probe_t(const PutArgs& a, int pb, hipStream_t st, const La
 // each of their groups.
 constexpr int64_t kApplyKeys = 4, kApplyBlocks = 8;
 template <class M>
-hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st, const LaunchHook& hook) {
+hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream_t st) {
   constexpr int64_t NG = (kApplyThreads / 64) * M::RPW;
   const int64_t blocks = std::max<int64_t>(std::min<int64_t>(kApplyBlocks * a.cus, (a.n + NG - 1) / NG),
                                            (a.n + NG * kApplyKeys - 1) / (NG * kApplyKeys));
   auto kern = a.clock != nullptr ? k_put_apply<M, true> : k_put_apply<M, false>;
-  hook(K_PUT_APPLY, 0, st);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kApplyThreads), 0, st, u, a.store);
-  hook(K_PUT_APPLY, 1, st);
   return hipGetLastError();
 }
 
 #ifdef MLKV_MAP
 template hipError_t launch_put_probe_t<MLKV_MAP>(const PutArgs&, int, hipStream_t, const LaunchHook&);
-template hipError_t launch_put_apply_t<MLKV_MAP>(const PutArgs&, const PutApplyArgs&, hipStream_t, const LaunchHook&);
+template hipError_t launch_put_apply_t<MLKV_MAP>(const PutArgs&, const PutApplyArgs&, hipStream_t);
 #else
 #define MLKV_EXTERN(M)                                                                                   \
   extern template hipError_t launch_put_probe_t<M>(const PutArgs&, int, hipStream_t, const LaunchHook&); \
-  extern template hipError_t launch_put_apply_t<M>(const PutArgs&, const PutApplyArgs&, hipStream_t, const LaunchHook&);
+  extern template hipError_t launch_put_apply_t<M>(const PutArgs&, const PutApplyArgs&, hipStream_t);
 MLKV_MAPS(MLKV_EXTERN)
 
 template <class F>
@@ -2728,37 +2726,35 @@ static hipError_t lds_attr(const void* f, int bytes, bool (&done)[kMaxDev]) {
 
 // Launches grouping kernel `kern` (an instance, with `done` of its own) with its LDS.
 template <class Kern, class... A>
-static hipError_t launch_grouping(Kern kern, bool (&done)[64], unsigned blocks, hipStream_t st, const LaunchHook& hook,
+static hipError_t launch_grouping(Kern kern, bool (&done)[64], unsigned blocks, hipStream_t st,
                                   const A&... args) {
   hipError_t e = lds_attr(reinterpret_cast<const void*>(kern), (int)GroupLds::total, done);
   if (e != hipSuccess) return e;
-  hook(K_PUT_GROUP, 0, st);
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(kGroupThreads), GroupLds::total, st, args...);
-  hook(K_PUT_GROUP, 1, st);
   return hipGetLastError();
 }
 
 template <bool kUpsert, int VEC, bool kClk>
 static hipError_t launch_group_t(const PutGroupArgs& g, const uint32_t* total, const AssignArgs& s, const PutArgs& a,
-                                 unsigned blocks, hipStream_t st, const LaunchHook& hook) {
+                                 unsigned blocks, hipStream_t st) {
   static bool done[64] = {}, done_sorted[64] = {};
   if (total != nullptr)
-    return launch_grouping(k_rsort_group<kUpsert, VEC, kClk>, done_sorted, blocks, st, hook, g, total, s, a.store,
+    return launch_grouping(k_rsort_group<kUpsert, VEC, kClk>, done_sorted, blocks, st, g, total, s, a.store,
                            a.seed);
-  return launch_grouping(k_put_group<kUpsert, VEC, kClk>, done, blocks, st, hook, g, s, a.store, a.seed);
+  return launch_grouping(k_put_group<kUpsert, VEC, kClk>, done, blocks, st, g, s, a.store, a.seed);
 }
 
 // The grouping kernel of a put: over the partitions, or over the sorted items
 // (`total` of them).
 static hipError_t launch_group(const PutGroupArgs& g, const uint32_t* total, const AssignArgs& s, const PutArgs& a,
-                               unsigned blocks, hipStream_t st, const LaunchHook& hook) {
-  if (a.op != kOpAssign) return launch_group_t<false, 4, false>(g, total, s, a, blocks, st, hook);
+                               unsigned blocks, hipStream_t st) {
+  if (a.op != kOpAssign) return launch_group_t<false, 4, false>(g, total, s, a, blocks, st);
   const bool clk = a.clock != nullptr;
   if (a.D >= 4)
-    return clk ? launch_group_t<true, 4, true>(g, total, s, a, blocks, st, hook)
-               : launch_group_t<true, 4, false>(g, total, s, a, blocks, st, hook);
-  return clk ? launch_group_t<true, 1, true>(g, total, s, a, blocks, st, hook)
-             : launch_group_t<true, 1, false>(g, total, s, a, blocks, st, hook);
+    return clk ? launch_group_t<true, 4, true>(g, total, s, a, blocks, st)
+               : launch_group_t<true, 4, false>(g, total, s, a, blocks, st);
+  return clk ? launch_group_t<true, 1, true>(g, total, s, a, blocks, st)
+             : launch_group_t<true, 1, false>(g, total, s, a, blocks, st);
 }
 
 // The radix passes over put_probe's items (one partition): *sorted, *total.
@@ -2835,8 +2831,14 @@ hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, 
   const int64_t nb = radix ? std::max<int64_t>(a.cus, (a.n + kRsChunk - 1) / kRsChunk) : (int64_t)1 << a.pb;
   if (radix && (e = launch_radix_sort(a, st, hook, &g.items, &total)) != hipSuccess) return e;
   s.blocks = (uint32_t)std::min<int64_t>(nb, kMaxRanges);
-  e = launch_group(g, total, s, a, (unsigned)nb, st, hook);
-  if (e != hipSuccess || a.op == kOpAssign) return e;
+  const int timed = radix ? K_RSORT_REDUCE : K_PUT_REDUCE;  // the grouping and the updates, timed as one
+  hook(timed, 0, st);
+  e = launch_group(g, total, s, a, (unsigned)nb, st);
+  if (e != hipSuccess) return e;
+  if (a.op == kOpAssign) {
+    hook(timed, 1, st);
+    return hipSuccess;
+  }
   PutApplyArgs u;
   u.idx = a.idx;
   u.grads = a.grads;
@@ -2848,7 +2850,9 @@ hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, 
   u.op = a.op;
   u.lr = a.lr;
   u.eps = a.eps;
-  return dispatch_map(a.D, [&](auto m) { return launch_put_apply_t<decltype(m)>(a, u, st, hook); });
+  e = dispatch_map(a.D, [&](auto m) { return launch_put_apply_t<decltype(m)>(a, u, st); });
+  hook(timed, 1, st);
+  return e;
 }
 
 hipError_t launch_lookup(Bucket* idx, uint32_t nb_log2, const uint64_t* keys, int64_t n, int64_t* rows_out,
