@@ -17,11 +17,16 @@ using namespace mlkv;
 // A set of scratch buffers replaced by a larger one; freed once `done` (an
 // event recorded behind the last work that may use them) has completed.
 struct ScratchSet {
-  std::vector<void*> ptrs;
+  void* ptr = nullptr;
+  size_t bytes = 0;
   hipEvent_t done = nullptr;
 };
 
 struct mlkv_table {
+  void* memory = nullptr;   // the allocation of the index, the rows, the accumulators and the control block
+  size_t memory_bytes = 0;
+  void* scratch = nullptr;  // the allocation of the per-call scratch below
+  size_t scratch_bytes = 0;
   int device = 0;
   int32_t dim = 0;
   int64_t capacity = 0;
@@ -119,19 +124,101 @@ hipError_t dev_alloc(T** p, size_t bytes) {
   return hipMalloc(reinterpret_cast<void**>(p), bytes);
 }
 
-// The scratch buffers of a table, as one set (grown as a whole).
-void free_scratch_set(const ScratchSet& s) {
-  for (void* p : s.ptrs) (void)hipFree(p);
+// Released table memory, kept for the next table: a program that opens and
+// closes tables otherwise pays the driver for mapping (and clearing) it each
+// time, 0.3 to 8 ms for 200 MB, varying within a process. At most kPoolBytes
+// in all; the oldest blocks go first, and all of them go before an allocation
+// is reported as failed. A block comes back only once nothing on the device
+// uses it, and is taken under the lock, so any thread and stream may have it.
+constexpr size_t kPoolBytes = 256ull << 20;
+struct PoolBlock {
+  int device;
+  void* ptr;
+  size_t bytes;
+};
+std::mutex g_pool_mu;
+std::vector<PoolBlock> g_pool;  // oldest first
+size_t g_pool_bytes = 0;
+
+// Frees the oldest kept blocks until at most `keep` bytes remain (g_pool_mu held).
+void pool_trim(size_t keep) {
+  while (g_pool_bytes > keep) {
+    (void)hipFree(g_pool.front().ptr);
+    g_pool_bytes -= g_pool.front().bytes;
+    g_pool.erase(g_pool.begin());
+  }
 }
 
-ScratchSet current_set(mlkv_table* t) {
-  ScratchSet s;
-  s.ptrs = {t->newlist, t->tile_cnt, t->items, t->meta, t->spill, t->partials, t->pc_key, t->pc_row,
-            t->rs_cnt, t->units, t->miss, t->plan_slot, t->mid_xkey, t->mid_xslot, t->rl_list, t->rl_cnt, t->rl_cuts};
-  return s;
+// Memory for `*bytes` on the current device: a kept block at most a quarter
+// larger (*bytes becomes its size), else a new allocation.
+hipError_t pool_take(void** p, size_t* bytes) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  size_t best = g_pool.size();
+  for (size_t k = 0; k < g_pool.size(); ++k)
+    if (g_pool[k].device == dev && g_pool[k].bytes >= *bytes && g_pool[k].bytes <= *bytes + *bytes / 4 &&
+        (best == g_pool.size() || g_pool[k].bytes < g_pool[best].bytes))
+      best = k;
+  if (best < g_pool.size()) {
+    *p = g_pool[best].ptr;
+    *bytes = g_pool[best].bytes;
+    g_pool_bytes -= *bytes;
+    g_pool.erase(g_pool.begin() + (ptrdiff_t)best);
+    return hipSuccess;
+  }
+  e = dev_alloc(p, *bytes);
+  if (e == hipErrorOutOfMemory && !g_pool.empty()) {
+    (void)hipGetLastError();
+    pool_trim(0);
+    e = dev_alloc(p, *bytes);
+  }
+  return e;
 }
+
+// Gives back a block of pool_take that no queued work uses any more.
+void pool_give(int device, void* p, size_t bytes) {
+  if (p == nullptr) return;
+  if (bytes > kPoolBytes) {
+    (void)hipFree(p);
+    return;
+  }
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  pool_trim(kPoolBytes - bytes);
+  g_pool.push_back({device, p, bytes});
+  g_pool_bytes += bytes;
+}
+
+// Several arrays in one allocation, each at a multiple of 256 bytes. An
+// allocation and its release cost the host tens of microseconds each, and a
+// release waits for the device: a table's buffers as 25 allocations took 1.3 ms
+// to close.
+struct Arrays {
+  std::vector<std::pair<void**, size_t>> list;
+  template <class T>
+  void add(T** p, size_t bytes) {
+    *p = nullptr;
+    list.push_back({reinterpret_cast<void**>(p), (bytes + 255) / 256 * 256});
+  }
+  hipError_t alloc(void** base, size_t* bytes) {
+    *base = nullptr;
+    *bytes = 0;
+    for (auto& a : list) *bytes += a.second;
+    hipError_t e = pool_take(base, bytes);
+    if (e != hipSuccess) return e;
+    char* at = static_cast<char*>(*base);
+    for (auto& a : list) {
+      *a.first = at;
+      at += a.second;
+    }
+    return hipSuccess;
+  }
+};
 
 void clear_workspace_ptrs(mlkv_table* t) {
+  t->scratch = nullptr;
+  t->scratch_bytes = 0;
   t->miss = nullptr;
   t->plan_slot = nullptr;
   t->pc_key = nullptr;
@@ -154,9 +241,27 @@ void clear_workspace_ptrs(mlkv_table* t) {
   t->spill_words = 0;
 }
 
+// Releases the scratch (no queued work uses it).
 void free_workspace(mlkv_table* t) {
-  free_scratch_set(current_set(t));
+  pool_give(t->device, t->scratch, t->scratch_bytes);
   clear_workspace_ptrs(t);
+}
+
+// Retires the scratch behind an event recorded on `st`, which the work queued
+// before uses; nothing is retired if that fails.
+hipError_t retire_workspace(mlkv_table* t, hipStream_t st) {
+  ScratchSet old;
+  old.ptr = t->scratch;
+  old.bytes = t->scratch_bytes;
+  hipError_t e = hipEventCreateWithFlags(&old.done, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(old.done, st);
+  if (e != hipSuccess) {
+    if (old.done != nullptr) (void)hipEventDestroy(old.done);
+    return e;
+  }
+  t->retired.push_back(old);
+  clear_workspace_ptrs(t);
+  return hipSuccess;
 }
 
 // Frees the scratch sets replaced by larger ones, once the work queued
@@ -164,12 +269,11 @@ void free_workspace(mlkv_table* t) {
 int release_retired(mlkv_table* t) {
   int rc = MLKV_OK;
   for (auto& r : t->retired) {
-    if (r.done != nullptr) {
-      hipError_t e = hipEventSynchronize(r.done);
-      if (e != hipSuccess && rc == MLKV_OK) rc = hip_fail(e, "hipEventSynchronize");
-      (void)hipEventDestroy(r.done);
-    }
-    free_scratch_set(r);
+    hipError_t e = hipEventSynchronize(r.done);
+    if (e != hipSuccess && rc == MLKV_OK) rc = hip_fail(e, "hipEventSynchronize");
+    (void)hipEventDestroy(r.done);
+    if (e == hipSuccess) pool_give(t->device, r.ptr, r.bytes);
+    else (void)hipFree(r.ptr);
   }
   t->retired.clear();
   return rc;
@@ -217,14 +321,7 @@ int ensure_workspace(mlkv_table* t, int64_t n, hipStream_t st) {
   want = (want + kPutTile - 1) / kPutTile * kPutTile;
   hipError_t e = hipSuccess;
   if (t->ws_n > 0) {
-    ScratchSet old = current_set(t);
-    if ((e = hipEventCreateWithFlags(&old.done, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipEventRecord(old.done, st)) != hipSuccess) {
-      if (old.done != nullptr) (void)hipEventDestroy(old.done);
-      return hip_fail(e, "retiring scratch");
-    }
-    t->retired.push_back(old);
-    clear_workspace_ptrs(t);
+    if ((e = retire_workspace(t, st)) != hipSuccess) return hip_fail(e, "retiring scratch");
   }
   const int64_t get_tiles = (want + kGetTileMin - 1) / kGetTileMin + t->cus + 1;
   // put tiles are kPutTile keys, or fewer so that every CU gets one
@@ -232,34 +329,34 @@ int ensure_workspace(mlkv_table* t, int64_t n, hipStream_t st) {
   const int64_t slots = std::max<int64_t>(want, put_tiles * kPutTile);
   const uint64_t spill_words = 4ull * (uint64_t)want + 4096;
   const uint64_t rl_entries = 2ull * (uint64_t)want + 64ull * kMaxRanges;
-  if ((e = dev_alloc(&t->newlist, sizeof(NewKey) * ((size_t)slots + kGetTile))) != hipSuccess ||
-      (e = dev_alloc(&t->tile_cnt, sizeof(uint32_t) * (size_t)get_tiles)) != hipSuccess ||
-      (e = dev_alloc(&t->items, sizeof(uint64_t) * (size_t)slots)) != hipSuccess ||
-      (e = dev_alloc(&t->meta, sizeof(uint32_t) * (size_t)kMaxParts * (size_t)put_tiles)) != hipSuccess ||
-      (e = dev_alloc(&t->spill, sizeof(uint64_t) * (size_t)spill_words)) != hipSuccess ||
-      (e = dev_alloc(reinterpret_cast<char**>(&t->units), unit_bytes(want))) != hipSuccess ||
-      // radix counts: 2^kRsMaxBits digit rows of (radix tiles rounded up to 4), then the item total
-      (e = dev_alloc(&t->rs_cnt, sizeof(uint32_t) * (((size_t)(put_tiles + 3) / 4 + 4) * (1u << kRsMaxBits) + 64))) !=
-          hipSuccess ||
-      (e = dev_alloc(&t->partials, sizeof(double) * (size_t)want * (size_t)t->dim)) != hipSuccess ||
-      (e = dev_alloc(&t->pc_key, sizeof(uint64_t) * (size_t)slots)) != hipSuccess ||
-      (e = dev_alloc(&t->pc_row, sizeof(uint32_t) * (size_t)slots)) != hipSuccess ||
-      (e = dev_alloc(&t->mid_xkey, sizeof(uint64_t) * (size_t)slots)) != hipSuccess ||
-      (e = dev_alloc(&t->mid_xslot, sizeof(uint32_t) * (size_t)slots)) != hipSuccess ||
-      // range lists: twice the keys in all, so that a range may hold twice its share
-      (e = dev_alloc(&t->rl_list, sizeof(NewKey) * rl_entries)) != hipSuccess ||
-      (e = dev_alloc(&t->rl_cnt, sizeof(uint32_t) * (2 * kMaxRanges + 1))) != hipSuccess ||
-      (e = dev_alloc(&t->rl_cuts, sizeof(uint64_t) * kMaxRanges)) != hipSuccess ||
+  Arrays a;
+  a.add(&t->newlist, sizeof(NewKey) * ((size_t)slots + kGetTile));
+  a.add(&t->tile_cnt, sizeof(uint32_t) * (size_t)get_tiles);
+  a.add(&t->items, sizeof(uint64_t) * (size_t)slots);
+  a.add(&t->meta, sizeof(uint32_t) * (size_t)kMaxParts * (size_t)put_tiles);
+  a.add(&t->spill, sizeof(uint64_t) * (size_t)spill_words);
+  a.add(&t->units, unit_bytes(want));
+  // radix counts: 2^kRsMaxBits digit rows of (radix tiles rounded up to 4), then the item total
+  a.add(&t->rs_cnt, sizeof(uint32_t) * (((size_t)(put_tiles + 3) / 4 + 4) * (1u << kRsMaxBits) + 64));
+  a.add(&t->partials, sizeof(double) * (size_t)want * (size_t)t->dim);
+  a.add(&t->pc_key, sizeof(uint64_t) * (size_t)slots);
+  a.add(&t->pc_row, sizeof(uint32_t) * (size_t)slots);
+  a.add(&t->mid_xkey, sizeof(uint64_t) * (size_t)slots);
+  a.add(&t->mid_xslot, sizeof(uint32_t) * (size_t)slots);
+  // range lists: twice the keys in all, so that a range may hold twice its share
+  a.add(&t->rl_list, sizeof(NewKey) * rl_entries);
+  a.add(&t->rl_cnt, sizeof(uint32_t) * (2 * kMaxRanges + 1));
+  a.add(&t->rl_cuts, sizeof(uint64_t) * kMaxRanges);
+  if (t->cache_rows > 0) {
+    a.add(&t->miss, sizeof(uint32_t) * (size_t)want);
+    a.add(&t->plan_slot, sizeof(uint32_t) * (size_t)want);
+  }
+  if ((e = a.alloc(&t->scratch, &t->scratch_bytes)) != hipSuccess ||
       (e = hipMemsetAsync(t->rl_cnt, 0, sizeof(uint32_t) * (2 * kMaxRanges + 1), st)) != hipSuccess ||
       (e = hipMemsetAsync(t->pc_key, 0xFF, sizeof(uint64_t) * (size_t)slots, st)) != hipSuccess) {  // no key cached
-    free_workspace(t);
+    (void)hipFree(t->scratch);  // (waits for a memset that was queued)
+    clear_workspace_ptrs(t);
     return hip_fail(e, "scratch allocation");
-  }
-  if (t->cache_rows > 0 &&
-      ((e = dev_alloc(&t->miss, sizeof(uint32_t) * (size_t)want)) != hipSuccess ||
-       (e = dev_alloc(&t->plan_slot, sizeof(uint32_t) * (size_t)want)) != hipSuccess)) {
-    free_workspace(t);
-    return hip_fail(e, "lookahead scratch allocation");
   }
   t->ws_n = want;
   t->spill_words = spill_words;
@@ -379,10 +476,12 @@ mlkv_table* open_table(int32_t dim, int64_t capacity, uint64_t seed, float max_l
   t->cus = std::max(1, t->cus);
   t->cache_rows = cache_rows;
   const int64_t hbm_rows = cache_rows > 0 ? cache_rows : capacity;
-  if ((e = dev_alloc(&t->idx, sizeof(Bucket) * t->nb)) != hipSuccess ||
-      (e = dev_alloc(&t->rows, sizeof(float) * (size_t)hbm_rows * (size_t)dim)) != hipSuccess ||
-      (e = dev_alloc(&t->state, sizeof(float) * (size_t)capacity)) != hipSuccess ||
-      (e = dev_alloc(&t->ctrl, sizeof(Ctrl))) != hipSuccess) {
+  Arrays a;
+  a.add(&t->idx, sizeof(Bucket) * t->nb);
+  a.add(&t->rows, sizeof(float) * (size_t)hbm_rows * (size_t)dim);
+  a.add(&t->state, sizeof(float) * (size_t)capacity);
+  a.add(&t->ctrl, sizeof(Ctrl));
+  if ((e = a.alloc(&t->memory, &t->memory_bytes)) != hipSuccess) {
     hip_fail(e, "table allocation");
     mlkv_close(t);
     return nullptr;
@@ -471,15 +570,10 @@ void mlkv_close(mlkv_table* t) {
   (void)release_retired(t);
   free_workspace(t);
   prof_release(t);
-  (void)hipFree(t->idx);
-  (void)hipFree(t->rows);
-  (void)hipFree(t->state);
-  (void)hipFree(t->ctrl);
-  (void)hipFree(t->clock);
-  (void)hipFree(t->slot_of_row);
-  (void)hipFree(t->row_of_slot);
-  (void)hipFree(t->dirty);
-  (void)hipFree(t->keep);
+  pool_give(t->device, t->memory, t->memory_bytes);
+  for (void* p : {(void*)t->clock, (void*)t->slot_of_row,
+                  (void*)t->row_of_slot, (void*)t->dirty, (void*)t->keep})
+    if (p != nullptr) (void)hipFree(p);
   if (t->host_alloc != nullptr) (void)hipHostFree(t->host_alloc);
   delete t;
 }
@@ -786,7 +880,8 @@ int put_call(mlkv_table* t, const uint64_t* d_keys, const float* src, int64_t n,
   int rc = check_table(t);
   if (rc) return rc;
   if ((rc = check_put(t, d_keys, src, n, op, lr, eps)) != MLKV_OK || n == 0) return rc;
-  if ((rc = ensure_workspace(t, n, static_cast<hipStream_t>(hip_stream))) != MLKV_OK) return rc;
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if ((rc = ensure_workspace(t, n, st)) != MLKV_OK) return rc;
   const PutArgs a = put_args(t, d_keys, src, n, op, lr, eps);
   hipError_t e = launch_put(a, static_cast<hipStream_t>(hip_stream), hook_of(t));
   if (e != hipSuccess) return hip_fail(e, "put launch");
