@@ -310,7 +310,12 @@ constexpr int kAssignMine = 2048;  // list entries a block ranks directly at a t
 // direct ranking is otherwise used up to kAssignDirectWork new
 // keys x tile chunks.
 constexpr uint64_t kAssignDirectWork = 768;
-constexpr int kRangeSamples = 2048;  // sample of the new keys that splits the key space among the blocks
+// Sample of the new keys that splits the key space among the blocks: the more
+// of them, the fewer ranges outgrow kRangeCap, which are ranked in chunks. A
+// put's blocks of 1024 threads sort 4096 as fast as a get's of 512 sort 2048 (a
+// million rows loaded: 2.8 ms with 2048, 1.95 with 4096).
+template <int NT>
+constexpr int kRangeSamples = NT >= 1024 ? 4096 : 2048;
 constexpr int kRangeCap = 3072;      // keys of a block's key range ranked in LDS at once
 
 // Each tile's list of new keys is sorted (ascending key). For the key range
@@ -530,7 +535,9 @@ __device__ __forceinline__ uint64_t sample_at(uint64_t k, uint64_t M, uint32_t S
 // LDS of a block that assigns rows (NT threads).
 template <int NT>
 struct AssignLds {
-  uint64_t buf[kChunk + 2 * kAssignMine];  // 48 KiB; the two ranking methods lay it out differently
+  // 48 or 64 KiB; the two ranking methods lay it out differently
+  static constexpr int kBuf = std::max(kChunk + 2 * kAssignMine, std::max(2 * kRangeSamples<NT>, kRangeCap * 14 / 8));
+  uint64_t buf[kBuf];
   unsigned long long w64[NT / 64];
   uint64_t cut[2];
   __align__(16) uint32_t pref[NT + 1];
@@ -561,9 +568,9 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
   uint32_t& s_nc = lds.nc;
   uint64_t* const s_cut = lds.cut;
   uint64_t* const s_buf = lds.buf;
-  constexpr int kSortPT = kRangeSamples / NT;
-  static_assert(kRangeCap * 14 <= (int)sizeof(lds.buf) && kRangeSamples * 16 <= (int)sizeof(lds.buf), "LDS");
-  static_assert(kRangeSamples == NT * kSortPT && kRangeCap <= 65536 && kRangeCap % NT == 0, "sample and range sizes");
+  constexpr int kSortPT = kRangeSamples<NT> / NT;
+  static_assert(kRangeCap * 14 <= (int)sizeof(lds.buf) && kRangeSamples<NT> * 16 <= (int)sizeof(lds.buf), "LDS");
+  static_assert(kRangeSamples<NT> == NT * kSortPT && kRangeCap <= 65536 && kRangeCap % NT == 0, "sample and range sizes");
   if (M == 0) return;
 
   if (err) {  // undo this call's insertions: the index returns to its state before the call
@@ -611,7 +618,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
         }
       __syncthreads();
     } else {
-      constexpr uint32_t S = kRangeSamples;
+      constexpr uint32_t S = kRangeSamples<NT>;
       uint32_t* s_sat = reinterpret_cast<uint32_t*>(s_buf + S);     // [S] offsets of the samples in the lists
       {
         const int tpt = (ntiles + NT - 1) / NT;  // consecutive tiles per thread
@@ -2879,6 +2886,27 @@ hipError_t launch_read_rows(const RowStore& store, const float* state, int D, co
   return hipGetLastError();
 }
 
+// A long contiguous copy (rows 0 .. nrows-1 of a table in HBM), kFlatUnits
+// accesses of 16 bytes a thread, around the caches: bound by HBM. One float a
+// thread with a 64-bit division each (below, for tiered tables) took 238 us for
+// 2M rows of dim 64.
+constexpr int kFlatUnits = 4;
+__global__ __launch_bounds__(256) void k_copy_flat(const float* __restrict__ src, float* __restrict__ dst,
+                                                   uint64_t n) {
+  const uint64_t b = (uint64_t)blockIdx.x * (256 * kFlatUnits) + threadIdx.x;
+  const uint64_t n4 = n / 4;
+  for (uint64_t base = b; base < n4; base += (uint64_t)gridDim.x * (256 * kFlatUnits)) {
+    Words4 v[kFlatUnits];
+#pragma unroll
+    for (int u = 0; u < kFlatUnits; ++u)
+      if (base + u * 256 < n4) v[u] = __builtin_nontemporal_load(reinterpret_cast<const Words4*>(src) + base + u * 256);
+#pragma unroll
+    for (int u = 0; u < kFlatUnits; ++u)
+      if (base + u * 256 < n4) __builtin_nontemporal_store(v[u], reinterpret_cast<Words4*>(dst) + base + u * 256);
+  }
+  if (b < n - 4 * n4) dst[4 * n4 + b] = src[4 * n4 + b];
+}
+
 // Rows 0 .. nrows-1 in order, from wherever each lives.
 __global__ __launch_bounds__(256) void k_export_rows(const RowStore store, int64_t nrows, int D,
                                                      float* __restrict__ out) {
@@ -2892,6 +2920,12 @@ __global__ __launch_bounds__(256) void k_export_rows(const RowStore store, int64
 hipError_t launch_export_rows(const RowStore& store, int64_t nrows, int D, float* out, hipStream_t st) {
   const uint64_t total = (uint64_t)nrows * (uint64_t)D;
   if (total == 0) return hipSuccess;
+  if (store.slot == nullptr) {
+    const uint64_t blocks = std::min<uint64_t>((total / 4 + 256 * kFlatUnits - 1) / (256 * kFlatUnits), 1u << 22);
+    hipLaunchKernelGGL(k_copy_flat, dim3((unsigned)std::max<uint64_t>(blocks, 1)), dim3(256), 0, st, store.rows, out,
+                       total);
+    return hipGetLastError();
+  }
   const uint64_t grid = std::min<uint64_t>((total + 255) / 256, 65536);
   hipLaunchKernelGGL(k_export_rows, dim3((unsigned)grid), dim3(256), 0, st, store, nrows, D, out);
   return hipGetLastError();
