@@ -240,14 +240,24 @@ int64_t mlkv_num_slots(mlkv_table *t);
  * 2^31 - 1), so that later calls of at most n keys allocate nothing. A call
  * larger than any reserved or seen before grows the scratch itself: it
  * allocates device memory (hipMalloc) but does not wait for the device; the
- * replaced buffers are freed by the next mlkv_sync, mlkv_reserve or
- * mlkv_close once the work queued before the replacement has finished. This
+ * replaced buffers are released by the next mlkv_sync, mlkv_reserve or
+ * mlkv_close once the work queued before the replacement has finished (freed,
+ * or kept for the next table, see mlkv_close). This
  * call synchronizes the device. Not part of the paper's interface: a setup
  * call for callers that want no allocation on the path of their steps. */
 int mlkv_reserve(mlkv_table *t, int64_t n);
 
-/* Releases the table and all of its device memory (synchronizes the device). */
+/* Releases the table (synchronizes the device). Its device memory is freed,
+ * except that up to 256 MiB per process, of closed tables and of replaced
+ * scratch (mlkv_sync, mlkv_reserve), stay allocated for the tables opened
+ * next. They are freed by mlkv_trim, and before any call of this library
+ * fails for want of device memory. */
 void mlkv_close(mlkv_table *t);
+
+/* Frees the device memory kept from closed tables and replaced scratch (see
+ * mlkv_close); returns the bytes freed. For programs that leave all device
+ * memory to others once their tables are closed. No table is affected. */
+int64_t mlkv_trim(void);
 
 /* Thread-local text of the last error reported by this library. */
 const char *mlkv_last_error(void);

@@ -11,6 +11,7 @@
 
 #include "mlkv.h"
 #include "mlkv_kernels.h"
+#include "mlkv_pool.h"
 
 using namespace mlkv;
 
@@ -117,77 +118,16 @@ int hip_fail(hipError_t e, const char* what) {
   return e == hipErrorOutOfMemory ? MLKV_ENOMEM : MLKV_EDEVICE;
 }
 
+// The process's kept memory. Never destroyed: a table may be closed while the
+// process ends.
+DevicePool& pool() {
+  static DevicePool* p = new DevicePool;
+  return *p;
+}
+
 template <class T>
 hipError_t dev_alloc(T** p, size_t bytes) {
-  *p = nullptr;
-  if (bytes == 0) bytes = 256;
-  return hipMalloc(reinterpret_cast<void**>(p), bytes);
-}
-
-// Released table memory, kept for the next table: a program that opens and
-// closes tables otherwise pays the driver for mapping (and clearing) it each
-// time, 0.3 to 8 ms for 200 MB, varying within a process. At most kPoolBytes
-// in all; the oldest blocks go first, and all of them go before an allocation
-// is reported as failed. A block comes back only once nothing on the device
-// uses it, and is taken under the lock, so any thread and stream may have it.
-constexpr size_t kPoolBytes = 256ull << 20;
-struct PoolBlock {
-  int device;
-  void* ptr;
-  size_t bytes;
-};
-std::mutex g_pool_mu;
-std::vector<PoolBlock> g_pool;  // oldest first
-size_t g_pool_bytes = 0;
-
-// Frees the oldest kept blocks until at most `keep` bytes remain (g_pool_mu held).
-void pool_trim(size_t keep) {
-  while (g_pool_bytes > keep) {
-    (void)hipFree(g_pool.front().ptr);
-    g_pool_bytes -= g_pool.front().bytes;
-    g_pool.erase(g_pool.begin());
-  }
-}
-
-// Memory for `*bytes` on the current device: a kept block at most a quarter
-// larger (*bytes becomes its size), else a new allocation.
-hipError_t pool_take(void** p, size_t* bytes) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> lock(g_pool_mu);
-  size_t best = g_pool.size();
-  for (size_t k = 0; k < g_pool.size(); ++k)
-    if (g_pool[k].device == dev && g_pool[k].bytes >= *bytes && g_pool[k].bytes <= *bytes + *bytes / 4 &&
-        (best == g_pool.size() || g_pool[k].bytes < g_pool[best].bytes))
-      best = k;
-  if (best < g_pool.size()) {
-    *p = g_pool[best].ptr;
-    *bytes = g_pool[best].bytes;
-    g_pool_bytes -= *bytes;
-    g_pool.erase(g_pool.begin() + (ptrdiff_t)best);
-    return hipSuccess;
-  }
-  e = dev_alloc(p, *bytes);
-  if (e == hipErrorOutOfMemory && !g_pool.empty()) {
-    (void)hipGetLastError();
-    pool_trim(0);
-    e = dev_alloc(p, *bytes);
-  }
-  return e;
-}
-
-// Gives back a block of pool_take that no queued work uses any more.
-void pool_give(int device, void* p, size_t bytes) {
-  if (p == nullptr) return;
-  if (bytes > kPoolBytes) {
-    (void)hipFree(p);
-    return;
-  }
-  std::lock_guard<std::mutex> lock(g_pool_mu);
-  pool_trim(kPoolBytes - bytes);
-  g_pool.push_back({device, p, bytes});
-  g_pool_bytes += bytes;
+  return pool().alloc(reinterpret_cast<void**>(p), bytes);
 }
 
 // Several arrays in one allocation, each at a multiple of 256 bytes. An
@@ -205,7 +145,7 @@ struct Arrays {
     *base = nullptr;
     *bytes = 0;
     for (auto& a : list) *bytes += a.second;
-    hipError_t e = pool_take(base, bytes);
+    hipError_t e = pool().take(base, bytes);
     if (e != hipSuccess) return e;
     char* at = static_cast<char*>(*base);
     for (auto& a : list) {
@@ -243,7 +183,7 @@ void clear_workspace_ptrs(mlkv_table* t) {
 
 // Releases the scratch (no queued work uses it).
 void free_workspace(mlkv_table* t) {
-  pool_give(t->device, t->scratch, t->scratch_bytes);
+  pool().give(t->device, t->scratch, t->scratch_bytes);
   clear_workspace_ptrs(t);
 }
 
@@ -272,7 +212,7 @@ int release_retired(mlkv_table* t) {
     hipError_t e = hipEventSynchronize(r.done);
     if (e != hipSuccess && rc == MLKV_OK) rc = hip_fail(e, "hipEventSynchronize");
     (void)hipEventDestroy(r.done);
-    if (e == hipSuccess) pool_give(t->device, r.ptr, r.bytes);
+    if (e == hipSuccess) pool().give(t->device, r.ptr, r.bytes);
     else (void)hipFree(r.ptr);
   }
   t->retired.clear();
@@ -570,13 +510,15 @@ void mlkv_close(mlkv_table* t) {
   (void)release_retired(t);
   free_workspace(t);
   prof_release(t);
-  pool_give(t->device, t->memory, t->memory_bytes);
+  pool().give(t->device, t->memory, t->memory_bytes);
   for (void* p : {(void*)t->clock, (void*)t->slot_of_row,
                   (void*)t->row_of_slot, (void*)t->dirty, (void*)t->keep})
     if (p != nullptr) (void)hipFree(p);
   if (t->host_alloc != nullptr) (void)hipHostFree(t->host_alloc);
   delete t;
 }
+
+int64_t mlkv_trim(void) { return (int64_t)pool().trim(); }
 
 }  // extern "C"
 

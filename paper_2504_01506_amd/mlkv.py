@@ -64,6 +64,7 @@ def load() -> ctypes.CDLL:
         "mlkv_reserve": (INT, [P, I64]),
         "mlkv_set_dedup": (INT, [P, INT]),
         "mlkv_close": (None, [P]),
+        "mlkv_trim": (I64, []),
         "mlkv_last_error": (ctypes.c_char_p, []),
         "mlkv_lookup_rows": (INT, [P, P, I64, P, P]),
         "mlkv_export": (INT, [P, I64, P, P, P, P, P]),
@@ -216,6 +217,11 @@ def mlkv_set_dedup(t: int, mode: int) -> int:
 
 def mlkv_close(t: int) -> None:
     load().mlkv_close(t)
+
+
+def mlkv_trim() -> int:
+    """Frees the device memory kept from closed tables; returns the bytes freed."""
+    return load().mlkv_trim()
 
 
 def mlkv_last_error() -> str:

@@ -39,6 +39,36 @@ def test_tables_reopened_on_released_memory(dim):
         _life(k, 5000, dim, bound=1 if k == 2 else None)
 
 
+def test_closed_tables_memory_is_kept_bounded_and_given_back():
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    def life(rows):
+        t = mlkv.Table(64, rows)
+        t.reserve(1000)
+        held = free()
+        t.close()
+        return held
+
+    slack = 16 << 20  # the driver's granularity, and what other code of the process allocates meanwhile
+    mlkv.mlkv_trim()
+    assert mlkv.mlkv_trim() == 0
+    base = free()
+    held = life(200_000)  # 51 MB of rows, 8 of index, and the scratch
+    kept = base - free()
+    assert 0 < kept <= (256 << 20) + slack
+    assert free() < base - (40 << 20), "the table's memory was not kept"
+    assert abs(life(200_000) - held) <= slack, "an equal table did not take the kept memory"
+    for rows in (300_000, 400_000, 500_000, 600_000, 700_000):
+        life(rows)
+        assert base - free() <= (256 << 20) + slack
+    given = mlkv.mlkv_trim()
+    assert 0 < given <= 256 << 20
+    assert mlkv.mlkv_trim() == 0 and abs(base - free()) <= slack
+    log(f"[reopen] kept {kept >> 20} MiB, given back {given >> 20} MiB")
+
+
 def test_tables_opened_and_closed_from_several_threads():
     errors = []
 
