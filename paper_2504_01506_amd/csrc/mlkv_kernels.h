@@ -189,6 +189,7 @@ struct PutGroupArgs {
   const uint64_t* items;
   const uint32_t* meta;
   int ntiles;
+  uint32_t parts;  // partitions
   PutUnits units;
   Ctrl* ctrl;
   uint64_t epoch;

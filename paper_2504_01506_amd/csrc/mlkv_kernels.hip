@@ -302,14 +302,18 @@ __device__ __forceinline__ int call_verdict(Ctrl* ctrl, uint64_t epoch, uint64_t
 constexpr int kAssignThreads = 512;
 constexpr int kAssignMine = 2048;  // list entries a block ranks directly at a time
 // With few new keys each block ranks its tiles' keys against all of them,
-// streamed through LDS once per 256 tiles of the call: about 13 us plus 44 ns
-// per (new key x 256 tiles) on MI355X (55 us at 256 new keys of a 213k-key,
-// 832-tile batch; 1.4 ms at 8192), while key ranges take 44-50 us from a few
-// hundred keys up when each block must search every tile's list for its
-// range, and far less with range lists (those calls always take them). The
-// direct ranking is otherwise used up to kAssignDirectWork new
-// keys x tile chunks.
-constexpr uint64_t kAssignDirectWork = 768;
+// streamed through LDS once per NT tiles of the call; with more, each block
+// ranks the keys of a key range, which costs a put about 50 us to begin with
+// (a sorted sample, a search of every tile's list). A put of 213k keys, 256
+// tiles, that inserts 2,129 of them takes 47 us directly and 84 by range,
+// with 10,649 64 and 89, with 31,948 111 and 102. A get's blocks take their
+// range from range lists where a call of as many ranges came before, which
+// beats the direct ranking sooner (213k keys, 2 times 512 tiles, 425 new: 33
+// us directly, 28 by range; 4096 keys, 614 new: 27 directly, 49 with each
+// tile's keys compared with all others, the earlier direct ranking). Limits
+// in new keys x rounds of NT tiles.
+template <int NT>
+constexpr uint64_t kAssignDirectWork = NT >= 1024 ? 16384 : 768;
 // Sample of the new keys that splits the key space among the blocks: the more
 // of them, the fewer ranges outgrow kRangeCap, which are ranked in chunks. A
 // put's blocks of 1024 threads sort 4096 as fast as a get's of 512 sort 2048 (a
@@ -588,7 +592,7 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
   // the probe kernel filed the new keys by range (RangeLists): ranking them
   // by range then costs little for any number of them
   const bool listed = rl.list != nullptr && ctrl->rl_epoch == epoch && ctrl->rl_overflow_epoch != epoch;
-  if (listed || M * (uint64_t)((ntiles + 255) / 256) > kAssignDirectWork) {
+  if (listed || M * (uint64_t)((ntiles + NT - 1) / NT) > kAssignDirectWork<NT>) {
     // ---- many new keys: key ranges. Block g ranks the new keys of the g-th
     // key range among themselves, after the count of new keys below the
     // range. The probe kernel has filed the keys by range when cut points for
@@ -850,66 +854,90 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
     return;
   }
 
-  // ---- few new keys: this block owns the tiles t = blockIdx.x (mod
-  // a.blocks); it takes them kAssignBatch at a time (thread j holds entry j
-  // of each tile) and ranks their keys against all M new keys of the call.
-  uint64_t* s_chunk = s_buf;                                              // [kChunk]
-  uint64_t* s_key = s_buf + kChunk;                                       // [kAssignMine]
-  uint32_t* s_slot = reinterpret_cast<uint32_t*>(s_key + kAssignMine);    // [kAssignMine]
-  uint32_t* s_rank = s_slot + kAssignMine;                                // [kAssignMine]
-  constexpr int kAssignBatch = kAssignMine / NT;
-  constexpr int kTilesAt = kAssignMine / TM;  // tiles taken at a time, TM entries each
-  for (int tb = blockIdx.x; tb < ntiles; tb += a.blocks * kTilesAt) {
-    uint32_t have = 0;
+  // ---- few new keys: this block owns those of the tiles t = blockIdx.x (mod
+  // a.blocks), whatever number of tiles that is. It sorts them, kAssignMine at
+  // a time, and counts every new key of the call at the first of them above it
+  // (a search in LDS); the prefix sums of the counts are their ranks.
+  constexpr int PER = kAssignMine / NT;
+  static_assert(kChunk >= kAssignMine && kAssignMine % NT == 0, "the own keys take the chunk's place");
+  uint64_t* s_chunk = s_buf;                                                   // [kChunk], then the own keys
+  uint64_t* s_sorted = s_buf + kChunk;                                        // [kAssignMine]
+  uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_sorted + kAssignMine);      // [kAssignMine]
+  uint32_t* s_rank = s_cnt + kAssignMine;                                     // [kAssignMine]
+  const int g = (int)blockIdx.x, G = (int)a.blocks;
+  const int own = g < ntiles ? (ntiles - 1 - g) / G + 1 : 0;
+  for (int o0 = 0; o0 < own; o0 += NT) {
+    const int no = min(NT, own - o0);
+    for (uint32_t k0 = 0;; k0 += kAssignMine) {
+      const uint32_t c = (int)threadIdx.x < no ? tile_cnt[g + (o0 + (int)threadIdx.x) * G] : 0u;
+      uint32_t total;
+      const uint32_t pre = block_exclusive_scan<NT>(c, s_w, &total);
+      if (k0 >= total) break;  // (block-uniform)
+      const uint32_t m = min((uint32_t)kAssignMine, total - k0);
+      uint32_t P2 = 1;
+      while (P2 < m) P2 <<= 1;
+      s_pref[threadIdx.x] = pre;
+      __syncthreads();
+      uint64_t mk[PER];
+      uint32_t ms[PER];
 #pragma unroll
-    for (int b = 0; b < kAssignBatch; ++b) {
-      const int m = b * NT + (int)threadIdx.x;
-      const int t = tb + m / TM * (int)a.blocks;
-      const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      const uint32_t j = m % TM;
-      if (j < c) {
-        const NewKey nk = newlist[(size_t)t * tile_size + j];
-        s_key[m] = nk.key;
-        s_slot[m] = nk.slot;
-        have = 1;
-      } else {
-        s_slot[m] = kPendingRow;  // marks an unused entry
+      for (int u = 0; u < PER; ++u) {
+        const uint32_t j = threadIdx.x + u * NT;
+        mk[u] = kEmptyKey;
+        ms[u] = 0;
+        if (j < m) {
+          int lo = 0, hi = no - 1;
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_pref[mid] <= k0 + j) lo = mid;
+            else hi = mid - 1;
+          }
+          const NewKey nk = newlist[(size_t)(g + (o0 + lo) * G) * tile_size + (k0 + j - s_pref[lo])];
+          mk[u] = nk.key;
+          ms[u] = nk.slot;
+        }
+        if (j < P2) s_sorted[j] = mk[u];
+        s_cnt[j] = 0;
       }
-      s_rank[m] = 0;
-    }
-    if (block_sum_u64<NT>(have, s_w64) == 0) continue;
-    for_each_new_key_chunk<NT>(newlist, tile_cnt, ntiles, tile_size, s_pref, s_w, s_chunk,
-                               [&](const uint64_t* ck, uint32_t cnt) {
+      __syncthreads();
+      block_bitonic_sort<NT>(s_sorted, P2);
+      auto not_above = [&](uint64_t key) {  // own keys <= key
+        uint32_t x = 0;
+        for (uint32_t step = P2; step >= 1; step >>= 1)
+          if (x + step <= m && s_sorted[x + step - 1] <= key) x += step;
+        return x;
+      };
+      for_each_new_key_chunk<NT>(newlist, tile_cnt, ntiles, tile_size, s_pref, s_w, s_chunk,
+                                 [&](const uint64_t* ck, uint32_t cnt) {
+                                   for (uint32_t e = threadIdx.x; e < cnt; e += NT) {
+                                     const uint32_t x = not_above(ck[e]);
+                                     if (x < m) atomicAdd(&s_cnt[x], 1u);
+                                   }
+                                 });
+      uint32_t v[PER], sum = 0, tot;
 #pragma unroll
-                                 for (int b = 0; b < kAssignBatch; ++b) {
-                                   const int m = b * NT + (int)threadIdx.x;
-                                   if (s_slot[m] == kPendingRow) continue;
-                                   const uint64_t mk = s_key[m];
-                                   uint32_t r = 0;
-                                   for (uint32_t e = 0; e < cnt; ++e) r += ck[e] < mk ? 1u : 0u;
-                                   s_rank[m] += r;
-                                 }
-                               });
+      for (int u = 0; u < PER; ++u) sum += v[u] = s_cnt[threadIdx.x * PER + u];
+      uint32_t acc = block_exclusive_scan<NT>(sum, s_w, &tot);
 #pragma unroll
-    for (int b = 0; b < kAssignBatch; ++b) {
-      const int m = b * NT + (int)threadIdx.x;
-      const uint32_t slot = s_slot[m];
-      if (slot == kPendingRow) continue;
-      const uint32_t row = (uint32_t)(size0 + s_rank[m]);
-      idx[slot / kSlots].row[slot % kSlots] = row;
-      state[row] = 0.0f;
-      if (clock != nullptr) clock[row] = new_row_clock(cepoch);
-      if (a.values != nullptr) s_key[m] = take_position(idx, slot);
+      for (int u = 0; u < PER; ++u) s_cnt[threadIdx.x * PER + u] = acc += v[u];
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const uint32_t j = threadIdx.x + u * NT;
+        if (j >= m) continue;
+        const uint32_t r = s_cnt[not_above(mk[u]) - 1];
+        const uint32_t row = (uint32_t)(size0 + r);
+        idx[ms[u] / kSlots].row[ms[u] % kSlots] = row;
+        state[row] = 0.0f;
+        if (clock != nullptr) clock[row] = new_row_clock(cepoch);
+        s_chunk[j] = a.values != nullptr ? take_position(idx, ms[u]) : mk[u];
+        s_rank[j] = r;
+      }
+      __syncthreads();
+      if (a.values != nullptr) write_value_rows<NT>(s_chunk, s_rank, m, size0, store, D, a.values);
+      else write_init_rows<NT>(s_chunk, s_rank, m, size0, store, D, seed);
+      __syncthreads();
     }
-    if (a.values != nullptr) __syncthreads();
-    // initial or value rows, a wave per row
-    for (int b = 0; b < kTilesAt; ++b) {
-      const int t = tb + b * (int)a.blocks;
-      const uint32_t c = t < ntiles ? tile_cnt[t] : 0u;
-      if (a.values != nullptr) write_value_rows<NT>(s_key + b * TM, s_rank + b * TM, c, size0, store, D, a.values);
-      else write_init_rows<NT>(s_key + b * TM, s_rank + b * TM, c, size0, store, D, seed);
-    }
-    __syncthreads();
   }
 }
 
@@ -2026,11 +2054,12 @@ __global__ __launch_bounds__(kGroupThreads, 8) void k_put_group(const PutGroupAr
   const int tid = threadIdx.x, ntiles = a.ntiles;
   const uint32_t* pm = a.meta + (size_t)p * ntiles;
   const bool one_chunk = ntiles <= NT;  // common case: one thread per tile
-  const uint32_t mt0 = one_chunk && tid < ntiles ? pm[tid] : 0u;
+  const uint32_t mt0 = one_chunk && p < a.parts && tid < ntiles ? pm[tid] : 0u;
 
-  // entries of this partition in every tile
-  uint32_t mp, pre0 = 0;
-  if (one_chunk) {
+  // entries of this partition in every tile (blocks past the partitions only assign rows)
+  uint32_t mp = 0, pre0 = 0;
+  if (p >= a.parts) {
+  } else if (one_chunk) {
     pre0 = block_exclusive_scan<NT>(mt0 >> 16, s_w, &mp);
   } else {
     uint64_t mp64 = 0;
@@ -2791,6 +2820,10 @@ static hipError_t launch_radix_sort(const PutArgs& a, hipStream_t st, const Laun
   return hipSuccess;
 }
 
+// Blocks of a hash put's grouping kernel at least, so that a few partitions'
+// new keys are ranked and written by more.
+constexpr int64_t kAssignBlocks = 32;
+
 hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, int phase) {
   const bool radix = a.dedup == kDedupRadix;
   const int64_t ntiles = (a.n + a.tlen - 1) / a.tlen;
@@ -2835,7 +2868,9 @@ hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, 
   const uint32_t* total = nullptr;
   // blocks: one per partition, or (radix) one per CU at least, at most kRsChunk
   // sorted items each before the cuts move
-  const int64_t nb = radix ? std::max<int64_t>(a.cus, (a.n + kRsChunk - 1) / kRsChunk) : (int64_t)1 << a.pb;
+  const int64_t nb = radix ? std::max<int64_t>(a.cus, (a.n + kRsChunk - 1) / kRsChunk)
+                           : std::max<int64_t>((int64_t)1 << a.pb, std::min<int64_t>(ntiles, kAssignBlocks));
+  g.parts = 1u << a.pb;
   if (radix && (e = launch_radix_sort(a, st, hook, &g.items, &total)) != hipSuccess) return e;
   s.blocks = (uint32_t)std::min<int64_t>(nb, kMaxRanges);
   const int timed = radix ? K_RSORT_REDUCE : K_PUT_REDUCE;  // the grouping and the updates, timed as one
