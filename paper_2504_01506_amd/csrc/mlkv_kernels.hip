@@ -86,18 +86,54 @@ __device__ __forceinline__ typename VecT<VEC>::T init_vec(uint64_t s0, int col) 
 }
 
 #ifndef MLKV_MAP
+// Copies the rows of a wave's 64 positions (`first` on) into `out`, LPR lanes a
+// row, every load of a lane in flight at once: row is the lane's own
+// position's row, kPendingRow for a key new in the call (its row is generated
+// from s0), kNoCopy for a position to leave alone. out's rows may start at any
+// 4-byte boundary.
+constexpr uint32_t kNoCopy = kPendingRow - 1;  // (no row's number: a capacity is at most 2^32 - 2)
+template <int LPR, bool kStream>
+__device__ __forceinline__ void copy_wave_rows(float* __restrict__ out, const RowStore& store, int64_t first,
+                                               uint32_t row, uint64_t s0) {
+  const int D = store.D, lane = threadIdx.x & 63;
+  const int c = lane % LPR * 4;
+  const bool on = c < D;
+  const int col = c < D - 4 ? c : D - 4;  // the last lane of a row: its last four columns
+  const int g = lane / LPR;
+  float* const o = out + (size_t)first * (size_t)D + col;
+  float4 v[LPR];
+  uint32_t r[LPR];
+#pragma unroll
+  for (int u = 0; u < LPR; ++u) {
+    r[u] = __shfl(row, u * (64 / LPR) + g, 64);
+    if (on && r[u] < kNoCopy) v[u] = load_vec<4>(store.ptr(r[u]) + col);
+  }
+#pragma unroll
+  for (int u = 0; u < LPR; ++u) {
+    if (!on || r[u] >= kNoCopy) continue;
+    float* p = o + (size_t)(u * (64 / LPR) + g) * (size_t)D;
+    if constexpr (kStream) store_vec_nt<4>(p, v[u]);
+    else store_vec<4>(p, v[u]);
+  }
+  if (__ballot(row == kPendingRow ? 1 : 0) == 0) return;
+#pragma unroll 1
+  for (int u = 0; u < LPR; ++u) {
+    const int at = u * (64 / LPR) + g;
+    const uint32_t x = __shfl(row, at, 64);
+    const uint64_t s = __shfl((unsigned long long)s0, at, 64);
+    if (on && x == kPendingRow) store_vec<4>(o + (size_t)at * (size_t)D, init_vec<4>(s, col));
+  }
+}
+
 // Get, first kernel: each position's key is looked up (inserted if missing)
-// and its row left in row[i] (kPendingRow: the key is new in the call); the
-// second kernel copies the rows. Bound by the latency of the dependent loads
-// key -> bucket line, so it carries nothing else: without the row copy it
-// needs half the registers and has twice the waves in flight. Only a row of
-// kNarrowUnits accesses or fewer (VEC > 0) is copied here, by its key's lane:
-// the second kernel's pass over the positions costs more then (two steps of
-// the 2^20-operation key-value mix, rows of 16 bytes: 164 us against 168).
+// and its row left in row[i] (kPendingRow: the key is new in the call). Rows of
+// some widths and batch sizes are copied here too (LPR lanes a row, 1: by the
+// key's own lane; VEC 0: none), the others by the second kernel, see
+// copy_lanes. Bound by the latency of the dependent loads key -> bucket line (->
+// row), so few registers and many waves.
 // kPcIn: a position whose key equals pc_key[i] takes row[i] without
 // probing (an instance of its own, so that other gets run unchanged)
-constexpr uint32_t kNarrowUnits = 1;
-template <int VEC, bool kTrack, bool kPcIn>
+template <int VEC, int LPR, bool kTrack, bool kPcIn, bool kStream>
 __global__ __launch_bounds__(kGetTile) void k_get_probe(
     Bucket* __restrict__ idx, uint32_t nb_log2, const uint64_t* __restrict__ keys, int64_t n,
     float* __restrict__ out, const RowStore store, uint64_t seed, NewKey* __restrict__ newlist, uint32_t* __restrict__ tile_cnt, Ctrl* ctrl, uint64_t epoch,
@@ -172,19 +208,14 @@ __global__ __launch_bounds__(kGetTile) void k_get_probe(
     blocked[i] = blk ? 1 : 0;
     served = !blk;
   }
-  if constexpr (VEC > 0) {
-    if (served) {
-      const int D = store.D;
-      const float* w = pr.status == P_HIT ? store.ptr(pr.row) : nullptr;
-      const uint64_t s0 = splitmix_mix(key ^ seed);
-#pragma unroll
-      for (uint32_t u = 0; u < kNarrowUnits; ++u) {
-        const int c = (int)u * VEC;
-        if (c >= D) break;
-        const int col = VEC == 1 || c < D - VEC ? c : D - VEC;
-        store_vec<VEC>(out + (size_t)i * (size_t)D + col, w != nullptr ? load_vec<VEC>(w + col) : init_vec<VEC>(s0, col));
-      }
-    }
+  if constexpr (LPR > 1) {
+    copy_wave_rows<LPR, kStream>(out, store, base + (tid & ~63),
+                                 !served ? kNoCopy : pr.status == P_HIT ? pr.row : kPendingRow,
+                                 splitmix_mix(key ^ seed));
+  } else if constexpr (VEC > 0) {
+    if (served)  // a row is one access
+      store_vec<VEC>(out + (size_t)i * VEC, pr.status == P_HIT ? load_vec<VEC>(store.ptr(pr.row))
+                                                               : init_vec<VEC>(splitmix_mix(key ^ seed), 0));
   }
   __syncthreads();
   // the tile's list of new keys, in ascending key order (each at its rank)
@@ -293,11 +324,12 @@ __device__ __forceinline__ int call_verdict(Ctrl* ctrl, uint64_t epoch, uint64_t
 }
 
 // ===========================================================================
-// Get, second kernel: the rows of the call's positions are copied out, then
-// its first blocks assign rows to the call's new keys (ascending key order),
-// write their initial rows and zero accumulators; or roll the call back. The
-// copy reads only rows that were present before the call and generates those
-// of new keys from their seed, so neither part waits for the other.
+// Get, second kernel: the rows of the call's positions are copied out (if the
+// first has not), then its first blocks assign rows to the call's new keys
+// (ascending key order), write their initial rows and zero accumulators; or
+// roll the call back. The copy reads only rows that were present before the
+// call and generates those of new keys from their seed, so neither part waits
+// for the other.
 // ===========================================================================
 constexpr int kAssignThreads = 512;
 constexpr int kAssignMine = 2048;  // list entries a block ranks directly at a time
@@ -947,15 +979,11 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
 // end. Rows of keys present before the call are read from the table, rows of
 // keys new in it are generated from their seed (they equal what the table
 // will hold), rows of blocked positions are left alone (kTrack).
-// Bound by HBM. As a part of the probe kernel, where a wave copied the rows of
-// its own 64 positions with 4 to 64 lanes a row, 150k rows of dim 400 took 178
-// us with the probe and 1M of dim 128 took 274; apart they take 11 + 97 and 46
-// + 189 (and dim 64, 213k rows, 12 + 17 against 24, where the launch of the
-// row assignment, 4.8 us, is saved). Two units a thread; four are 4 to 8 %
-// slower at these widths. An output of kStreamOut bytes does not stay in the 32
-// MB of L2 anyway and goes around it (non-temporal), which leaves the caches
-// to the rows and to the kernels that follow: two DLRM steps 199 -> 186 us,
-// two of dim 400 640 -> 595.
+// Bound by HBM (copy_lanes says which gets copy their rows here). Two units a
+// thread; four are 4 to 8 % slower at dims 128 and 400. An output of kStreamOut
+// bytes does not stay in the 32 MB of L2 anyway and goes around it
+// (non-temporal), which leaves the caches to the rows and to the kernels that
+// follow: two DLRM steps 199 -> 186 us, two of dim 400 640 -> 595.
 constexpr int kCopyThreads = kAssignThreads;
 constexpr int kCopyUnits = 2;
 constexpr uint64_t kStreamOut = 32ull << 20;
@@ -2610,11 +2638,32 @@ __global__ __launch_bounds__(256) void k_read_clock(const unsigned long long* __
 // Launchers
 // ===========================================================================
 #ifndef MLKV_MAP
-template <int VEC>
+template <int VEC, int LPR, bool kStream>
 static auto probe_kernel(const GetArgs& a) {
-  return a.clock != nullptr ? k_get_probe<VEC, true, false>
-         : a.pc_in          ? k_get_probe<VEC, false, true>
-                            : k_get_probe<VEC, false, false>;
+  return a.clock != nullptr ? k_get_probe<VEC, LPR, true, false, kStream>
+         : a.pc_in          ? k_get_probe<VEC, LPR, false, true, kStream>
+                            : k_get_probe<VEC, LPR, false, false, kStream>;
+}
+
+// Lanes a row with which the probe kernel copies rows of `units` accesses; 0:
+// the second kernel copies them. Copied with the probe, other waves' lookups
+// hide the row copy's latency and one launch has nothing to copy; apart, the
+// probe has twice the waves in flight and the copy evens out its work. Times of
+// one get in us, copied with the probe / apart, rows drawn uniformly:
+//   dim      16k keys      131k          213k          426k          1M
+//    16     10.2/10.4    15.2/16.1     20.6/23.5     33.4/36.5     68.0/70.4
+//    32     11.0/10.4    17.5/19.2     23.9/26.5     39.8/42.0     84.8/86.4
+//    64     12.8/10.7    23.0/26.2     34.9/36.1     70.6/61.3    149.3/143.3
+// Rows of 5 accesses and more need more keys than one tile a CU, and those of
+// 9 and more, whose kernel has 6 blocks of 256 lanes on a CU (78 registers), no
+// more than these take at once. Wider rows are copied apart: 150k of dim 400 took
+// 178 us with the probe and take 11 + 97, 1M of dim 128 274 and 46 + 189.
+static int copy_lanes(uint64_t units, int64_t n, int cus) {
+  if (units == 1) return 1;
+  if (units <= 4) return 4;
+  if (units > 16 || n <= (int64_t)kGetTile * cus) return 0;
+  if (units <= 8) return 8;
+  return n <= 6 * (int64_t)kGetTile * cus ? 16 : 0;
 }
 
 hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) {
@@ -2625,11 +2674,14 @@ hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) 
   if (rl.list != nullptr) rl.cap = (uint32_t)std::min<uint64_t>(rl.entries / ranges, 0xFFFFFFFFull);
   const int vec = a.D >= 4 ? 4 : 1;
   const uint64_t units = (uint64_t)(a.D + vec - 1) / vec;  // of a row
-  const bool narrow = a.out != nullptr && units <= kNarrowUnits;
+  const int lanes = a.out == nullptr || (vec == 1 && units > 1) ? 0 : copy_lanes(units, a.n, a.cus);
+  const bool stream = (uint64_t)a.n * (uint64_t)a.D * sizeof(float) >= kStreamOut;
   hook(K_GET_PROBE, 0, st);
-  auto kern = !narrow    ? probe_kernel<0>(a)
-              : vec == 4 ? probe_kernel<4>(a)
-                         : probe_kernel<1>(a);
+  auto kern = lanes == 0    ? probe_kernel<0, 0, false>(a)
+              : lanes == 1  ? (vec == 4 ? probe_kernel<4, 1, false>(a) : probe_kernel<1, 1, false>(a))
+              : lanes == 4  ? (stream ? probe_kernel<4, 4, true>(a) : probe_kernel<4, 4, false>(a))
+              : lanes == 8  ? (stream ? probe_kernel<4, 8, true>(a) : probe_kernel<4, 8, false>(a))
+                            : (stream ? probe_kernel<4, 16, true>(a) : probe_kernel<4, 16, false>(a));
   hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(kGetTile), 0, st, a.idx, a.nb_log2, a.keys, a.n, a.out,
                      a.store, a.seed, a.newlist, a.tile_cnt, a.ctrl, a.epoch, a.clock, a.cepoch, a.bound, a.blocked,
                      a.pc_key, a.pos_row, tlen, rl, ranges);
@@ -2637,7 +2689,7 @@ hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const uint64_t per_block = (uint64_t)kCopyThreads * kCopyUnits;
-  const bool copy = a.out != nullptr && !narrow;
+  const bool copy = a.out != nullptr && lanes == 0;
   const uint64_t blocks =
       copy ? std::min<uint64_t>(((uint64_t)a.n * units + per_block - 1) / per_block, kCopyBlocks) : 0;
   GetRowsArgs r;
@@ -2669,7 +2721,6 @@ hipError_t launch_get(const GetArgs& a, hipStream_t st, const LaunchHook& hook) 
   const unsigned grid = (unsigned)std::max<uint64_t>(blocks, ranges);
   const bool track = a.clock != nullptr;
   hook(K_GET_ROWS, 0, st);
-  const bool stream = (uint64_t)a.n * (uint64_t)a.D * sizeof(float) >= kStreamOut;
   auto rows = vec != 4 ? (track ? k_get_rows<1, true, false> : k_get_rows<1, false, false>)
               : stream ? (track ? k_get_rows<4, true, true> : k_get_rows<4, false, true>)
                        : (track ? k_get_rows<4, true, false> : k_get_rows<4, false, false>);
