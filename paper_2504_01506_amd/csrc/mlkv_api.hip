@@ -376,6 +376,59 @@ const char* mlkv_last_error(void) { return g_err.c_str(); }
 
 namespace {
 
+// Per-call scratch of a get held outside the table (the allocation-free
+// entry point): the new-key lists, the per-tile counts, the key-range
+// overflow lists and the positions' rows. Such a get leaves the table's record of found rows alone.
+struct GetScratch {
+  NewKey* newlist;
+  uint32_t* tile_cnt;
+  uint64_t* xkey;
+  uint32_t* xslot;
+  uint32_t* pos_row;
+};
+
+// ---- scratch of the allocation-free get ----
+// A file-scope device array, one copy per GPU, sized for kNoAllocMaxKeys keys:
+// new-key lists (16 B per key), per-tile counts, key-range lists (12 B per key),
+// the positions' rows (4 B per key).
+constexpr int64_t kNoAllocMaxKeys = MLKV_NOALLOC_MAX_KEYS;
+constexpr size_t kNaNewlist = 0;
+// a tile's list starts at its first position; the last tile may reach past n
+constexpr size_t kNaTileCnt = kNaNewlist + sizeof(NewKey) * ((size_t)kNoAllocMaxKeys + kGetTile);
+constexpr size_t kNaXkey = kNaTileCnt + 4096;
+constexpr size_t kNaXslot = kNaXkey + sizeof(uint64_t) * (size_t)kNoAllocMaxKeys;
+constexpr size_t kNaRow = kNaXslot + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
+constexpr size_t kNaBytes = kNaRow + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
+static_assert(kNaTileCnt + sizeof(uint32_t) * ((kNoAllocMaxKeys + kGetTileMin - 1) / kGetTileMin) <= kNaXkey,
+              "tile counts fit their region");
+
+__device__ __align__(256) unsigned char scratch[kNaBytes];
+
+// Device address of `scratch` on each device (the name itself is only a
+// host-side stand-in), taken once per device with that device current.
+std::mutex g_scratch_mu;
+constexpr int kMaxDevices = 64;
+void* g_scratch_addr[kMaxDevices] = {};
+
+int noalloc_scratch(int device, GetScratch* out) {
+  if (device < 0 || device >= kMaxDevices) return fail(MLKV_EDEVICE, "device ordinal out of range");
+  std::lock_guard<std::mutex> lock(g_scratch_mu);
+  if (g_scratch_addr[device] == nullptr) {
+    void* p = nullptr;
+    hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+    if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
+    if (p == nullptr) return fail(MLKV_EDEVICE, "hipGetSymbolAddress(scratch) returned NULL");
+    g_scratch_addr[device] = p;
+  }
+  unsigned char* base = static_cast<unsigned char*>(g_scratch_addr[device]);
+  out->newlist = reinterpret_cast<NewKey*>(base + kNaNewlist);
+  out->tile_cnt = reinterpret_cast<uint32_t*>(base + kNaTileCnt);
+  out->xkey = reinterpret_cast<uint64_t*>(base + kNaXkey);
+  out->xslot = reinterpret_cast<uint32_t*>(base + kNaXslot);
+  out->pos_row = reinterpret_cast<uint32_t*>(base + kNaRow);
+  return MLKV_OK;
+}
+
 // Opens a table; cache_rows > 0 makes it tiered (rows at home in pinned host
 // memory, cache_rows of them in an HBM cache).
 mlkv_table* open_table(int32_t dim, int64_t capacity, uint64_t seed, float max_load, int64_t cache_rows) {
@@ -414,6 +467,13 @@ mlkv_table* open_table(int32_t dim, int64_t capacity, uint64_t seed, float max_l
     return nullptr;
   }
   t->cus = std::max(1, t->cus);
+  GetScratch fixed;  // (its array is part of this file's code)
+  if ((e = load_code(dim)) != hipSuccess || (cache_rows > 0 && (e = load_tier_code()) != hipSuccess)) {
+    hip_fail(e, "loading device code");
+    delete t;
+    return nullptr;
+  }
+  (void)noalloc_scratch(t->device, &fixed);  // (mlkv_get_noalloc reports a failure)
   t->cache_rows = cache_rows;
   const int64_t hbm_rows = cache_rows > 0 ? cache_rows : capacity;
   Arrays a;
@@ -524,17 +584,6 @@ int64_t mlkv_trim(void) { return (int64_t)pool().trim(); }
 
 namespace {
 
-// Per-call scratch of a get held outside the table (the allocation-free
-// entry point): the new-key lists, the per-tile counts, the key-range
-// overflow lists and the positions' rows. Such a get leaves the table's record of found rows alone.
-struct GetScratch {
-  NewKey* newlist;
-  uint32_t* tile_cnt;
-  uint64_t* xkey;
-  uint32_t* xslot;
-  uint32_t* pos_row;
-};
-
 // Host-side checks of a get call's arguments (nothing is queued).
 int check_get(mlkv_table* t, const uint64_t* d_keys, int64_t n, uint8_t* d_blocked, bool count) {
   if (n < 0 || n > 0x7FFFFFFFll) return fail(MLKV_EINVAL, "n must be in [0, 2^31 - 1]");
@@ -618,48 +667,6 @@ int get_call(mlkv_table* t, const uint64_t* d_keys, int64_t n, float* d_out, uin
                             fixed ? LaunchHook{} : hook_of(t));
   if (e != hipSuccess) return hip_fail(e, "mlkv_get launch");
   get_done(t, count, fixed != nullptr);
-  return MLKV_OK;
-}
-
-// ---- scratch of the allocation-free get ----
-// A file-scope device array, one copy per GPU, sized for kNoAllocMaxKeys keys:
-// new-key lists (16 B per key), per-tile counts, key-range lists (12 B per key),
-// the positions' rows (4 B per key).
-constexpr int64_t kNoAllocMaxKeys = MLKV_NOALLOC_MAX_KEYS;
-constexpr size_t kNaNewlist = 0;
-// a tile's list starts at its first position; the last tile may reach past n
-constexpr size_t kNaTileCnt = kNaNewlist + sizeof(NewKey) * ((size_t)kNoAllocMaxKeys + kGetTile);
-constexpr size_t kNaXkey = kNaTileCnt + 4096;
-constexpr size_t kNaXslot = kNaXkey + sizeof(uint64_t) * (size_t)kNoAllocMaxKeys;
-constexpr size_t kNaRow = kNaXslot + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
-constexpr size_t kNaBytes = kNaRow + sizeof(uint32_t) * (size_t)kNoAllocMaxKeys;
-static_assert(kNaTileCnt + sizeof(uint32_t) * ((kNoAllocMaxKeys + kGetTileMin - 1) / kGetTileMin) <= kNaXkey,
-              "tile counts fit their region");
-
-__device__ __align__(256) unsigned char scratch[kNaBytes];
-
-// Device address of `scratch` on each device (the name itself is only a
-// host-side stand-in), taken once per device with that device current.
-std::mutex g_scratch_mu;
-constexpr int kMaxDevices = 64;
-void* g_scratch_addr[kMaxDevices] = {};
-
-int noalloc_scratch(int device, GetScratch* out) {
-  if (device < 0 || device >= kMaxDevices) return fail(MLKV_EDEVICE, "device ordinal out of range");
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (g_scratch_addr[device] == nullptr) {
-    void* p = nullptr;
-    hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return hip_fail(e, "hipGetSymbolAddress(scratch)");
-    if (p == nullptr) return fail(MLKV_EDEVICE, "hipGetSymbolAddress(scratch) returned NULL");
-    g_scratch_addr[device] = p;
-  }
-  unsigned char* base = static_cast<unsigned char*>(g_scratch_addr[device]);
-  out->newlist = reinterpret_cast<NewKey*>(base + kNaNewlist);
-  out->tile_cnt = reinterpret_cast<uint32_t*>(base + kNaTileCnt);
-  out->xkey = reinterpret_cast<uint64_t*>(base + kNaXkey);
-  out->xslot = reinterpret_cast<uint32_t*>(base + kNaXslot);
-  out->pos_row = reinterpret_cast<uint32_t*>(base + kNaRow);
   return MLKV_OK;
 }
 

@@ -317,6 +317,15 @@ struct RsSrc {
 hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits, uint32_t* cnt, int rtiles,
                              int stride, uint64_t* dst, uint32_t* total_out, hipStream_t st,
                              const LaunchHook& hook);
+// Loads the code that tables of dim D run (load_tier_code: of tiered tables) on
+// the current device, where a process has not done so yet. The library has a
+// code object for each row map; the runtime otherwise loads one at the first
+// launch from it: a first put took 0.7 ms instead of 0.1, and one under stream
+// capture would load (and allocate) there.
+hipError_t load_code(int D);
+hipError_t load_tier_code();
+template <class M>
+hipError_t load_map_code();
 template <class M>
 hipError_t launch_put_probe_t(const PutArgs& a, int pb, hipStream_t st, const LaunchHook& hook);
 template <class M>

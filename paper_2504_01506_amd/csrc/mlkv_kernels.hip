@@ -2777,11 +2777,19 @@ hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream
   return hipGetLastError();
 }
 
+template <class M>
+hipError_t load_map_code() {
+  hipFuncAttributes f;
+  return hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_put_apply<M, false>));
+}
+
 #ifdef MLKV_MAP
+template hipError_t load_map_code<MLKV_MAP>();
 template hipError_t launch_put_probe_t<MLKV_MAP>(const PutArgs&, int, hipStream_t, const LaunchHook&);
 template hipError_t launch_put_apply_t<MLKV_MAP>(const PutArgs&, const PutApplyArgs&, hipStream_t);
 #else
 #define MLKV_EXTERN(M)                                                                                   \
+  extern template hipError_t load_map_code<M>();                                                         \
   extern template hipError_t launch_put_probe_t<M>(const PutArgs&, int, hipStream_t, const LaunchHook&); \
   extern template hipError_t launch_put_apply_t<M>(const PutArgs&, const PutApplyArgs&, hipStream_t);
 MLKV_MAPS(MLKV_EXTERN)
@@ -2796,6 +2804,12 @@ static hipError_t dispatch_map(int D, F f) {
   if (D <= 256) return f(MapD256{});
   if (D <= 512) return f(MapD512{});
   return f(MapD1024{});
+}
+
+hipError_t load_code(int D) {
+  hipFuncAttributes f;
+  const hipError_t e = hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_lookup));
+  return e != hipSuccess ? e : dispatch_map(D, [](auto m) { return load_map_code<decltype(m)>(); });
 }
 
 // Lets kernel `f` use `bytes` of dynamic LDS on the current device; `done`

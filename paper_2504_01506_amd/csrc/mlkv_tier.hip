@@ -206,6 +206,11 @@ __global__ __launch_bounds__(kCopyThreads) void k_tier_copy(const uint32_t* __re
   }
 }
 
+hipError_t load_tier_code() {
+  hipFuncAttributes f;
+  return hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_tier_plan));
+}
+
 hipError_t launch_tier_lookahead(const TierArgs& a, hipStream_t st, const LaunchHook& hook) {
   if (a.n == 0) return hipSuccess;
   hook(K_TIER_MARK, 0, st);
