@@ -2201,19 +2201,21 @@ __device__ __forceinline__ void add_raw(double* acc, const RawRow<VEC>& r, bool 
 // units, a block each: its lane groups take the unit's items in turn, and
 // their fp64 sums are added in a fixed order (across the wave's groups, then
 // across waves). Then the other sums, a lane group each, items in order; then
-// the keys seen once, kApplyRows of them a group at a time. Which block takes
-// which unit changes no result.
+// the keys seen once, a lane group each. Which block takes which unit changes
+// no result.
 // Bound by HBM: gradient rows and in-tile sums in, table rows in and out.
 // ---------------------------------------------------------------------------
 constexpr int kApplyThreads = 256;
 template <class M>
 struct ApplyCfg {
   static constexpr int B = (M::K * M::VEC >= 8) ? 2 : 4;       // rows of a sum a group has in flight
-  static constexpr int BS = (M::K * M::VEC >= 8) ? 1 : 2;      // keys seen once it updates at a time
   // gradient rows of 256 bytes and more are read around the caches; shorter
   // ones share their lines with other keys' rows
   static constexpr bool kStream = M::LPR * M::VEC >= 64;
-  static constexpr int WAVES = (M::K * M::VEC >= 16) ? 3 : (M::K * M::VEC >= 8) ? 4 : 5;  // per SIMD
+  // waves per SIMD. Six with a key seen once at a time: two at a time and five
+  // waves took 99 us against 96.5 (a put of 213k uniform keys, dim 128), 603
+  // against 584 (1M, dim 256); eight spill (113 us).
+  static constexpr int WAVES = (M::K * M::VEC >= 16) ? 3 : (M::K * M::VEC >= 8) ? 4 : 6;
 };
 
 template <class M, bool kClk>
@@ -2222,7 +2224,7 @@ __global__ __launch_bounds__(kApplyThreads, ApplyCfg<M>::WAVES) void k_put_apply
   using Ops = SegmentOps<M>;
   constexpr int VEC = M::VEC, LPR = M::LPR, K = M::K, RPW = M::RPW;
   constexpr int NW = kApplyThreads / 64, NG = NW * RPW;
-  constexpr int B = ApplyCfg<M>::B, BS = ApplyCfg<M>::BS, DMAX = LPR * K * VEC;
+  constexpr int B = ApplyCfg<M>::B, DMAX = LPR * K * VEC;
   constexpr bool kStream = ApplyCfg<M>::kStream;
   using V = typename VecT<VEC>::T;
   __shared__ double s_sum[NW][DMAX];
@@ -2342,42 +2344,19 @@ __global__ __launch_bounds__(kApplyThreads, ApplyCfg<M>::WAVES) void k_put_apply
 
   // ---- keys seen once: g is the key's gradient row ----
   const uint32_t ns = (uint32_t)a.ctrl->unit_single;
-  for (uint32_t e0 = g0; e0 < ns; e0 += groups * BS) {
-    V gq[BS][K], ws[BS][K];
-    float Gs[BS];
-    uint32_t rw[BS], cs[BS];
-    float* wr[BS];
+  for (uint32_t e = g0; e < ns; e += groups) {
+    const uint64_t x = a.units.single[e];
+    const uint32_t row = unit_row(a.idx, item_tag(x), item_fresh(x));
+    float* wr = store.wptr(row);
+    const float* gr = a.grads + (size_t)item_pos(x) * (size_t)D;
+    V g[K];
 #pragma unroll
-    for (int u = 0; u < BS; ++u) {
-      const uint32_t e = e0 + u * groups;
-      rw[u] = 0;
-      Gs[u] = 0.0f;
-      cs[u] = 0u;
-      wr[u] = nullptr;
-      if (e < ns) {
-        const uint64_t x = a.units.single[e];
-        rw[u] = unit_row(a.idx, item_tag(x), item_fresh(x));
-        wr[u] = store.wptr(rw[u]);
-        const float* gr = a.grads + (size_t)item_pos(x) * (size_t)D;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int col = M::col(k, q, D);
-          if (M::on(k, q, D)) {
-            gq[u][k] = load_vec_once<VEC, kStream>(gr + col);
-            ws[u][k] = load_vec<VEC>(wr[u] + col);
-          }
-        }
-        if (adagrad) Gs[u] = a.state[rw[u]];
-        if (clk) cs[u] = clock_low(a.clock, rw[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < BS; ++u) {
-      if (wr[u] == nullptr) continue;
-      if (adagrad) Ops::adagrad(gq[u], ws[u], Gs[u], wr[u], a.state, rw[u], D, q, d_pow2, inv_d, a.lr, a.eps);
-      else Ops::sgd(gq[u], ws[u], wr[u], D, q, a.lr);
-      if (clk) put_clock_low(a.clock, rw[u], cs[u]);
-    }
+    for (int k = 0; k < K; ++k)
+      if (M::on(k, q, D)) g[k] = load_vec_once<VEC, kStream>(gr + M::col(k, q, D));
+    load_row(row, wr);
+    if (adagrad) Ops::adagrad(g, w, G, wr, a.state, row, D, q, d_pow2, inv_d, a.lr, a.eps);
+    else Ops::sgd(g, w, wr, D, q, a.lr);
+    if (clk) put_clock_low(a.clock, row, cl);
   }
 }
 
