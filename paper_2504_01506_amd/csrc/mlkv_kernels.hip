@@ -2211,7 +2211,7 @@ __device__ __forceinline__ void add_raw(double* acc, const RawRow<VEC>& r, bool 
 
 // ---------------------------------------------------------------------------
 // Put, third kernel: the update of every unit (Adagrad or SGD). First the long
-// units, a block each: its lane groups take the unit's items in turn, and
+// units, a block each (see lane_max): its lane groups take the unit's items in turn, and
 // their fp64 sums are added in a fixed order (across the wave's groups, then
 // across waves). Then the other sums, a lane group each, items in order; then
 // the keys seen once, a lane group each. Which block takes which unit changes
@@ -2308,9 +2308,16 @@ __global__ __launch_bounds__(kApplyThreads, ApplyCfg<M>::WAVES) void k_put_apply
 
   // ---- long units ----
   const uint32_t nl = (uint32_t)(a.ctrl->unit_multi >> 32);
+  // Where there are more of them than blocks, lane groups take the shorter ones
+  // with the other sums: a block each took 217 us for 1M lookups of 65,536 keys
+  // (dim 4, about 16 items a key; with lane groups 123, the earlier single kernel
+  // 134) and 69 for 213k of 16,384 (43, 34). Up to 64 items each against 32 is
+  // 120 us and 141 for 1M of 32,768 keys, 59 and 51 for 213k of 4096.
+  const uint32_t lane_max = nl > 8u * gridDim.x ? 64u : nl > gridDim.x ? 32u : 0u;
   for (uint32_t e = blockIdx.x; e < nl; e += gridDim.x) {
     const uint4 t = a.units.lng[e];
     const uint32_t n = t.y & ~kUnitFresh;
+    if (n <= lane_max) continue;  // (block-uniform)
     uint32_t row = 0;
     float* wr = nullptr;
     if (gid == 0) {
@@ -2345,8 +2352,9 @@ __global__ __launch_bounds__(kApplyThreads, ApplyCfg<M>::WAVES) void k_put_apply
   // ---- other sums ----
   const uint32_t groups = gridDim.x * NG, g0 = blockIdx.x * NG + gid;
   const uint32_t nm = (uint32_t)a.ctrl->unit_multi;
-  for (uint32_t e = g0; e < nm; e += groups) {
-    const uint4 t = a.units.multi[e];
+  for (uint32_t e = g0; e < nm + (lane_max != 0u ? nl : 0u); e += groups) {
+    const uint4 t = e < nm ? a.units.multi[e] : a.units.lng[e - nm];
+    if (e >= nm && (t.y & ~kUnitFresh) > lane_max) continue;
     const uint32_t row = unit_row(a.idx, t.x, (t.y & kUnitFresh) != 0);
     float* wr = store.wptr(row);
     load_row(row, wr);

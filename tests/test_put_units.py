@@ -10,6 +10,7 @@ updated rows and accumulators within the harness's bound.
 """
 import numpy as np
 import pytest
+import torch
 
 from oracle import oracle as O
 from paper_2504_01506_amd import mlkv
@@ -58,6 +59,46 @@ def test_sums_of_every_length_class(dim, dedup):
     pr.compare_rows()
     log(f"[units] dim {dim} {dedup} stats={pr.stats}")
     pr.close()
+
+
+@pytest.mark.parametrize("dim", [4, 40, 130])
+@pytest.mark.parametrize("n,nkeys", [(140_000, 4096), (280_000, 16_384), (600_000, 32_768)])
+def test_more_long_sums_than_blocks(dim, n, nkeys):
+    # every key in about n / nkeys put tiles: lane groups add the sums of up
+    # to 32 items (64 with many more), blocks the others
+    rng = np.random.default_rng(n + dim)
+    pr = Pair(dim, nkeys + 10)
+    keys = _spread(np.concatenate([np.arange(nkeys), rng.integers(0, nkeys, size=n - nkeys)]))
+    pr.get(_spread(np.arange(nkeys)))
+    pr.put(keys, rng.normal(0, 0.01, size=(n, dim)).astype(np.float32), 0.01, 1e-8)
+    pr.put_sgd(keys, rng.normal(0, 0.01, size=(n, dim)).astype(np.float32), 0.05)
+    pr.compare_rows()
+    pr.close()
+
+
+def test_many_long_sums_take_no_longer_than_more_short_ones():
+    n, us = 1 << 20, {}
+    t = mlkv.Table(4, 1 << 18)
+    t.reserve(n)
+    for s in range(0, 1 << 18, 1 << 16):
+        t.get(torch.arange(s, s + (1 << 16), device="cuda"), None)
+    g = torch.full((n, 4), 1e-3, device="cuda")
+    for nkeys in (1 << 16, 1 << 18):  # about 16 and 4 put tiles a key
+        ts = []
+        for _ in range(8):
+            keys = torch.randint(0, nkeys, (n,), device="cuda")
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            t.put_grad(keys, g, 0.01, 1e-8)
+            b.record()
+            torch.cuda.synchronize()
+            ts.append(a.elapsed_time(b) * 1e3)
+        us[nkeys] = float(np.median(ts))
+    assert t.sync() == mlkv.MLKV_OK
+    t.close()
+    log(f"[units] 1M lookups, us by keys: {us}")
+    assert us[1 << 16] < 1.35 * us[1 << 18]  # 217 against 129 us with a block for each long sum; 124 against 125
 
 
 @pytest.mark.parametrize("dim", [1, 4, 30, 130])
