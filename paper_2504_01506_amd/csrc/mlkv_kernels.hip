@@ -2017,12 +2017,17 @@ __device__ __forceinline__ void upsert_sorted(IP it, SP seg, uint32_t S, const P
                                 [&](uint32_t s) { return it[seg[s0 + s + 1] - 1]; });
 }
 
-// Partition larger than the block's LDS share: the same steps on a global
-// scratch area (bitonic sort in place).
+// Partition of more items than the block groups in LDS (a few keys with an item
+// in nearly every put tile): the items are sorted in place, in the block's LDS
+// if kSortLds hold them, else in a global scratch area (a put of 1M lookups of
+// 1024 keys, dim 64: 384 us with every sort in the scratch area, 243 so).
+constexpr int kSortLds = 8192;
+static_assert(8 * (kSortLds + kGroupThreads / 2) <= (int)GroupLds::w64, "the sorted items and s_to fit beside s_w and s_misc");
 template <bool kUpsert, int VEC, bool kClk>
 __device__ __forceinline__ void group_partition_global(const PutGroupArgs& a, const RowStore& store, uint32_t p, uint32_t mp, uint32_t* s_w,
-                                                      uint64_t* s_misc, uint32_t* s_to) {
+                                                      uint64_t* s_misc, uint64_t* s_it) {
   constexpr int NT = kGroupThreads;
+  uint32_t* s_to = reinterpret_cast<uint32_t*>(s_it + kSortLds);
   uint32_t P2 = 1;
   while (P2 < mp) P2 <<= 1;
   if (threadIdx.x == 0) {
@@ -2037,26 +2042,29 @@ __device__ __forceinline__ void group_partition_global(const PutGroupArgs& a, co
     if (threadIdx.x == 0) atomicCAS(&a.ctrl->latched, 0, -4);
     return;
   }
-  uint64_t* it = a.spill + base;
   uint32_t* seg = reinterpret_cast<uint32_t*>(a.spill + base + P2);  // [mp + 1], then [mp] segments of the items
   uint32_t* sid = seg + mp + 1;
-  uint32_t dst = 0;
-  for (int t0 = 0; t0 < a.ntiles; t0 += NT) {
-    const int t = t0 + (int)threadIdx.x;
-    const uint32_t mt = t < a.ntiles ? a.meta[(size_t)p * a.ntiles + t] : 0u;
-    const uint32_t off = mt & 0xFFFFu, cnt = mt >> 16;
-    uint32_t tot;
-    const uint32_t pre = block_exclusive_scan<NT>(cnt, s_w, &tot);
-    for (uint32_t j = 0; j < cnt; ++j) it[dst + pre + j] = a.items[(size_t)t * kPutTile + off + j];
-    dst += tot;
-  }
-  for (uint32_t j = mp + threadIdx.x; j < P2; j += NT) it[j] = ~0ull;
-  __syncthreads();
-  block_bitonic_sort<NT>(it, P2);
-  const uint32_t S = encode_segments<NT>(it, mp, seg, sid, s_w);
-  if constexpr (kUpsert) upsert_sorted<NT, VEC, kClk>(it, seg, S, a, store);
-  else units_of_sorted<NT>(it, seg, sid, S, a.units, a.ctrl, reinterpret_cast<unsigned long long*>(s_misc),
-                           reinterpret_cast<uint32_t*>(s_misc + 2), s_to);
+  auto group = [&](uint64_t* it) {
+    uint32_t dst = 0;
+    for (int t0 = 0; t0 < a.ntiles; t0 += NT) {
+      const int t = t0 + (int)threadIdx.x;
+      const uint32_t mt = t < a.ntiles ? a.meta[(size_t)p * a.ntiles + t] : 0u;
+      const uint32_t off = mt & 0xFFFFu, cnt = mt >> 16;
+      uint32_t tot;
+      const uint32_t pre = block_exclusive_scan<NT>(cnt, s_w, &tot);
+      for (uint32_t j = 0; j < cnt; ++j) it[dst + pre + j] = a.items[(size_t)t * kPutTile + off + j];
+      dst += tot;
+    }
+    for (uint32_t j = mp + threadIdx.x; j < P2; j += NT) it[j] = ~0ull;
+    __syncthreads();
+    block_bitonic_sort<NT>(it, P2);
+    const uint32_t S = encode_segments<NT>(it, mp, seg, sid, s_w);
+    if constexpr (kUpsert) upsert_sorted<NT, VEC, kClk>(it, seg, S, a, store);
+    else units_of_sorted<NT>(it, seg, sid, S, a.units, a.ctrl, reinterpret_cast<unsigned long long*>(s_misc),
+                             reinterpret_cast<uint32_t*>(s_misc + 2), s_to);
+  };
+  if (P2 <= (uint32_t)kSortLds) group(s_it);
+  else group(a.spill + base);
 }
 
 // The verdict of a put call (see call_verdict); a put whose probe ran ahead
@@ -2109,8 +2117,7 @@ __global__ __launch_bounds__(kGroupThreads, 8) void k_put_group(const PutGroupAr
   const PutVerdict v = put_verdict<NT>(a.ctrl, a.epoch, a.capacity, aa.tile_cnt, ntiles, s_w64);
 
   if (!v.err && mp > (uint32_t)kRedCap) {
-    group_partition_global<kUpsert, VEC, kClk>(a, store, p, mp, s_w, reinterpret_cast<uint64_t*>(s_raw + L::misc),
-                                               reinterpret_cast<uint32_t*>(s_raw + L::hcnt));
+    group_partition_global<kUpsert, VEC, kClk>(a, store, p, mp, s_w, reinterpret_cast<uint64_t*>(s_raw + L::misc), s_it);
   } else if (!v.err && mp > 0) {
     // ---- gather the partition's items into LDS, tile order ----
     uint32_t dst = 0;

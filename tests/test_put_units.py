@@ -144,3 +144,22 @@ def test_a_table_loaded_from_equally_full_tiles(how):
         pr.upsert(keys, rows)
     pr.compare_rows()
     pr.close()
+
+
+@pytest.mark.parametrize("how", ["put", "upsert"])
+@pytest.mark.parametrize("n,nkeys", [(1 << 20, 700), (8_600 * TILE, 3)])
+def test_partitions_larger_than_a_block_groups(how, n, nkeys):
+    # keys with an item in nearly every put tile: partitions of 1024 to 8192
+    # items are sorted in LDS, of 8600 in the scratch area
+    rng = np.random.default_rng(nkeys)
+    pr = Pair(1, nkeys + 10)
+    keys = _spread(rng.integers(0, nkeys, size=n))
+    rows = rng.normal(0, 0.01, size=(n, 1)).astype(np.float32)
+    if how == "put":
+        pr.put(keys, rows, 0.01, 1e-8)
+        pr.put(keys, rows, 0.01, 1e-8)
+    else:
+        pr.upsert(keys, rows)
+        pr.upsert(keys[::-1].copy(), rows)
+    pr.compare_rows()
+    pr.close()
