@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBPS = 8000.0
 METRIC = "embedding get+put keys/sec and achieved HBM GB/s (% of peak), 1 MI355X"
 METRIC_KV = "key-value operations/sec, 50% get / 50% put, 1 MI355X"
-KERNELS = ("get_probe", "get_rows", "put_probe", "put_reduce", "rsort_count", "rsort_scatter",
+KERNELS = ("get_probe_gather", "assign_new", "put_probe", "put_reduce", "rsort_count", "rsort_scatter",
            "rsort_reduce")
 
 
@@ -49,10 +49,10 @@ def kernel_bytes(n, U, M, D, dedup="hash"):
     reduce's bytes are rsort_reduce's; the sort passes move scratch only."""
     b = {
         # keys in, one index entry (8 B tag + 4 B row) per distinct key
-        "get_probe": 8 * n + 12 * U,
+        "get_probe_gather": 8 * n + 12 * U,
         # distinct existing rows read, output rows written; new rows, their
         # accumulators, index tag + row id
-        "get_rows": 4 * D * (U - M) + 4 * D * n + (4 * D + 16) * M,
+        "assign_new": 4 * D * (U - M) + 4 * D * n + (4 * D + 16) * M,
         # keys in, one index entry per distinct key
         "put_probe": 8 * n + 12 * U,
         # gradient rows in, distinct rows read and written, accumulators read
@@ -71,8 +71,8 @@ def kernel_bytes_kv(nr, Ur, nw, Uw, D, dedup="hash"):
     existing keys, then a put of nw values over Uw distinct existing keys
     (the last value of each key is written)."""
     b = {
-        "get_probe": 8 * nr + 12 * Ur,
-        "get_rows": 4 * D * Ur + 4 * D * nr,
+        "get_probe_gather": 8 * nr + 12 * Ur,
+        "assign_new": 4 * D * Ur + 4 * D * nr,
         "put_probe": 8 * nw + 12 * Uw,
         # the winning value of each key in, its row written
         "put_reduce": 8 * D * Uw,

@@ -290,14 +290,16 @@ int mlkv_read_rows(mlkv_table *t, const int64_t *d_rows, int64_t n, float *d_row
 int mlkv_read_staleness(mlkv_table *t, const int64_t *d_rows, int64_t n, uint32_t *d_out, void *hip_stream);
 
 /* ---- per-kernel timing (benchmarks) ----
- * The library runs MLKV_NUM_KERNELS kernels: 0 get_probe and
- * 1 get_rows for mlkv_get, mlkv_get_bounded and mlkv_lookahead;
- * 2 put_probe and 3 put_reduce (its grouping and update launches together)
- * for mlkv_put_grad, mlkv_put_grad_sgd and mlkv_put; 4 tier_mark, 5 tier_plan
- * and 6 tier_copy for mlkv_lookahead on a tiered table; with radix dedup
+ * The library runs MLKV_NUM_KERNELS kernels: 0 get_probe_gather and
+ * 1 assign_new for mlkv_get, mlkv_get_bounded and mlkv_lookahead (rows wider
+ * than 16 floats and batches of some sizes are copied out in assign_new, not in
+ * get_probe_gather: a get's time is both); 2 put_probe and 3 put_reduce (its
+ * grouping and update launches together) for mlkv_put_grad,
+ * mlkv_put_grad_sgd and mlkv_put; 4 tier_mark, 5 tier_plan and 6 tier_copy for
+ * mlkv_lookahead on a tiered table; with radix dedup
  * (mlkv_set_dedup) a put runs 2 put_probe, then 7 rsort_count and
- * 8 rsort_scatter once per radix pass, then 9 rsort_reduce. While enabled, HIP events are recorded on
- * the call's stream before and after every launch. mlkv_profile_read waits
+ * 8 rsort_scatter once per radix pass, then 9 rsort_reduce. While enabled, HIP
+ * events are recorded on the call's stream before and after every launch. mlkv_profile_read waits
  * for the recorded launches, writes per-kernel sums of their durations (ms)
  * and launch counts into the host arrays total_ms[MLKV_NUM_KERNELS] and
  * launches[MLKV_NUM_KERNELS], and forgets them. */

@@ -1038,7 +1038,7 @@ int mlkv_profile_read(mlkv_table* t, double* total_ms, int64_t* launches) {
 }
 
 const char* mlkv_kernel_name(int kernel) {
-  static const char* names[K_COUNT] = {"get_probe", "get_rows", "put_probe", "put_reduce",
+  static const char* names[K_COUNT] = {"get_probe_gather", "assign_new", "put_probe", "put_reduce",
                                        "tier_mark", "tier_plan", "tier_copy", "rsort_count",
                                        "rsort_scatter", "rsort_reduce"};
   return (kernel >= 0 && kernel < K_COUNT) ? names[kernel] : nullptr;

@@ -71,6 +71,15 @@ def test_host_side_validation_without_a_gpu(lib):
     lib.mlkv_close(None)  # no-op
 
 
+def test_kernel_names(lib):
+    # callers match timings by these names
+    from paper_2504_01506_amd import mlkv
+    names = [mlkv.mlkv_kernel_name(k) for k in range(mlkv.MLKV_NUM_KERNELS)]
+    assert names == ["get_probe_gather", "assign_new", "put_probe", "put_reduce", "tier_mark", "tier_plan",
+                     "tier_copy", "rsort_count", "rsort_scatter", "rsort_reduce"]
+    assert lib.mlkv_kernel_name(-1) is None and lib.mlkv_kernel_name(mlkv.MLKV_NUM_KERNELS) is None
+
+
 def test_single_hip_runtime_in_process(lib):
     from paper_2504_01506_amd import mlkv
     rts = mlkv.hip_runtimes_loaded()
