@@ -41,18 +41,20 @@ METRIC = "embedding get+put keys/sec and achieved HBM GB/s (% of peak), 1 MI355X
 METRIC_KV = "key-value operations/sec, 50% get / 50% put, 1 MI355X"
 KERNELS = ("get_probe_gather", "assign_new", "put_probe", "put_reduce", "rsort_count", "rsort_scatter",
            "rsort_reduce")
+# timed as one: which of the two copies the rows depends on their width and the batch
+GET_KERNELS = ("get_probe_gather", "assign_new")
 
 
 def kernel_bytes(n, U, M, D, dedup="hash"):
     """Algorithmic bytes each kernel must move for one batch: n lookups, U
-    distinct keys of which M are new, rows of D fp32. With radix dedup the
-    reduce's bytes are rsort_reduce's; the sort passes move scratch only."""
+    distinct keys of which M are new, rows of D fp32; "get" stands for the two
+    kernels of a get. With radix dedup the reduce's bytes are rsort_reduce's;
+    the sort passes move scratch only."""
     b = {
-        # keys in, one index entry (8 B tag + 4 B row) per distinct key
-        "get_probe_gather": 8 * n + 12 * U,
+        # keys in, one index entry (8 B tag + 4 B row) per distinct key;
         # distinct existing rows read, output rows written; new rows, their
         # accumulators, index tag + row id
-        "assign_new": 4 * D * (U - M) + 4 * D * n + (4 * D + 16) * M,
+        "get": 8 * n + 12 * U + 4 * D * (U - M) + 4 * D * n + (4 * D + 16) * M,
         # keys in, one index entry per distinct key
         "put_probe": 8 * n + 12 * U,
         # gradient rows in, distinct rows read and written, accumulators read
@@ -71,13 +73,28 @@ def kernel_bytes_kv(nr, Ur, nw, Uw, D, dedup="hash"):
     existing keys, then a put of nw values over Uw distinct existing keys
     (the last value of each key is written)."""
     b = {
-        "get_probe_gather": 8 * nr + 12 * Ur,
-        "assign_new": 4 * D * Ur + 4 * D * nr,
+        "get": 8 * nr + 12 * Ur + 4 * D * Ur + 4 * D * nr,
         "put_probe": 8 * nw + 12 * Uw,
         # the winning value of each key in, its row written
         "put_reduce": 8 * D * Uw,
     }
     return radix_bytes(b) if dedup == "radix" else b
+
+
+def kernel_info(prof, nbytes):
+    """Per kernel its mean time and launches, and its bytes and rate where
+    nbytes (totals over the launches) has any; "get" is the two kernels of a
+    get as one. prof: kernel -> (ms in all, launches)."""
+    prof = {k: prof[k] for k in KERNELS if prof[k][1]}
+    if all(k in prof for k in GET_KERNELS):
+        prof["get"] = (sum(prof[k][0] for k in GET_KERNELS), prof[GET_KERNELS[0]][1])
+    info = {}
+    for k, (ms, cnt) in prof.items():
+        info[k] = {"avg_us": round(ms * 1e3 / cnt, 3), "launches": cnt}
+        if k in nbytes:
+            info[k]["alg_bytes_per_launch"] = int(nbytes[k] / cnt)
+            info[k]["gbps"] = round(nbytes[k] / (ms * 1e-3) / 1e9, 1)
+    return info
 
 
 def source_digest():
@@ -483,17 +500,9 @@ def main():
     mlkv.mlkv_profile_enable(t.h, False)
     ms_prof = ev2.elapsed_time(ev3) / args.steps
     assert t.sync() == mlkv.MLKV_OK
-    kinfo = {}
+    kinfo = kernel_info(prof, {k: sum(bs[k] for bs in bytes_steps[first:first + args.steps])
+                               for k in bytes_steps[first]})
     host_link = None
-    for kname in KERNELS:
-        tot_ms, cnt = prof[kname]
-        b = sum(bytes_steps[s].get(kname, 0) for s in timed)
-        if cnt == 0:
-            continue
-        avg_us = tot_ms * 1e3 / cnt
-        kinfo[kname] = {"avg_us": round(avg_us, 3), "launches": cnt,
-                        "alg_bytes_per_launch": int(b / cnt),
-                        "gbps": round(b / cnt / (avg_us * 1e-6) / 1e9, 1)}
     if tiered and prof["tier_copy"][1] > 0:
         # the steps' lookahead copies: rows in over the host link, dirty rows back
         tier1 = t.cache_stats()
