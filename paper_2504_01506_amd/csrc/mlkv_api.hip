@@ -244,7 +244,7 @@ PutUnits units_of(const mlkv_table* t) {
   u.lng = u.multi + t->ws_n;
   u.single = reinterpret_cast<uint64_t*>(u.lng + t->ws_n / kLongNarrow + 1);
   u.mitem = reinterpret_cast<uint32_t*>(u.single + t->ws_n);
-  u.long_over = kLongNarrow;
+  u.long_over = t->dim <= 32 ? kLongNarrow : kLongWide;
   return u;
 }
 

@@ -290,10 +290,12 @@ struct TierArgs {
 // shorter than that), at any alignment. A map of one float per lane and a
 // whole wave per row, which widths that are no multiple of four (and buffers
 // off 16 bytes) took before, left most lanes idle: two steps of 106,496
-// lookups at dim 10 took 849 us and take 137. Not fewer than four lanes: with
-// one per row of dim 4 a block has 1024 lane groups, which cut nearly every
-// segment into pieces that one of them adds up (two steps of 194,468 lookups
-// 243 us against 152).
+// lookups at dim 10 took 849 us and take 137. Not fewer than four lanes, though
+// rows of dim 4 leave three of them idle: with one, a block has 1024 lane groups
+// for the in-tile sums of hot keys and a wave holds 64 sums of different
+// lengths. Put of 4096 / 65k / 194k / 1M lookups at dim 4 (Zipf 1.1) with four
+// lanes, two and one: 29 / 37 / 46 / 154 us, 31 / 40 / 48 / 154 and 34 / 44 / 50
+// / 155; uniform keys 22 / 29 / 44 / 166, 23 / 29 / 44 / 168 and 22 / 29 / 44 / 165.
 using MapD3 = RowMap<1, 4, 1>;      // dim <= 3
 using MapD16 = RowMap<4, 4, 1>;     // dim <= 16
 using MapD32 = RowMap<4, 8, 1>;     // dim <= 32

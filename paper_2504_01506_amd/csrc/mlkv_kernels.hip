@@ -1,6 +1,6 @@
-// HIP kernels of libmlkv for gfx950 (MI355X): hash-index probe, row gather,
-// in-batch dedup by MSD radix partition + LDS sort + run-length encoding, and
-// the fp64 segment-reduce fused with the row-wise Adagrad scatter-update.
+// HIP kernels of libmlkv for gfx950 (MI355X): hash-index probe, row copy, row
+// assignment of new keys, in-batch dedup by hash partition and LDS grouping (or
+// a radix sort), and the fp64 sums with the row-wise Adagrad or SGD update.
 //
 // The kernels that move rows are templates over a row map. This file is
 // compiled once for each map M with MLKV_MAP=M (that map's kernels and their
@@ -53,27 +53,6 @@ __device__ __forceinline__ void store_vec_nt(float* p, const typename VecT<VEC>:
         reinterpret_cast<Words4*>(p));
   } else {
     __builtin_nontemporal_store(v, p);
-  }
-}
-
-// Loads W consecutive 32-bit words (W = 1, 2, 4 or 8; 16-byte aligned when W >= 4).
-template <int W>
-__device__ __forceinline__ void load_words(uint32_t* dst, const uint32_t* src) {
-  if constexpr (W >= 4) {
-#pragma unroll
-    for (int h = 0; h < W / 4; ++h) {
-      const uint4 v = reinterpret_cast<const uint4*>(src)[h];
-      dst[4 * h] = v.x;
-      dst[4 * h + 1] = v.y;
-      dst[4 * h + 2] = v.z;
-      dst[4 * h + 3] = v.w;
-    }
-  } else if constexpr (W == 2) {
-    const uint2 v = *reinterpret_cast<const uint2*>(src);
-    dst[0] = v.x;
-    dst[1] = v.y;
-  } else {
-    dst[0] = *src;
   }
 }
 
@@ -681,8 +660,10 @@ __device__ __forceinline__ void assign_new(const AssignArgs& a, const RowStore& 
       for (uint32_t u = 0; u < kSortPT; ++u) v[u] = newlist[s_sat[threadIdx.x + u * NT]].key;
       // the cut points: the samples of rank g S / G and (g + 1) S / G of the
       // sorted sample (with fewer new keys than samples a key is sampled more
-      // than once, and equal cut points give an empty range); eight sample
-      // gaps per range keep the largest range near twice the mean
+      // than once, and equal cut points give an empty range): at 512 ranges
+      // eight sample gaps a range in a put, four in a get. The largest range is
+      // two to three times the mean: of a put's ranges 41 to 46 of 512 hold more
+      // than kRangeCap keys at 2^20 new ones, nearly all from 1.57M on
       sort_keys<NT, kSortPT>(v, s_buf, s_buf + S);
       {
         const uint32_t r1 = (uint32_t)((uint64_t)g * S / G), r2 = (uint32_t)((uint64_t)(g + 1) * S / G);
@@ -1007,7 +988,8 @@ __device__ __forceinline__ void copy_rows(const GetRowsArgs& a) {
     for (int u = 0; u < kCopyUnits; ++u) {
       const uint32_t e = rem + (uint32_t)u * kCopyThreads + threadIdx.x;  // < Q + PER
       // e / Q by magic = ceil(2^32 / Q): exact, since e * (magic * Q - 2^32) < (Q + PER) * Q < 2^32
-      const uint32_t d = Q == 1 ? e : (uint32_t)(((uint64_t)e * a.magic) >> 32);
+      // (Q > 1: the probe kernel copies rows of one unit)
+      const uint32_t d = (uint32_t)(((uint64_t)e * a.magic) >> 32);
       p[u] = p0 + d;
       const int c = (int)(e - d * Q) * VEC;
       col[u] = VEC == 1 || c < D - VEC ? c : D - VEC;  // the last unit of a row: its last four columns
@@ -2932,7 +2914,6 @@ hipError_t launch_put(const PutArgs& a, hipStream_t st, const LaunchHook& hook, 
   g.values = a.grads;
   g.clock = a.clock;
   g.units = a.units;
-  g.units.long_over = a.D <= 32 ? kLongNarrow : kLongWide;
   g.ctrl = a.ctrl;
   g.epoch = a.epoch;
   g.capacity = a.capacity;

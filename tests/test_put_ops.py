@@ -82,10 +82,10 @@ def test_full_size_dlrm_sgd_and_put():
 
 @pytest.mark.parametrize("dim,bound", [(4, None), (64, None), (130, None), (16, 1)])
 def test_upsert_of_present_keys_takes_the_last_position_across_tiles(dim, bound):
-    # a put whose partitions hold no key new in the call writes each row from
-    # its key's last position without grouping; a call with a few new keys
-    # mixes such partitions with grouped ones. Zipf repeats put one key in
-    # many tiles, so the last position is found across tiles.
+    # an upsert finds each key's last position in an LDS hash of its partition
+    # and writes the rows of present keys there, those of new keys where they
+    # are assigned; the second call has a few new keys. Zipf repeats put one
+    # key in many tiles, so the last position is found across tiles.
     rng = np.random.default_rng(dim + 7)
     nkeys, n = 40_000, 300_000
     pr = Pair(dim, 60_000, staleness_bound=bound)
