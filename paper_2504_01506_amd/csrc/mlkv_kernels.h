@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <atomic>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -326,6 +327,19 @@ hipError_t launch_rsort_pass(const RsSrc& src, uint32_t cap, int shift, int bits
 // capture would load (and allocate) there.
 hipError_t load_code(int D);
 hipError_t load_tier_code();
+// Loads the code object of `kernel` on the current device, unless `on` (a bit
+// for each of the first 64 devices) says that was done.
+inline hipError_t load_once(std::atomic<uint64_t>& on, const void* kernel) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+  if ((on.load(std::memory_order_relaxed) & bit) != 0) return hipSuccess;
+  hipFuncAttributes f;
+  e = hipFuncGetAttributes(&f, kernel);
+  if (e == hipSuccess) on.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
 template <class M>
 hipError_t load_map_code();
 template <class M>

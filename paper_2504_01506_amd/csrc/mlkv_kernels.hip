@@ -2785,8 +2785,8 @@ hipError_t launch_put_apply_t(const PutArgs& a, const PutApplyArgs& u, hipStream
 
 template <class M>
 hipError_t load_map_code() {
-  hipFuncAttributes f;
-  return hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_put_apply<M, false>));
+  static std::atomic<uint64_t> on{0};
+  return load_once(on, reinterpret_cast<const void*>(k_put_apply<M, false>));
 }
 
 #ifdef MLKV_MAP
@@ -2813,8 +2813,8 @@ static hipError_t dispatch_map(int D, F f) {
 }
 
 hipError_t load_code(int D) {
-  hipFuncAttributes f;
-  const hipError_t e = hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_lookup));
+  static std::atomic<uint64_t> on{0};
+  const hipError_t e = load_once(on, reinterpret_cast<const void*>(k_lookup));
   return e != hipSuccess ? e : dispatch_map(D, [](auto m) { return load_map_code<decltype(m)>(); });
 }
 

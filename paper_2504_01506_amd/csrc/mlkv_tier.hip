@@ -207,8 +207,8 @@ __global__ __launch_bounds__(kCopyThreads) void k_tier_copy(const uint32_t* __re
 }
 
 hipError_t load_tier_code() {
-  hipFuncAttributes f;
-  return hipFuncGetAttributes(&f, reinterpret_cast<const void*>(k_tier_plan));
+  static std::atomic<uint64_t> on{0};
+  return load_once(on, reinterpret_cast<const void*>(k_tier_plan));
 }
 
 hipError_t launch_tier_lookahead(const TierArgs& a, hipStream_t st, const LaunchHook& hook) {
